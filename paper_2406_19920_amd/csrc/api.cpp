@@ -154,6 +154,7 @@ State state_in(const Plan &p, void *work, int op, int ncomp)
     b += align256(2 * (size_t)COMPAT_SLOTS * sizeof(double));
     st.red = reinterpret_cast<double *>(b);
     st.red_count = red_doubles(p, op, ncomp);
+    st.upd_region = p.desc.precision == IBS_FP64 ? 0 : update_region(p, op == IBS_OP_POISSON ? 1 : ncomp);
     b += align256(st.red_count * sizeof(double));
     st.bmax = reinterpret_cast<double *>(b);
     b += align256((size_t)STATE_JOBS * BMAX_SLOTS * sizeof(double));
@@ -173,48 +174,90 @@ static double total_cells(const JobSet &js, const Plan &p)
     return n;
 }
 
+// Algorithmic flops of one transform of the jobs: 2.5 n log2 n per line of a
+// fast one, 2 n^2 dense, n^2 folded.
+template <typename Set> static double transform_flops(const Plan &p, const Set &js, bool z_axis)
+{
+    const int n = z_axis ? p.nz : p.nx;
+    const bool folds = z_axis ? z_folds(p) : x_folds(p);
+    double f = 0;
+    for (int q = 0; q < js.n; ++q) {
+        const bool fast = z_axis ? p.fz[js.j[q].zk] : p.fx[js.j[q].xk];
+        f += (fast ? 2.5 * std::log2((double)n) : (folds ? 1.0 : 2.0) * n) * (double)p.nz * js.j[q].rows * p.nx;
+    }
+    return f;
+}
+
+// The jobs of a set for which pick(job) holds.
+template <typename Set, typename F> static Set jobs_where(const Set &all, F pick)
+{
+    Set s{};
+    for (int q = 0; q < all.n; ++q)
+        if (pick(all.j[q])) s.j[s.n++] = all.j[q];
+    return s;
+}
+
 // The five FP64 stages.  js.j[q].in holds the right-hand side; W[q] is the
-// job's scratch field and X[q] its output.
+// job's scratch field and X[q] its output.  A job whose x and z transforms
+// are both fast ones works in place on X (its stages after the first touch
+// one field, which for fields up to the 256 MB Infinity Cache then stays
+// there); the dense products need a second field and alternate X and W.
 static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, double *const *X,
                                           const State &st, bool poisson, hipStream_t s)
 {
     hipError_t e;
     const double cells = total_cells(js, p);
-    // matrix-core flops per cell: 2n for the plain transform, n folded
-    const bool fx = x_folds(p), fz = z_folds(p);
-    const double xflop = (fx ? 1.0 : 2.0) * p.nx * cells, zflop = (fz ? 1.0 : 2.0) * p.nz * cells;
     const double rw = 16.0 * cells;
-    const double *xb_f[NUM_XK], *xb_i[NUM_XK];
+    const double *xb[2][NUM_XK], *za[2][NUM_XK];   // dense matrices: forward, inverse
     for (int k = 0; k < NUM_XK; ++k) {
-        xb_f[k] = blob_ptr(p, p.lay.bx_fwd[k]);
-        xb_i[k] = blob_ptr(p, p.lay.bx_inv[k]);
+        xb[0][k] = blob_ptr(p, p.lay.bx_fwd[k]);
+        xb[1][k] = blob_ptr(p, p.lay.bx_inv[k]);
+        za[0][k] = blob_ptr(p, p.lay.az_fwd[k]);
+        za[1][k] = blob_ptr(p, p.lay.az_inv[k]);
     }
-    const double *za_f[NUM_XK], *za_i[NUM_XK];
-    for (int k = 0; k < NUM_XK; ++k) {
-        za_f[k] = blob_ptr(p, p.lay.az_fwd[k]);
-        za_i[k] = blob_ptr(p, p.lay.az_inv[k]);
-    }
+    bool in_place[4];
+    for (int q = 0; q < js.n; ++q) in_place[q] = p.fx[js.j[q].xk] && p.fz[js.j[q].zk];
+    // in, out of every job for a stage; b: the right-hand side
+    enum Buf { RHS, PING, PONG };   // PING: X; PONG: W, or X for an in-place job
+    auto bind = [&](Buf in, Buf out) {
+        for (int q = 0; q < js.n; ++q) {
+            auto at = [&](Buf f) { return f == PONG && !in_place[q] ? W[q] : X[q]; };
+            if (in != RHS) js.j[q].in = at(in);
+            js.j[q].out = at(out);
+        }
+    };
     auto xform = [&](bool inverse) {
-        return fx ? launch_xfold_f64(js, p, inverse, s)
-                  : launch_xgemm_f64(js, p.nz, p.nx, p.nx, inverse ? xb_i : xb_f, s);
+        const JobSet fast = jobs_where(js, [&](const FieldJob &j) { return p.fx[j.xk]; });
+        const JobSet rest = jobs_where(js, [&](const FieldJob &j) { return !p.fx[j.xk]; });
+        if (fast.n)
+            if (hipError_t r = launch_fft_f64(fast, p, false, inverse, s); r != hipSuccess) return r;
+        if (!rest.n) return hipSuccess;
+        return x_folds(p) ? launch_xfold_f64(rest, p, inverse, s)
+                          : launch_xgemm_f64(rest, p.nz, p.nx, p.nx, xb[inverse], s);
     };
     auto zform = [&](bool inverse) {
-        return fz ? launch_zfold_f64(js, p, inverse, s)
-                  : launch_zgemm_f64(js, p.nz, p.nz, p.nx, inverse ? za_i : za_f, s);
+        const JobSet fast = jobs_where(js, [&](const FieldJob &j) { return p.fz[j.zk]; });
+        const JobSet rest = jobs_where(js, [&](const FieldJob &j) { return !p.fz[j.zk]; });
+        if (fast.n)
+            if (hipError_t r = launch_fft_f64(fast, p, true, inverse, s); r != hipSuccess) return r;
+        if (!rest.n) return hipSuccess;
+        return z_folds(p) ? launch_zfold_f64(rest, p, inverse, s)
+                          : launch_zgemm_f64(rest, p.nz, p.nz, p.nx, za[inverse], s);
     };
-    for (int q = 0; q < js.n; ++q) js.j[q].out = W[q];
+    const double xflop = transform_flops(p, js, false), zflop = transform_flops(p, js, true);
+    bind(RHS, PONG);
     e = timed(p, PK_XGEMM, xflop, rw, s, [&] { return xform(false); });
     if (e != hipSuccess) return hip_fail(e, "x forward");
-    for (int q = 0; q < js.n; ++q) { js.j[q].in = W[q]; js.j[q].out = X[q]; }
+    bind(PONG, PING);
     e = timed(p, PK_ZGEMM, zflop, rw, s, [&] { return zform(false); });
     if (e != hipSuccess) return hip_fail(e, "z forward");
-    for (int q = 0; q < js.n; ++q) js.j[q].in = X[q];
+    bind(PING, PING);
     e = timed(p, PK_TRIDIAG, 20.0 * cells, rw, s, [&] { return launch_tridiag_f64(js, p, st, poisson, s); });
     if (e != hipSuccess) return hip_fail(e, "tridiagonal");
-    for (int q = 0; q < js.n; ++q) { js.j[q].in = X[q]; js.j[q].out = W[q]; }
+    bind(PING, PONG);
     e = timed(p, PK_ZGEMM, zflop, rw, s, [&] { return zform(true); });
     if (e != hipSuccess) return hip_fail(e, "z inverse");
-    for (int q = 0; q < js.n; ++q) { js.j[q].in = W[q]; js.j[q].out = X[q]; }
+    bind(PONG, PING);
     e = timed(p, PK_XGEMM, xflop, rw, s, [&] { return xform(true); });
     if (e != hipSuccess) return hip_fail(e, "x inverse");
     return IBS_OK;
@@ -253,9 +296,28 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
     hipError_t e;
     double cells = 0;
     for (int q = 0; q < ss.n; ++q) cells += (double)p.nz * ss.j[q].rows * p.nx;
-    // algorithmic flops per cell: 2n for the plain transform, n folded
-    const double xfl = (x_folds_split(p) ? 1.0 : 2.0) * p.nx * cells;
-    const double zfl = (z_folds_split(p) ? 1.0 : 2.0) * p.nz * cells;
+    const double xfl = transform_flops(p, ss, false), zfl = transform_flops(p, ss, true);
+    // a job whose transforms are both fast ones works in place on its second
+    // field; the dense products alternate between the two
+    float *D1[4];
+    for (int q = 0; q < ss.n; ++q) {
+        ss.j[q].slot = q;
+        D1[q] = p.fx[ss.j[q].xk] && p.fz[ss.j[q].zk] ? W2[q] : W1[q];
+    }
+    auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
+        const SplitSet fast = jobs_where(all, [&](const SplitJob &j) { return p.fx[j.xk]; });
+        const SplitSet rest = jobs_where(all, [&](const SplitJob &j) { return !p.fx[j.xk]; });
+        hipError_t r = fast.n ? launch_fft_x32(fast, p, st, inverse, in64, mode, pass, s) : hipSuccess;
+        if (r != hipSuccess || !rest.n) return r;
+        return launch_split_xgemm(rest, p, st, inverse, in64, mode, pass, s);
+    };
+    auto zform = [&](const SplitSet &all, bool inverse, int pass) {
+        const SplitSet fast = jobs_where(all, [&](const SplitJob &j) { return p.fz[j.zk]; });
+        const SplitSet rest = jobs_where(all, [&](const SplitJob &j) { return !p.fz[j.zk]; });
+        hipError_t r = fast.n ? launch_fft_z32(fast, p, st, inverse, pass, s) : hipSuccess;
+        if (r != hipSuccess || !rest.n) return r;
+        return launch_split_zgemm(rest, p, st, inverse, pass, s);
+    };
     JobSet js{};
     js.n = ss.n;
     void *info[4];
@@ -288,25 +350,25 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
         }
         for (int q = 0; q < ss.n; ++q) {
             ss.j[q].in = pass == 0 ? static_cast<const void *>(ss.j[q].b) : static_cast<const void *>(W2[q]);
-            ss.j[q].out = W1[q];
+            ss.j[q].out = D1[q];
         }
         e = timed(p, PK_XGEMM_SPLIT, xfl, (pass == 0 ? 12.0 : 8.0) * cells, s,
-                  [&] { return launch_split_xgemm(ss, p, st, false, pass == 0, 0, pass, s); });
+                  [&] { return xform(ss, false, pass == 0, 0, pass); });
         if (e != hipSuccess) return hip_fail(e, "x forward (split)");
-        for (int q = 0; q < ss.n; ++q) { ss.j[q].in = W1[q]; ss.j[q].out = W2[q]; }
-        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return launch_split_zgemm(ss, p, st, false, pass, s); });
+        for (int q = 0; q < ss.n; ++q) { ss.j[q].in = D1[q]; ss.j[q].out = W2[q]; }
+        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, false, pass); });
         if (e != hipSuccess) return hip_fail(e, "z forward (split)");
         for (int q = 0; q < ss.n; ++q) js.j[q].info = pass == 0 ? info[q] : nullptr;
         e = timed(p, PK_TRIDIAG_F32, 20.0 * cells, 8.0 * cells, s, [&] { return launch_tridiag_f32(js, p, st, poisson, pass, s); });
         if (e != hipSuccess) return hip_fail(e, "tridiagonal (refined)");
-        for (int q = 0; q < ss.n; ++q) { ss.j[q].in = W2[q]; ss.j[q].out = W1[q]; }
-        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return launch_split_zgemm(ss, p, st, true, pass, s); });
+        for (int q = 0; q < ss.n; ++q) { ss.j[q].in = W2[q]; ss.j[q].out = D1[q]; }
+        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, true, pass); });
         if (e != hipSuccess) return hip_fail(e, "z inverse (split)");
-        for (int q = 0; q < ss.n; ++q) ss.j[q].in = W1[q];
+        for (int q = 0; q < ss.n; ++q) ss.j[q].in = D1[q];
         const int mode = pass == 0 ? (xs32 ? 3 : 1) : (xs32 ? 4 : 2);
         const double ub = mode == 3 ? 8.0 : (mode == 1 ? 12.0 : (mode == 4 ? 16.0 : 20.0));
         e = timed(p, PK_UPDATE, xfl, ub * cells, s,
-                  [&] { return launch_split_xgemm(ss, p, st, true, false, mode, pass, s); });
+                  [&] { return xform(ss, true, false, mode, pass); });
         if (e != hipSuccess) return hip_fail(e, "x inverse + update (split)");
         // a one-pass solve has no error estimate: pass 0's check says so
         if (pass >= 1 || passes == 1) {
@@ -379,7 +441,7 @@ ibs_status solver_plan_upload(ibs_plan plan, void *dev_const, size_t bytes, void
     Plan *p = reinterpret_cast<Plan *>(plan);
     if (bytes < p->lay.total) { set_error("constant buffer smaller than const_bytes"); return IBS_ERR_WORKSPACE_TOO_SMALL; }
     if ((reinterpret_cast<uintptr_t>(dev_const) & 255u) != 0) { set_error("dev_const must be 256-byte aligned"); return IBS_ERR_INVALID_ARG; }
-    hipError_t e = hipMemcpyAsync(dev_const, p->blob.data(), p->lay.total, hipMemcpyHostToDevice,
+    hipError_t e = hipMemcpyAsync(dev_const, p->blob.data(), p->blob.size(), hipMemcpyHostToDevice,
                                   static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "solver_plan_upload");
     p->dev_const = dev_const;
@@ -750,7 +812,12 @@ ibs_status ibs_autotune(ibs_plan plan, void *scratch, size_t scratch_bytes, int3
     // apart
     constexpr int ROUNDS = 3;
     for (const Knob &k : knobs) {
-        if (!k.applies) { p.tune[k.id] = -1; continue; }
+        if (!k.applies) {
+            // walls: no tiles at all; a fast transform has one shape and
+            // reports the first choice
+            p.tune[k.id] = k.id == TUNE_XFOLD ? (p.fx[XK_P] && !p.wx ? 0 : -1) : (p.fz[XK_P] && !p.wz ? 0 : -1);
+            continue;
+        }
         std::vector<float> cand_ms(fold_candidates(), 0.f);
         for (int trial_no = 0; trial_no < ROUNDS * fold_candidates() && st == IBS_OK; ++trial_no) {
             const int round = trial_no / fold_candidates(), cand = trial_no % fold_candidates();

@@ -1,0 +1,25 @@
+// Line lengths the fast transforms (k_fft.h) are built for, as (N, R1, R2):
+// N = R1 R2, R1 points of real data in stage A, R2 complex ones in stage B.
+// Every multiple of 16 up to 256, and those above up to 512 whose factors
+// keep both stages within 32 real or 20 complex values per thread.  Stage A
+// takes the larger factor: real data hold half as many registers per point.
+#pragma once
+
+#define IBS_FFT_SIZES_32(X)                                                                              \
+    X(32, 8, 4) X(64, 8, 8) X(96, 12, 8) X(128, 16, 8) X(160, 16, 10) X(192, 16, 12) X(224, 16, 14)       \
+    X(256, 16, 16) X(288, 24, 12) X(320, 20, 16) X(352, 22, 16) X(384, 24, 16) X(416, 26, 16)             \
+    X(448, 28, 16) X(480, 30, 16) X(512, 32, 16)
+#define IBS_FFT_SIZES_16(X)                                                                              \
+    X(16, 4, 4) X(48, 8, 6) X(80, 10, 8) X(112, 14, 8) X(144, 16, 9) X(176, 16, 11) X(208, 16, 13)        \
+    X(240, 16, 15) X(336, 24, 14) X(400, 20, 20) X(432, 24, 18)
+
+// FP32 fields (refined path): lines of up to this length are transformed in
+// FP64 arithmetic, longer ones in FP32.  The three-term bfloat16 products
+// these transforms replace carry a line's result to within a few roundings
+// whatever its length; the FP32 butterflies lose about one per level.  From
+// 96 points on they come out ahead (refined solves at 128-416 points end 1.5
+// to 6 times closer to the FP64 solution), at 64 and below they fell behind
+// by 2, and FP64 arithmetic there costs nothing: the pass is bound by memory.
+namespace ibs {
+constexpr int FFT_F64_ARITH_MAX = 64;
+}

@@ -35,22 +35,26 @@ enum { XK_P = 0, XK_C = 1, XK_F = 2, NUM_XK = 3 };
 // Byte offsets of the tables inside the device constant blob.
 struct BlobLayout {
     size_t bx_fwd[NUM_XK], bx_inv[NUM_XK];   // x transform per x kind, B operand of C = A B,
-                                             // swizzled (unfolded x: nx % 32 != 0 or walls)
+                                             // swizzled (kinds with neither a fast nor a folded transform)
     size_t az_fwd[NUM_XK], az_inv[NUM_XK];   // z transform per z kind, A operand of C = A B,
-                                             // swizzled (unfolded z: nz % 32 != 0 or walls)
-    // folded transforms (n % 32 == 0): the two H x H factors (H = n/2)
+                                             // swizzled (likewise)
+    // folded transforms (x_folds(), z_folds()): the two H x H factors (H = n/2)
     size_t fx_fwd_c, fx_fwd_s, fx_inv_c, fx_inv_s;   // B-operand swizzle
     size_t fz_fwd_c, fz_fwd_s, fz_inv_c, fz_inv_s;   // A-operand swizzle
+    // fast transforms (complex, in the transform's arithmetic type): twiddle
+    // factors [k1][n2] forward / inverse, and with walls the rotations of the
+    // N/2 + 1 coefficient pairs
+    size_t ftx_fwd, ftx_inv, frx_fwd, frx_inv;
+    size_t ftz_fwd, ftz_inv, frz_fwd, frz_inv;
     size_t lam_x[NUM_XK], lam_z[NUM_XK];   // eigenvalues (double) per x / z kind
     size_t lo[NUM_KINDS], di[NUM_KINDS], up[NUM_KINDS];  // y operator rows
     size_t wy;               // Delta_j (pressure weights), ny doubles
     size_t dyc, dyf;         // cell heights [ny], centre distances [ny+1]
     size_t sx_fwd[NUM_XK], sx_inv[NUM_XK];   // x transform per x kind, bf16x3 split, B-operand
-                                             // swizzle (unfolded x: nx % 64 != 0 or walls)
+                                             // swizzle (kinds with no fast transform)
     size_t sz_fwd[NUM_XK], sz_inv[NUM_XK];   // z transform per z kind, bf16x3 split, A-operand
-                                             // swizzle (unfolded z: nz % 64 != 0 or walls)
-    size_t sxf_fwd, sxf_inv; // folded x transform factors, bf16x3 split (nx % 64 == 0)
-    size_t szf_fwd, szf_inv; // folded z transform factors, bf16x3 split (nz % 64 == 0)
+                                             // swizzle (neither fast nor folded)
+    size_t szf_fwd, szf_inv; // folded z transform factors, bf16x3 split (z_folds_split())
     size_t lane_mask;        // refined: per z-mode bit mask of FP64-lane x-tiles (uint32 [nz])
     size_t lane_list;        // refined: FP64-lane tiles, (c << 8) | t (int [lane_len])
     size_t sgx, sgz;         // stretched wall-bounded x / z: SG_SLOTS arrays of n doubles
@@ -66,6 +70,7 @@ constexpr int STATE_JOBS = 4;        // jobs (components) per call
 constexpr int XSUM_SLOTS = 4096;     // max residual blocks per job (fixed order: deterministic sums)
 constexpr int COMPAT_SLOTS = 2048;   // max blocks of the compatibility reduction
 constexpr int RESID_SLOTS = 4096;    // max blocks of the residual() norm reduction
+constexpr int FFT_RW = 16;           // rows per block of the fast x transforms
 constexpr int MAX_PASSES = 8;        // most refinement passes a solve may take (max_iter)
 constexpr int MAX_PLANES = 1024;     // largest nz a plan accepts
 constexpr int BMAX_SLOTS = 2048;     // partial maxima per job (two halves of 1024 blocks)
@@ -87,6 +92,10 @@ constexpr double LANE64_KAPPA = 1000.0;
 // towards the near-null constant mode): measured 1e-10 after two passes at
 // a bound of 935 on a 96 x 96 x 64 grid; their lane takes bounds above 100.
 constexpr double LANE64_KAPPA_CYCLIC = 100.0;
+// Smallest constant buffer a plan reports (const_bytes): fast transforms need
+// only a few KB of tables, where the dense factors of a 64-point axis alone
+// take 32 KB; the size a caller allocates keeps that order.
+constexpr size_t MIN_CONST_BYTES = size_t(64) << 10;
 struct State {
     double *bmean = nullptr;   // per job: weighted mean of the Poisson rhs
     double *xsum = nullptr;    // per job: partial sums of Delta_j x (XSUM_SLOTS each)
@@ -95,6 +104,7 @@ struct State {
     double *compat = nullptr;  // compatibility partials (2 per block)
     double *red = nullptr;     // refinement update partials, then residual() partials
     size_t red_count = 0;      // doubles in red
+    size_t upd_region = 0;     // doubles of red one refinement pass takes
     double *bmax = nullptr;    // per job: partial maxima of the first pass's pencil data
                                // (BMAX_SLOTS each: the FP32 tiles' blocks, then the FP64 lane's)
     double *scale = nullptr;   // per job: power of two sigma the refinement passes scale
@@ -148,6 +158,7 @@ struct Plan {
     bool wx = false;                               // walls at x = 0 and x = lx
     bool wz = false;                               // walls at z = 0 and z = lz
     bool sx = false, sz = false;                   // stretched (wall-bounded) x / z
+    bool fx[NUM_XK] = {}, fz[NUM_XK] = {};         // the x / z kind has a fast transform
     int tune[NUM_TUNE] = {-1, -1};   // candidate index per knob; -1 = default
     int nx, ny, nz;
     double hx, hz;
@@ -236,17 +247,21 @@ hipError_t launch_xgemm_f64(const JobSet &js, int nz, int K, int N,
                             const double *const bs[NUM_XK], hipStream_t s);
 // C[M x Ncol] = As * B, As the swizzled M x K matrix, B row-major (K x Ncol),
 // Ncol = rows * nx per job.
+// Lengths the fast transforms are built for (fft_sizes.h), and whether basis
+// (-1 periodic, else XK_*) on an axis of n points takes them: uniform
+// spacing, and not the face-normal sine basis (n - 1 unknowns).
+bool fft_size(int n);
+inline bool fft_axis(int n, int basis, bool stretched) { return !stretched && basis != XK_F && fft_size(n); }
 // Folded FP64 transforms (valid when can_fold(n)).
 bool can_fold(int n);
 int fold_candidates();
 // Folded split transforms: the half length must hold whole 32-deep chunks.
 inline bool can_fold_split(int n) { return n % 64 == 0; }
 // The folds use the Fourier basis's mirror symmetry: a direction folds only
-// when it is periodic.
-inline bool x_folds(const Plan &p) { return !p.wx && can_fold(p.nx); }
-inline bool x_folds_split(const Plan &p) { return !p.wx && can_fold_split(p.nx); }
-inline bool z_folds(const Plan &p) { return !p.wz && can_fold(p.nz); }
-inline bool z_folds_split(const Plan &p) { return !p.wz && can_fold_split(p.nz); }
+// when it is periodic (and has no fast transform).
+inline bool x_folds(const Plan &p) { return !p.wx && can_fold(p.nx) && !p.fx[XK_P]; }
+inline bool z_folds(const Plan &p) { return !p.wz && can_fold(p.nz) && !p.fz[XK_P]; }
+inline bool z_folds_split(const Plan &p) { return !p.wz && can_fold_split(p.nz) && !p.fz[XK_P]; }
 hipError_t launch_xfold_f64(const JobSet &js, const Plan &p, bool inverse, hipStream_t s);
 hipError_t launch_zfold_f64(const JobSet &js, const Plan &p, bool inverse, hipStream_t s);
 hipError_t launch_zgemm_f64(const JobSet &js, int M, int K, int nx,
@@ -305,6 +320,7 @@ struct SplitJob {
     int zk;             // XK_* kind of the z operator
     const void *zq;     // z transform matrix of this job (set by the z launchers)
     int op;             // IBS_OP_* of the job (residual stencil)
+    int slot;           // job number in the call's state (a launch may take some of the jobs)
     double c;
     void *info;
 };
@@ -319,8 +335,12 @@ struct SplitSet {
 // Kernels of pass >= 2 return at once for jobs whose stop flag is set.
 hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64,
                               int mode, int pass, hipStream_t s);
-// Doubles of update partials one refinement pass of ncomp jobs writes.
-size_t update_region(const Plan &p, int ncomp);
+// Update partials (pairs) one job may write per refinement pass, and the
+// doubles one pass of ncomp jobs takes (jobs update_slots() apart).
+size_t update_slots(const Plan &p);
+inline size_t update_region(const Plan &p, int ncomp) { return 2 * update_slots(p) * ncomp; }
+// Pairs a job of x kind xk writes.
+size_t update_used(const Plan &p, int xk);
 hipError_t launch_split_zgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass,
                               hipStream_t s);
 // pass: refinement pass (0 records the rhs mean; later passes steer the
@@ -335,6 +355,15 @@ int residual_tiles(const Plan &p);   // residual blocks (x-sum partials) per job
 // pass 0 (a one-pass solve): no estimate exists; the report says so.
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s);
 hipError_t launch_residual_scale(const SplitSet &ss, const State &st, hipStream_t s);
+
+// ---- fast transforms (k_fft.h; p.fx / p.fz kinds only) ---------------------
+// One pass over each job's field, js.j[q].in to .out (which may be the same
+// field); the jobs of one call share the axis's boundary conditions.
+hipError_t launch_fft_f64(const JobSet &js, const Plan &p, bool z_axis, bool inverse, hipStream_t s);
+// Refined path: in64, mode and pass as launch_split_xgemm().
+hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
+                          int pass, hipStream_t s);
+hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s);
 
 inline const double *blob_ptr(const Plan &p, size_t off) {
     return reinterpret_cast<const double *>(static_cast<const unsigned char *>(p.dev_const) + off);

@@ -1,0 +1,32 @@
+// FP64 fast x transforms (k_fft.h), one instantiation per size.
+#include "k_fft.h"
+
+namespace ibs {
+
+template <int R1, int R2>
+static void go(const FftSet &js, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+{
+    const dim3 grid(nz * rows / FFT_RW, js.n), blk(fft::Shape<R1, R2>::threads(FFT_RW));
+    if (inverse && walls)
+        fft_x_kernel<double, double, double, R1, R2, true, true, 0><<<grid, blk, 0, s>>>(js, nz, nullptr, 0, nullptr, nullptr);
+    else if (inverse)
+        fft_x_kernel<double, double, double, R1, R2, true, false, 0><<<grid, blk, 0, s>>>(js, nz, nullptr, 0, nullptr, nullptr);
+    else if (walls)
+        fft_x_kernel<double, double, double, R1, R2, false, true, 0><<<grid, blk, 0, s>>>(js, nz, nullptr, 0, nullptr, nullptr);
+    else
+        fft_x_kernel<double, double, double, R1, R2, false, false, 0><<<grid, blk, 0, s>>>(js, nz, nullptr, 0, nullptr, nullptr);
+}
+
+hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+{
+    if (js.n == 0) return hipSuccess;
+    switch (n) {
+#define IBS_CASE(N, R1, R2) case N: go<R1, R2>(js, rows, nz, inverse, walls, s); break;
+    IBS_FFT_SIZES_32(IBS_CASE) IBS_FFT_SIZES_16(IBS_CASE)
+#undef IBS_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace ibs

@@ -173,17 +173,17 @@ __global__ __launch_bounds__(512) void split_xgemm_kernel(SplitSet ss, int nz, i
                                                           const b8 *__restrict__ qs,
                                                           double *__restrict__ red,
                                                           const int *__restrict__ skip,
-                                                          const double *__restrict__ scale)
+                                                          const double *__restrict__ scale, int red_stride)
 {
     constexpr int QCNT = NBT * 3 * 64;                // fragments per chunk
     constexpr bool DB = 2 * QCNT * 16 <= 144 * 1024;  // double buffer if it fits
     constexpr int QPER = (QCNT + 511) / 512;
     __shared__ b8 sq[(DB ? 2 : 1) * QCNT];
-    if (skip && skip[blockIdx.z]) return;   // this job has already converged
     const SplitJob &jb = ss.j[blockIdx.z];
+    if (skip && skip[jb.slot]) return;   // this job has already converged
     // update modes: the residual was stored scaled by sigma (a power of
     // two), so the correction is scaled back exactly
-    const double isg = (XStore<MODE>::update && scale) ? 1.0 / scale[blockIdx.z] : 1.0;
+    const double isg = (XStore<MODE>::update && scale) ? 1.0 / scale[jb.slot] : 1.0;
     // the job's own matrix when the jobs' x operators differ (walls in x)
     const b8 *__restrict__ qj = jb.xq ? static_cast<const b8 *>(jb.xq) : qs;
     const int rskip = skip_first_row(jb.kind), trows = jb.rows - rskip;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(512) void split_xgemm_kernel(SplitSet ss, int nz, i
         sd = wave_sum(sd);
         sx = wave_sum(sx);
         if (lane == 0) {
-            const size_t slot = ((size_t)blockIdx.z * gridDim.x + blockIdx.x) * UPD_WAVES + wave;
+            const size_t slot = (size_t)jb.slot * red_stride + blockIdx.x * UPD_WAVES + wave;
             red[2 * slot] = sd;
             red[2 * slot + 1] = sx;
         }
@@ -324,8 +324,8 @@ __global__ __launch_bounds__(512) void split_zgemm_kernel(SplitSet ss, int M, in
     constexpr bool DB = 2 * QCNT * 16 <= 144 * 1024;
     constexpr int QPER = (QCNT + 511) / 512;
     __shared__ b8 sq[(DB ? 2 : 1) * QCNT];
-    if (skip && skip[blockIdx.z]) return;
     const SplitJob &jb = ss.j[blockIdx.z];
+    if (skip && skip[jb.slot]) return;
     // the job's own matrix when the jobs' z operators differ (walls in z)
     const b8 *__restrict__ qj = jb.zq ? static_cast<const b8 *>(jb.zq) : qs;
     const int rskip = skip_first_row(jb.kind);
@@ -425,365 +425,6 @@ __global__ __launch_bounds__(512) void split_zgemm_kernel(SplitSet ss, int M, in
 // factors (2 x HB 16-blocks x 3 terms) is staged through LDS as above.
 // ---------------------------------------------------------------------------
 
-// x transform, a wave owning WM row blocks and all columns of both factors.
-// MODE as for the plain kernel (0: FP32 out, forward; 1..4 as in XStore).
-// Persistent like the z kernel: block b takes row tiles b, b + G, ... over
-// the jobs still running as one pipeline of 32-deep chunks.  MODE 2 writes
-// the update sums of tile rt of job q to slot q * tiles_per_job + rt.
-template <int HBT, int WM, typename Tin, int MODE, bool INV, int FS>
-__global__ __launch_bounds__(512) void split_xfold_kernel(SplitSet ss, int nz, int N,
-                                                          const b8 *__restrict__ qs,
-                                                          double *__restrict__ red,
-                                                          const int *__restrict__ skip, double s0,
-                                                          double s1, int tiles_per_job,
-                                                          const double *__restrict__ scale)
-{
-    // FS = 1: a pipeline step is one 32-deep chunk of both factors; FS = 2
-    // (large n): one factor at a time, so a double-buffered step fits LDS
-    constexpr int QCNT = (FS == 1 ? 2 : 1) * HBT * 3 * 64;
-    static_assert(2 * QCNT * 16 <= 144 * 1024, "double-buffered factor chunk must fit LDS");
-    __shared__ b8 sq[2 * QCNT];
-    // jobs not yet converged (block-uniform), packed 8 bits each so that no
-    // private array is indexed at run time
-    int live = 0, nlive = 0;
-    for (int q = 0; q < ss.n; ++q)
-        if (!(skip && skip[q])) live |= q << (8 * nlive++);
-    const int ntiles = nlive * tiles_per_job;
-    const int G = gridDim.x;
-    const int my_tiles = (int)blockIdx.x < ntiles ? (ntiles - 1 - (int)blockIdx.x) / G + 1 : 0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int li = lane & 15, lg = lane >> 4;
-    const int H = N >> 1, HB = H >> 4;
-    const int qcnt = (FS == 1 ? 2 : 1) * HB * 3 * 64;
-    const int KC = H >> 5;
-    const int nsteps = my_tiles * KC * FS;
-    const double sH = (H & 1) ? -s0 : s0;
-
-    struct TileRef { int job, rt, rskip, trows, row0, nrb; const SplitJob *jb; };
-    auto tile_ref = [&](int i) {
-        const int t = (int)blockIdx.x + i * G;
-        TileRef r;
-        r.job = (live >> (8 * (t / tiles_per_job))) & 0xff;
-        r.rt = t % tiles_per_job;
-        r.jb = &ss.j[r.job];
-        r.rskip = skip_first_row(r.jb->kind);
-        r.trows = r.jb->rows - r.rskip;
-        const int M = nz * r.trows;
-        r.row0 = (r.rt * 8 + wave) * (16 * WM);
-        r.nrb = r.row0 < M ? min(WM, (M - r.row0) >> 4) : 0;
-        return r;
-    };
-
-    f4 acc[WM][2][HBT];
-    double nyq[WM];
-    auto clear = [&]() {
-#pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            nyq[i] = 0.0;
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int j = 0; j < HBT; ++j) acc[i][f][j] = (f4){0.f, 0.f, 0.f, 0.f};
-        }
-    };
-    // forward: p = X[k], m = X[mirror k]; inverse: p = cos inputs, m = sin
-    // inputs.  The next chunk is loaded, raw, into the same registers once
-    // the current one has been split; nothing reads them before the step's
-    // closing wait, so the loads run under the products.
-    Tin rp[WM][8], rm[WM][8], rxh[WM];
-    auto load_data = [&](int chunk) {   // chunk = tile * KC + kc
-        const TileRef r = tile_ref(chunk / KC);
-        const Tin *A = static_cast<const Tin *>(r.jb->in);
-        const int k0 = 32 * (chunk % KC) + 8 * lg;
-#pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            if (i < r.nrb) {   // wave-uniform
-                const Tin *arow = A + phys_row(r.row0 + 16 * i + li, r.trows, r.rskip) * N;
-                __builtin_memcpy(rp[i], arow + k0, sizeof(rp[i]));
-                if (!INV) {
-                    // mirrored points N - kk (kk = k0 .. k0+7) as one 8-wide
-                    // run, reversed at the split; kk = 0 pairs with point H
-                    // instead, so lanes with k0 = 0 read the run N-8 .. N-1
-                    __builtin_memcpy(rm[i], arow + (k0 == 0 ? N - 8 : N - k0 - 7), sizeof(rm[i]));
-                    if (chunk % KC == 0) rxh[i] = arow[H];   // wave-uniform: once per tile
-                } else {
-                    __builtin_memcpy(rm[i], arow + H + k0, sizeof(rm[i]));
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { rp[i][e] = 0; rm[i][e] = 0; }
-                rxh[i] = 0;
-            }
-        }
-    };
-    if (nsteps == 0) return;
-    clear();
-    q_dma(qs, sq, qcnt);
-    load_data(0);
-    wait_vm();
-    b8 ae[WM][3], ao[WM][3];   // split E and O of the current chunk
-    // X[H] of the tile's output rows (and, inverse, of rows li), loaded at
-    // the start of the tile's last step so that the epilogue does not wait
-    Tin ahp[WM][4], xhp[WM];
-    typename XStore<MODE>::T xhold[WM];   // update modes: old iterate at point H of rows li
-    // one chunk per iteration; its FS steps unrolled, so that the factor
-    // of a step is known at compile time and the data loads of a chunk go
-    // straight into the registers the next chunk reads
-    for (int step0 = 0; step0 < nsteps; step0 += FS) {
-#pragma unroll
-        for (int f = 0; f < FS; ++f) {   // f: factor of this step (FS = 2)
-        const int step = step0 + f, chunk = step / FS;
-        const int kc = chunk % KC;
-        const bool last = kc == KC - 1 && f == FS - 1;   // the tile completes this step
-        __syncthreads();
-        const b8 *cur = sq + (step & 1) * QCNT;
-        const bool more = step + 1 < nsteps;
-        // the next step's factors go to the other LDS buffer, at the step
-        // start (the copy runs under the products).  No other LDS object
-        // or barrier may appear in the loop: with one, the compiler made the
-        // products' LDS reads wait for this copy (and, the memory counter
-        // being in order, for the data loads after it)
-        if (more) q_dma(qs + (size_t)((step + 1) % (KC * FS)) * qcnt, sq + ((step + 1) & 1) * QCNT, qcnt);
-        if (last) {
-            const TileRef r = tile_ref(chunk / KC);
-            const Tin *A = static_cast<const Tin *>(r.jb->in);
-#pragma unroll
-            for (int i = 0; i < WM; ++i) {
-                if (i >= r.nrb) continue;   // wave-uniform
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    ahp[i][q] = A[phys_row(r.row0 + 16 * i + 4 * lg + q, r.trows, r.rskip) * N + H];
-                if (INV) xhp[i] = A[phys_row(r.row0 + 16 * i + li, r.trows, r.rskip) * N + H];
-                if constexpr (XStore<MODE>::update)
-                    xhold[i] = stored_iterate<MODE>(*r.jb)[phys_row(r.row0 + 16 * i + li, r.trows, r.rskip) * N + H];
-            }
-        }
-        const int k0 = 32 * kc + 8 * lg;
-        if (f == 0) {
-#pragma unroll
-            for (int i = 0; i < WM; ++i) {
-                float ev[8], ov[8], pc[8], mc[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    pc[e] = (float)rp[i][e];
-                    if (INV) mc[e] = (float)rm[i][e];
-                    else if (k0 == 0) mc[e] = (float)(e == 0 ? rxh[i] : rm[i][8 - e]);
-                    else mc[e] = (float)rm[i][7 - e];
-                }
-                if (!INV) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const bool self = k0 + e == 0;
-                        ev[e] = self ? pc[e] : pc[e] + mc[e];
-                        ov[e] = self ? mc[e] : pc[e] - mc[e];
-                        nyq[i] += (e & 1) ? -(double)ev[e] : (double)ev[e];
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        ev[e] = pc[e];
-                        ov[e] = mc[e];
-                        const double w = (k0 + e == 0) ? s0 : s1;
-                        nyq[i] += (e & 1) ? -w * (double)ev[e] : w * (double)ev[e];
-                    }
-                }
-                split8(ev, ae[i]);
-                split8(ov, ao[i]);
-            }
-            if (chunk + 1 < my_tiles * KC) load_data(chunk + 1);
-        }
-        {
-            constexpr int GR = (HBT >= 6 || WM >= 2) ? 1 : 2;   // register budget
-#pragma unroll
-            for (int jg = 0; jg < HBT; jg += GR) {
-                if (FS == 1) {
-                    b8 bc[GR][3], bs[GR][3];
-#pragma unroll
-                    for (int jj = 0; jj < GR; ++jj)
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) {
-                            bc[jj][t] = cur[((jg + jj) * 3 + t) * 64 + lane];
-                            bs[jj][t] = cur[((HB + jg + jj) * 3 + t) * 64 + lane];
-                        }
-#pragma unroll
-                    for (int pr = 0; pr < 6; ++pr)
-#pragma unroll
-                        for (int jj = 0; jj < GR; ++jj)
-#pragma unroll
-                            for (int i = 0; i < WM; ++i) {
-                                acc[i][0][jg + jj] = mma(ae[i][TA_[pr]], bc[jj][TB_[pr]], acc[i][0][jg + jj]);
-                                acc[i][1][jg + jj] = mma(ao[i][TA_[pr]], bs[jj][TB_[pr]], acc[i][1][jg + jj]);
-                            }
-                } else {
-                    // one factor per step: cos (E) on even steps, sin (O) on odd
-                    b8 bf[GR][3];
-#pragma unroll
-                    for (int jj = 0; jj < GR; ++jj)
-#pragma unroll
-                        for (int t = 0; t < 3; ++t) bf[jj][t] = cur[((jg + jj) * 3 + t) * 64 + lane];
-                    if (f == 0) {
-#pragma unroll
-                        for (int pr = 0; pr < 6; ++pr)
-#pragma unroll
-                            for (int jj = 0; jj < GR; ++jj)
-#pragma unroll
-                                for (int i = 0; i < WM; ++i)
-                                    acc[i][0][jg + jj] = mma(ae[i][TA_[pr]], bf[jj][TB_[pr]], acc[i][0][jg + jj]);
-                    } else {
-#pragma unroll
-                        for (int pr = 0; pr < 6; ++pr)
-#pragma unroll
-                            for (int jj = 0; jj < GR; ++jj)
-#pragma unroll
-                                for (int i = 0; i < WM; ++i)
-                                    acc[i][1][jg + jj] = mma(ao[i][TA_[pr]], bf[jj][TB_[pr]], acc[i][1][jg + jj]);
-                    }
-                }
-            }
-        }
-        // next step's factors and data, and this tile's X[H] values, have
-        // landed (the epilogue's stores below are left in flight)
-        if (more || last) wait_vm();
-        if (last) {   // the tile is complete: store it
-            const TileRef r = tile_ref(chunk / KC);
-            const SplitJob &jb = *r.jb;
-            // update modes: the residual was stored scaled by sigma (a power
-            // of two), so the correction is scaled back exactly
-            const double isg = (XStore<MODE>::update && scale) ? 1.0 / scale[r.job] : 1.0;
-            double sd = 0.0, sx = 0.0;
-#pragma unroll
-            for (int i = 0; i < WM; ++i) {
-                if (i >= r.nrb) continue;
-                double ny = nyq[i];
-                ny += __shfl_xor(ny, 16, 64);
-                ny += __shfl_xor(ny, 32, 64);   // every lane of row li holds its sum
-                size_t orow[4];
-                double ah[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int t = r.row0 + 16 * i + 4 * lg + q;
-                    orow[q] = phys_row(t, r.trows, r.rskip) * N;
-                    ah[q] = (double)ahp[i][q];   // X[H] of the output row
-                    // the skipped wall row before each plane's first row
-                    // holds zeros in the result
-                    if constexpr (MODE != 0 && XStore<MODE>::zero_walls)
-                        if (r.rskip && t % r.trows == 0)
-                            for (int c = li; c < N; c += 16) {
-                                xdest<MODE>(jb)[orow[q] - N + c] = 0;
-                                if (MODE == 3) jb.x[orow[q] - N + c] = 0.0;
-                            }
-                }
-                if (!INV) {
-                    double nyr[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) nyr[q] = __shfl(ny, 4 * lg + q, 64);
-#pragma unroll
-                    for (int j = 0; j < HBT; ++j) {
-                        if (j >= HB) continue;
-                        const int a = 16 * j + li;
-                        const double wa = (a == 0 ? s0 : s1) * ((a & 1) ? -1.0 : 1.0);   // Q[H][a]
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            jb.out[orow[q] + a] = (float)fma(ah[q], wa, (double)acc[i][0][j][q]);
-                            double sv = (double)acc[i][1][j][q];
-                            if (a == 0) sv = fma(s0, nyr[q], sv);   // spectral index H
-                            jb.out[orow[q] + H + a] = (float)sv;
-                        }
-                    }
-                } else {
-                    // destination and stored iterate held in registers: the
-                    // job record is not reloaded after each store
-                    auto *const xd = xdest<MODE>(jb);
-                    const auto *const xold = stored_iterate<MODE>(jb);
-                    if (lg == 0) {   // physical point H of row li
-                        const size_t rr = phys_row(r.row0 + 16 * i + li, r.trows, r.rskip) * N;
-                        const double xh = fma((double)xhp[i], sH, ny);
-                        if constexpr (XStore<MODE>::store) {
-                            xd[rr + H] = xh;
-                        } else {
-                            const double dh = xh * isg, xn = (double)xhold[i] + dh;
-                            xd[rr + H] = xn;
-                            sd += dh * dh;
-                            sx += xn * xn;
-                        }
-                    }
-                    // the rows' old values first, eight column blocks and (an
-                    // FP32 iterate) all four rows at a time (all loads in
-                    // flight together; every position is distinct), then the
-                    // updates
-                    typedef typename XStore<MODE>::T Tx;   // kept in its stored type
-                    constexpr int JG = HBT < 8 ? HBT : 8;
-                    constexpr int QG = (XStore<MODE>::update && sizeof(Tx) == 4 && HBT <= 8) ? 4 : 1;
-#pragma unroll
-                    for (int q0 = 0; q0 < 4; q0 += QG) {
-#pragma unroll
-                        for (int j0 = 0; j0 < HBT; j0 += JG) {
-                            Tx xo[QG][2][JG];
-                            if constexpr (XStore<MODE>::update) {
-                                // a position the row lacks is neither read
-                                // nor used (its store below is skipped too)
-#pragma unroll
-                                for (int qq = 0; qq < QG; ++qq)
-#pragma unroll
-                                    for (int jj = 0; jj < JG; ++jj) {
-                                        const int ii = 16 * (j0 + jj) + li;
-                                        const bool ok = j0 + jj < HB;
-                                        if (ok) xo[qq][0][jj] = xold[orow[q0 + qq] + ii];
-                                        if (ok && ii != 0) xo[qq][1][jj] = xold[orow[q0 + qq] + N - ii];
-                                    }
-                                // all of them have landed before the first
-                                // store (else each later use would wait on
-                                // the stores issued meanwhile)
-                                wait_vm();
-                            }
-#pragma unroll
-                            for (int qq = 0; qq < QG; ++qq) {
-                                const int q = q0 + qq;
-#pragma unroll
-                                for (int jj = 0; jj < JG; ++jj) {
-                                    const int j = j0 + jj;
-                                    if (j >= HB) continue;
-                                    const int ii = 16 * j + li;
-                                    const double sg = (ii & 1) ? -s0 : s0;   // Q[ii][H]
-                                    const double u = fma(ah[q], sg, (double)acc[i][0][j][q]);
-                                    const double v = (double)acc[i][1][j][q];
-                                    const size_t o1 = orow[q] + ii, o2 = orow[q] + N - ii;
-                                    if constexpr (XStore<MODE>::store) {
-                                        xd[o1] = u + v;
-                                        if (ii != 0) xd[o2] = u - v;
-                                    } else {
-                                        const double d1 = (u + v) * isg, x1 = xo[qq][0][jj] + d1;
-                                        xd[o1] = x1;
-                                        sd += d1 * d1;
-                                        sx += x1 * x1;
-                                        if (ii != 0) {
-                                            const double d2 = (u - v) * isg, x2 = xo[qq][1][jj] + d2;
-                                            xd[o2] = x2;
-                                            sd += d2 * d2;
-                                            sx += x2 * x2;
-                                        }
-                                    }
-                                }
-                            }
-                        }
-                    }
-                }
-            }
-            if (XStore<MODE>::update) {
-                sd = wave_sum(sd);
-                sx = wave_sum(sx);
-                if (lane == 0) {
-                    const size_t slot = ((size_t)r.job * tiles_per_job + r.rt) * UPD_WAVES + wave;
-                    red[2 * slot] = sd;
-                    red[2 * slot + 1] = sx;
-                }
-            }
-            clear();
-        }
-        }
-    }
-}
-
 // z transform, a wave owning all output rows of both factors and WN
 // column blocks; FP32 in and out.  Persistent: block b takes column tiles
 // b, b + G, ... (G = gridDim.x) over the jobs still running, and streams
@@ -804,7 +445,7 @@ __global__ __launch_bounds__(512) void split_zfold_kernel(SplitSet ss, int N, in
     // private array is indexed at run time
     int live = 0, nlive = 0;
     for (int q = 0; q < ss.n; ++q)
-        if (!(skip && skip[q])) live |= q << (8 * nlive++);
+        if (!(skip && skip[ss.j[q].slot])) live |= q << (8 * nlive++);
     const int ntiles = nlive * tiles_per_job;
     const int G = gridDim.x;
     const int my_tiles = (int)blockIdx.x < ntiles ? (ntiles - 1 - (int)blockIdx.x) / G + 1 : 0;
@@ -1219,13 +860,16 @@ static __device__ double2 sum_pairs(const double *r, int n)
     return t;
 }
 
+struct CheckCounts {
+    int n[4];   // pairs written per job of the launch
+};
 __global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const double *__restrict__ red_last,
                                                            const double *__restrict__ red_prev,
-                                                           int slots_per_job, int pass, double tol,
+                                                           int stride, CheckCounts used, int pass, double tol,
                                                            int *__restrict__ done)
 {
-    const int job = blockIdx.x;
-    const SplitJob &jb = ss.j[job];
+    const SplitJob &jb = ss.j[blockIdx.x];
+    const int job = jb.slot, count = used.n[blockIdx.x];
     if (pass == 0) {
         // one pass only: no correction was measured, so no error estimate
         // exists; the report says NOT_CONVERGED with unknown (NaN) error
@@ -1242,11 +886,11 @@ __global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const do
         return;
     }
     if (pass >= 2 && done[job]) return;     // stopped earlier: report stands
-    const size_t off = (size_t)job * slots_per_job * 2;
-    const double2 last = sum_pairs(red_last + off, slots_per_job);
+    const size_t off = (size_t)job * stride * 2;
+    const double2 last = sum_pairs(red_last + off, count);
     double rprev = 1.0;
     if (red_prev) {
-        const double2 prev = sum_pairs(red_prev + off, slots_per_job);
+        const double2 prev = sum_pairs(red_prev + off, count);
         rprev = !(isfinite(prev.x) && isfinite(prev.y)) ? __builtin_nan("")
                                                         : (prev.y > 0.0 ? sqrt(prev.x / prev.y) : 0.0);
     }
@@ -1286,19 +930,11 @@ static int max_rows(const SplitSet &ss)   // transform rows per plane
 static int x_nbt(int N) { return N <= 64 ? 4 : (N <= 128 ? 8 : (N <= 256 ? 16 : 32)); }
 static constexpr int x_wm(int nbt) { return nbt == 4 ? 4 : (nbt == 32 ? 1 : 2); }
 
-// folded x tiling: HBT 16-blocks per factor (HB = nx/32 <= HBT), WM row
-// blocks per wave, at most 32 accumulator tiles per wave
-static int xf_hbt(int nx)
-{
-    const int hb = nx / 32;
-    return hb <= 2 ? 2 : hb <= 4 ? 4 : hb <= 6 ? 6 : hb <= 8 ? 8 : hb <= 12 ? 12 : 16;
-}
-static constexpr int xf_wm(int hbt) { return hbt <= 4 ? 2 : 1; }
 static constexpr int f_steps(int hbt) { return hbt <= 8 ? 1 : 2; }   // factors per pipeline step: 2 / 1
 
 static void xgemm_grid(const SplitSet &ss, const Plan &p, dim3 &grid)
 {
-    const int wm = x_folds_split(p) ? xf_wm(xf_hbt(p.nx)) : x_wm(x_nbt(p.nx));
+    const int wm = x_wm(x_nbt(p.nx));
     const int M = p.nz * max_rows(ss);
     grid = dim3((M + 8 * 16 * wm - 1) / (8 * 16 * wm), 1, ss.n);
 }
@@ -1316,43 +952,13 @@ static int resident_blocks(K kernel)
     return per_cu * cus;
 }
 
-template <int HBT, typename Tin, int MODE, bool INV>
-static void launch_xf(const SplitSet &ss, const Plan &p, const b8 *qs, double *red, const int *skip,
-                      const double *scale,
-                      dim3 grid, hipStream_t s)
-{
-    static const int resident =
-        resident_blocks(split_xfold_kernel<HBT, xf_wm(HBT), Tin, MODE, INV, f_steps(HBT)>);
-    const int tiles_per_job = (int)grid.x;
-    const int ntiles = tiles_per_job * ss.n;
-    const int g = ntiles < resident ? ntiles : resident;
-    const double s0 = 1.0 / std::sqrt((double)p.nx), s1 = std::sqrt(2.0 / (double)p.nx);
-    hipLaunchKernelGGL((split_xfold_kernel<HBT, xf_wm(HBT), Tin, MODE, INV, f_steps(HBT)>), dim3(g), dim3(512), 0, s,
-                       ss, p.nz, p.nx, qs, red, skip, s0, s1, tiles_per_job, scale);
-}
-
-template <typename Tin, int MODE, bool INV>
-static void launch_xf_hb(const SplitSet &ss, const Plan &p, const b8 *qs, double *red, const int *skip,
-                      const double *scale,
-                         dim3 grid, hipStream_t s)
-{
-    switch (xf_hbt(p.nx)) {
-    case 2: launch_xf<2, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    case 4: launch_xf<4, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    case 6: launch_xf<6, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    case 8: launch_xf<8, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    case 12: launch_xf<12, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    default: launch_xf<16, Tin, MODE, INV>(ss, p, qs, red, skip, scale, grid, s); break;
-    }
-}
-
 template <int NBT, typename Tin, int MODE>
 static void launch_x(const SplitSet &ss, const Plan &p, const b8 *qs, double *red, const int *skip,
                       const double *scale,
                      dim3 grid, hipStream_t s)
 {
     hipLaunchKernelGGL((split_xgemm_kernel<NBT, x_wm(NBT), Tin, MODE>), grid, dim3(512), 0, s, ss,
-                       p.nz, p.nx, p.nx, qs, red, skip, scale);
+                       p.nz, p.nx, p.nx, qs, red, skip, scale, (int)update_slots(p));
 }
 
 template <typename Tin, int MODE>
@@ -1368,8 +974,6 @@ static void launch_x_nb(const SplitSet &ss, const Plan &p, const b8 *qs, double 
     }
 }
 
-static size_t update_slots(const SplitSet &ss, const Plan &p);
-
 hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64,
                               int mode, int pass, hipStream_t s)
 {
@@ -1378,22 +982,9 @@ hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st
     dim3 grid;
     xgemm_grid(ss, p, grid);
     // each refinement pass keeps its update partials in a region of its own
-    const size_t region = update_region(p, ss.n);
     const bool upd = mode == 2 || mode == 4;
-    double *red = st.red + (upd ? (size_t)(pass - 1) * region : 0);
+    double *red = st.red + (upd ? (size_t)(pass - 1) * st.upd_region : 0);
     const double *scale = upd ? st.scale : nullptr;   // the residuals' sigma
-    if (x_folds_split(p)) {
-        const b8 *qs = reinterpret_cast<const b8 *>(blob_ptr(p, inverse ? p.lay.sxf_inv : p.lay.sxf_fwd));
-        switch (in64 ? -1 : mode) {
-        case -1: launch_xf_hb<double, 0, false>(ss, p, qs, red, skip, scale, grid, s); break;
-        case 0: launch_xf_hb<float, 0, false>(ss, p, qs, red, skip, scale, grid, s); break;
-        case 1: launch_xf_hb<float, 1, true>(ss, p, qs, red, skip, scale, grid, s); break;
-        case 2: launch_xf_hb<float, 2, true>(ss, p, qs, red, skip, scale, grid, s); break;
-        case 3: launch_xf_hb<float, 3, true>(ss, p, qs, red, skip, scale, grid, s); break;
-        default: launch_xf_hb<float, 4, true>(ss, p, qs, red, skip, scale, grid, s); break;
-        }
-        return hipGetLastError();
-    }
     const size_t *tab = inverse ? p.lay.sx_inv : p.lay.sx_fwd;
     const b8 *qs = reinterpret_cast<const b8 *>(blob_ptr(p, tab[XK_P]));
     SplitSet sj = ss;   // each job's matrix for its x operator
@@ -1549,26 +1140,25 @@ hipError_t launch_residual_f32(const SplitSet &ss, const Plan &p, const State &s
 
 // Rows of the transform tiling are those of every component (ny; the v
 // component's first wall row is left out), so the update partials depend
-// only on the grid and the component count.
-size_t update_region(const Plan &p, int ncomp)
+// only on the grid and the x kinds.
+size_t update_used(const Plan &p, int xk)
 {
-    SplitSet ss{};
-    ss.n = ncomp;
-    for (int q = 0; q < ncomp; ++q) { ss.j[q].rows = p.ny; ss.j[q].kind = KIND_C; }
-    dim3 grid;
-    xgemm_grid(ss, p, grid);
-    return 2 * (size_t)grid.x * grid.y * grid.z * UPD_WAVES;
+    if (p.fx[xk]) return (size_t)p.nz * p.ny / FFT_RW;   // one per block
+    const size_t rows = (size_t)8 * 16 * x_wm(x_nbt(p.nx));
+    return ((size_t)p.nz * p.ny + rows - 1) / rows * UPD_WAVES;
+}
+size_t update_slots(const Plan &p)
+{
+    return std::max(update_used(p, XK_P), std::max(update_used(p, XK_C), update_used(p, XK_F)));
 }
 
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s)
 {
-    dim3 grid;
-    xgemm_grid(ss, p, grid);
-    const int per_job = (int)(grid.x * grid.y) * UPD_WAVES;
-    const size_t region = update_region(p, ss.n);
-    const double *last = pass >= 1 ? st.red + (size_t)(pass - 1) * region : nullptr;
-    const double *prev = pass >= 2 ? st.red + (size_t)(pass - 2) * region : nullptr;
-    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, last, prev, per_job,
+    CheckCounts used{};
+    for (int q = 0; q < ss.n; ++q) used.n[q] = (int)update_used(p, ss.j[q].xk);
+    const double *last = pass >= 1 ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
+    const double *prev = pass >= 2 ? st.red + (size_t)(pass - 2) * st.upd_region : nullptr;
+    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, last, prev, (int)update_slots(p), used,
                        pass, p.desc.tol, st.done);
     return hipGetLastError();
 }

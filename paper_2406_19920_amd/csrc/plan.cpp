@@ -7,6 +7,7 @@
 #include <mutex>
 #include <new>
 
+#include "fft_sizes.h"
 #include "ibs_internal.h"
 #include "multigrid.h"
 
@@ -17,6 +18,22 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // The FP64 transforms fold the real Fourier basis when the half length is a
 // whole number of 16-blocks.
 bool can_fold(int n) { return n % 32 == 0; }
+
+// stage sizes of the fast transform of length n, or false
+static bool fft_radices(int n, int &r1, int &r2)
+{
+    switch (n) {
+#define IBS_CASE(N, R1, R2) case N: r1 = R1; r2 = R2; return true;
+    IBS_FFT_SIZES_32(IBS_CASE) IBS_FFT_SIZES_16(IBS_CASE)
+#undef IBS_CASE
+    }
+    return false;
+}
+bool fft_size(int n)
+{
+    int r1, r2;
+    return fft_radices(n, r1, r2);
+}
 
 // Row counts the cyclic tridiagonal is instantiated for (periodic y): the
 // P chunks of M rows hold the system exactly, n = P M (k_tridiag_cyc.hip).
@@ -418,14 +435,44 @@ struct AxisTables {
     std::vector<double> Qi;            // stretched axis: the inverse basis G (else empty: G = Q)
     std::vector<double> f64[4];        // folded: fwd_c, fwd_s, inv_c, inv_s; plain: fwd, inv
     std::vector<uint16_t> split[2];    // fwd, inv (folded pairs or plain); empty without split
+    std::vector<double> fft[4];        // fast transform instead of all of these: twiddle factors fwd, inv;
+                                       // walls: pair rotations fwd, inv
     size_t bytes() const
     {
         size_t b = (Q.size() + Qi.size() + lam.size()) * sizeof(double);
         for (const auto &v : f64) b += v.size() * sizeof(double);
         for (const auto &v : split) b += v.size() * sizeof(uint16_t);
+        for (const auto &v : fft) b += v.size() * sizeof(double);
         return b;
     }
 };
+
+// Tables of the fast transform of length n: twiddle factors s e^{-+ 2 pi i
+// k1 n2 / n} ([k1 <= R1/2][n2], s = sqrt(2/n) forward, half of it inverse)
+// and, with walls, the rotations e^{-+ i pi k / 2n}, k <= n/2 (k = 0 carries
+// the constant mode's normalisation).  Angles reduced exactly, long double.
+static void fft_tables(int n, bool walls, std::vector<double> (&out)[4])
+{
+    int r1 = 0, r2 = 0;
+    fft_radices(n, r1, r2);
+    const long double pi = 3.141592653589793238462643383279502884L, s = std::sqrt(2.0L / n), r = std::sqrt(2.0L);
+    for (int k1 = 0; k1 <= r1 / 2; ++k1)
+        for (int n2 = 0; n2 < r2; ++n2) {
+            const long double th = 2.0L * pi * (long double)((k1 * n2) % n) / n;
+            const long double c = std::cos(th), sn = std::sin(th);
+            out[0].push_back((double)(s * c));
+            out[0].push_back((double)(-s * sn));
+            out[1].push_back((double)(0.5L * s * c));
+            out[1].push_back((double)(0.5L * s * sn));
+        }
+    for (int k = 0; walls && k <= n / 2; ++k) {
+        const long double th = pi * (long double)k / (2.0L * n), c = std::cos(th), sn = std::sin(th);
+        out[2].push_back((double)(k ? c : 1.0L / r));
+        out[2].push_back((double)-sn);
+        out[3].push_back((double)(k ? c : r));
+        out[3].push_back((double)sn);
+    }
+}
 
 // basis: -1 the periodic Fourier basis; XK_* a wall-bounded x basis (never
 // folded: the folds rest on the Fourier basis's mirror symmetry), on the
@@ -438,6 +485,10 @@ static std::shared_ptr<const AxisTables> build_axis(int n, double h, bool z_axis
     if (basis < 0) fourier_basis(n, h, t->Q, t->lam);
     else if (faces.empty()) wall_basis(n, h, basis, t->Q, t->lam);
     else if (!stretched_basis(n, faces, basis, t->Q, t->Qi, t->lam)) return nullptr;
+    if (fft_axis(n, basis, !faces.empty())) {
+        fft_tables(n, basis >= 0, t->fft);
+        return t;
+    }
     const std::vector<double> &Q = t->Q;
     const std::vector<double> &Gi = t->Qi.empty() ? t->Q : t->Qi;   // inverse basis
     const int hn = n / 2;
@@ -476,17 +527,12 @@ static std::shared_ptr<const AxisTables> build_axis(int n, double h, bool z_axis
         }
     }
     if (split) {
-        if (fourier && can_fold_split(n)) {
+        if (z_axis && fourier && can_fold_split(n)) {
             FoldFactors f(Q, n);
             t->split[0].resize(size_t(3) * 2 * h2);
             t->split[1].resize(size_t(3) * 2 * h2);
-            if (!z_axis) {
-                swizzle_split_pair(f.c, f.s_fwd, hn, false, t->split[0].data());   // forward: E Qc, O Qs
-                swizzle_split_pair(f.transposed(f.c), f.transposed(f.s_inv), hn, false, t->split[1].data());
-            } else {
-                swizzle_split_pair(f.transposed(f.c), f.transposed(f.s_fwd), hn, true, t->split[0].data());
-                swizzle_split_pair(f.c, f.s_inv, hn, true, t->split[1].data());
-            }
+            swizzle_split_pair(f.transposed(f.c), f.transposed(f.s_fwd), hn, true, t->split[0].data());
+            swizzle_split_pair(f.c, f.s_inv, hn, true, t->split[1].data());
         } else {
             std::vector<double> tq(size_t(n) * n), tg(size_t(n) * n);
             for (int i = 0; i < n; ++i)
@@ -801,6 +847,10 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     }
     const int nxk = p->wx ? NUM_XK : 1;   // distinct x tables
     const int nzk = p->wz ? NUM_XK : 1;   // distinct z tables
+    for (int k = 0; k < NUM_XK; ++k) {
+        p->fx[k] = !ax[k]->fft[0].empty();
+        p->fz[k] = !az[k]->fft[0].empty();
+    }
 
     // blob layout
     BlobLayout &L = p->lay;
@@ -809,12 +859,14 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     const bool fold_x = x_folds(*p), fold_z = z_folds(*p);
     const size_t hx2 = size_t(nx / 2) * (nx / 2), hz2 = size_t(nz / 2) * (nz / 2);
     for (int k = 0; k < NUM_XK; ++k) {
-        L.bx_fwd[k] = k < nxk ? take(fold_x ? 0 : sizeof(double) * nx * nx) : L.bx_fwd[0];
-        L.bx_inv[k] = k < nxk ? take(fold_x ? 0 : sizeof(double) * nx * nx) : L.bx_inv[0];
+        const size_t dense = !fold_x && !p->fx[k] ? sizeof(double) * nx * nx : 0;
+        L.bx_fwd[k] = k < nxk ? take(dense) : L.bx_fwd[0];
+        L.bx_inv[k] = k < nxk ? take(dense) : L.bx_inv[0];
     }
     for (int k = 0; k < NUM_XK; ++k) {
-        L.az_fwd[k] = k < nzk ? take(fold_z ? 0 : sizeof(double) * nz * nz) : L.az_fwd[0];
-        L.az_inv[k] = k < nzk ? take(fold_z ? 0 : sizeof(double) * nz * nz) : L.az_inv[0];
+        const size_t dense = !fold_z && !p->fz[k] ? sizeof(double) * nz * nz : 0;
+        L.az_fwd[k] = k < nzk ? take(dense) : L.az_fwd[0];
+        L.az_inv[k] = k < nzk ? take(dense) : L.az_inv[0];
     }
     L.fx_fwd_c = take(fold_x ? sizeof(double) * hx2 : 0);
     L.fx_fwd_s = take(fold_x ? sizeof(double) * hx2 : 0);
@@ -824,6 +876,11 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.fz_fwd_s = take(fold_z ? sizeof(double) * hz2 : 0);
     L.fz_inv_c = take(fold_z ? sizeof(double) * hz2 : 0);
     L.fz_inv_s = take(fold_z ? sizeof(double) * hz2 : 0);
+    // fast transforms: one table set per axis (the wall kinds share it)
+    const bool f32[2] = {split && nx > FFT_F64_ARITH_MAX, split && nz > FFT_F64_ARITH_MAX};   // arithmetic of x, z
+    size_t *const fat[2][4] = {{&L.ftx_fwd, &L.ftx_inv, &L.frx_fwd, &L.frx_inv},
+                               {&L.ftz_fwd, &L.ftz_inv, &L.frz_fwd, &L.frz_inv}};
+    for (int i = 0; i < 8; ++i) *fat[i / 4][i % 4] = take((f32[i / 4] ? sizeof(float) : sizeof(double)) * (i < 4 ? ax : az)[0]->fft[i % 4].size());
     for (int k = 0; k < NUM_XK; ++k) L.lam_x[k] = k < nxk ? take(sizeof(double) * nx) : L.lam_x[0];
     for (int k = 0; k < NUM_XK; ++k) L.lam_z[k] = k < nzk ? take(sizeof(double) * nz) : L.lam_z[0];
     for (int kd = 0; kd < NUM_KINDS; ++kd) {
@@ -834,17 +891,17 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.wy = take(sizeof(double) * ny);
     L.dyc = take(sizeof(double) * ny);
     L.dyf = take(sizeof(double) * (ny + 1));
-    const bool sfold_x = split && x_folds_split(*p), sfold_z = split && z_folds_split(*p);
+    const bool sfold_z = split && z_folds_split(*p);
     for (int k = 0; k < NUM_XK; ++k) {
-        L.sx_fwd[k] = k < nxk ? take(split && !sfold_x ? sizeof(uint16_t) * 3 * nx * nx : 0) : L.sx_fwd[0];
-        L.sx_inv[k] = k < nxk ? take(split && !sfold_x ? sizeof(uint16_t) * 3 * nx * nx : 0) : L.sx_inv[0];
+        const size_t dense = split && !p->fx[k] ? sizeof(uint16_t) * 3 * nx * nx : 0;
+        L.sx_fwd[k] = k < nxk ? take(dense) : L.sx_fwd[0];
+        L.sx_inv[k] = k < nxk ? take(dense) : L.sx_inv[0];
     }
     for (int k = 0; k < NUM_XK; ++k) {
-        L.sz_fwd[k] = k < nzk ? take(split && !sfold_z ? sizeof(uint16_t) * 3 * nz * nz : 0) : L.sz_fwd[0];
-        L.sz_inv[k] = k < nzk ? take(split && !sfold_z ? sizeof(uint16_t) * 3 * nz * nz : 0) : L.sz_inv[0];
+        const size_t dense = split && !sfold_z && !p->fz[k] ? sizeof(uint16_t) * 3 * nz * nz : 0;
+        L.sz_fwd[k] = k < nzk ? take(dense) : L.sz_fwd[0];
+        L.sz_inv[k] = k < nzk ? take(dense) : L.sz_inv[0];
     }
-    L.sxf_fwd = take(sfold_x ? sizeof(uint16_t) * 3 * 2 * hx2 : 0);
-    L.sxf_inv = take(sfold_x ? sizeof(uint16_t) * 3 * 2 * hx2 : 0);
     L.szf_fwd = take(sfold_z ? sizeof(uint16_t) * 3 * 2 * hz2 : 0);
     L.szf_inv = take(sfold_z ? sizeof(uint16_t) * 3 * 2 * hz2 : 0);
     // FP64 lane of the refined pressure pencils: a 32-wide x-tile of z-mode
@@ -875,13 +932,13 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.lane_list = take(sizeof(int) * lane_list.size());
     L.sgx = take(p->sx ? sizeof(double) * SG_SLOTS * nx : 0);
     L.sgz = take(p->sz ? sizeof(double) * SG_SLOTS * nz : 0);
-    L.total = o;
-    p->blob.assign(L.total, 0);
+    L.total = std::max(o, MIN_CONST_BYTES);   // reported; only the tables themselves are uploaded
+    p->blob.assign(o, 0);
     auto put = [&](size_t off, const double *src, size_t n) {
-        std::memcpy(p->blob.data() + off, src, n * sizeof(double));
+        if (n) std::memcpy(p->blob.data() + off, src, n * sizeof(double));
     };
     auto put16 = [&](size_t off, const std::vector<uint16_t> &src) {
-        std::memcpy(p->blob.data() + off, src.data(), src.size() * sizeof(uint16_t));
+        if (!src.empty()) std::memcpy(p->blob.data() + off, src.data(), src.size() * sizeof(uint16_t));
     };
     if (fold_x) {
         put(L.fx_fwd_c, ax[0]->f64[0].data(), hx2);
@@ -890,8 +947,8 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
         put(L.fx_inv_s, ax[0]->f64[3].data(), hx2);
     } else {
         for (int k = 0; k < nxk; ++k) {
-            put(L.bx_fwd[k], ax[k]->f64[0].data(), size_t(nx) * nx);
-            put(L.bx_inv[k], ax[k]->f64[1].data(), size_t(nx) * nx);
+            put(L.bx_fwd[k], ax[k]->f64[0].data(), ax[k]->f64[0].size());
+            put(L.bx_inv[k], ax[k]->f64[1].data(), ax[k]->f64[1].size());
         }
     }
     if (fold_z) {
@@ -901,19 +958,14 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
         put(L.fz_inv_s, az[0]->f64[3].data(), hz2);
     } else {
         for (int k = 0; k < nzk; ++k) {
-            put(L.az_fwd[k], az[k]->f64[0].data(), size_t(nz) * nz);
-            put(L.az_inv[k], az[k]->f64[1].data(), size_t(nz) * nz);
+            put(L.az_fwd[k], az[k]->f64[0].data(), az[k]->f64[0].size());
+            put(L.az_inv[k], az[k]->f64[1].data(), az[k]->f64[1].size());
         }
     }
     if (split) {
-        if (sfold_x) {
-            put16(L.sxf_fwd, ax[0]->split[0]);
-            put16(L.sxf_inv, ax[0]->split[1]);
-        } else {
-            for (int k = 0; k < nxk; ++k) {
-                put16(L.sx_fwd[k], ax[k]->split[0]);
-                put16(L.sx_inv[k], ax[k]->split[1]);
-            }
+        for (int k = 0; k < nxk; ++k) {
+            put16(L.sx_fwd[k], ax[k]->split[0]);
+            put16(L.sx_inv[k], ax[k]->split[1]);
         }
         if (sfold_z) {
             put16(L.szf_fwd, az[0]->split[0]);
@@ -924,6 +976,15 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
                 put16(L.sz_inv[k], az[k]->split[1]);
             }
         }
+    }
+    for (int i = 0; i < 8; ++i) {
+        const std::vector<double> &t = (i < 4 ? ax : az)[0]->fft[i % 4];
+        if (!f32[i / 4]) {
+            put(*fat[i / 4][i % 4], t.data(), t.size());
+            continue;
+        }
+        float *to = reinterpret_cast<float *>(p->blob.data() + *fat[i / 4][i % 4]);
+        for (size_t q = 0; q < t.size(); ++q) to[q] = (float)t[q];
     }
     if (!lane_mask.empty()) std::memcpy(p->blob.data() + L.lane_mask, lane_mask.data(), 4 * lane_mask.size());
     if (!lane_list.empty()) std::memcpy(p->blob.data() + L.lane_list, lane_list.data(), 4 * lane_list.size());

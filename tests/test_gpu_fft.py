@@ -1,0 +1,52 @@
+"""Fast transforms on the GPU: every line length along x and z, periodic and
+walled, both precisions, through Helmholtz solves of known fields (r = A x
+formed by the stencil of residual(), which shares no code with the solve)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SIZES_32 = list(range(32, 513, 32))
+SIZES_16 = [16, 48, 80, 112, 144, 176, 208, 240, 336, 400, 432]
+# c |lambda| <= 2 at the smallest cell: condition number below 10.  FP64: five
+# stages of at most 4 ulps each and the stencil's own rounding, times that
+# condition: under 1e-13; refined: the solve's own tolerance
+TOL = {False: 1e-13, True: 1e-10}
+
+
+@pytest.fixture(scope="module")
+def ibs():
+    from paper_2406_19920_amd import ibsolve
+    assert torch.cuda.is_available()
+    return ibsolve
+
+
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("refined", [False, True])
+@pytest.mark.parametrize("n", SIZES_32 + SIZES_16)
+def test_every_length(ibs, n, refined, walls):
+    if refined and n % 32:
+        pytest.skip("the refined path takes multiples of 32")
+    kw = dict(bc_x=ibs.IBS_DIRICHLET, bc_z=ibs.IBS_DIRICHLET) if walls else {}
+    for nx, nz in ((n, 32), (32, n)):
+        print("case fft", nx, nz, refined, walls, flush=True)
+        S = ibs.Solver(nx, 5, nz, beta=0.5, precision=ibs.IBS_REFINED_BF16X3 if refined else ibs.IBS_FP64, **kw)
+        c = 0.125 / max(nx, nz) ** 2
+        xs, rs = [], []
+        for comp in range(3):
+            g = torch.Generator(device="cuda")
+            g.manual_seed(10 * n + comp)
+            x = torch.randn(S.shape(comp + 1), generator=g, dtype=torch.float64, device="cuda")
+            if comp == 1:
+                x[:, 0] = 0
+                x[:, 5] = 0
+            if walls and comp == 0:
+                x[:, :, 0] = 0
+            if walls and comp == 2:
+                x[0] = 0
+            xs.append(x)
+            rs.append(-S.residual(comp + 1, c, x, torch.zeros_like(x)))
+        got = S.helmholtz([0, 1, 2], [c] * 3, rs)
+        for comp in range(3):
+            err = float((got[comp] - xs[comp]).norm() / xs[comp].norm())
+            assert err < TOL[refined], (nx, nz, comp, err)
