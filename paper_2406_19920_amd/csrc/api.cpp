@@ -873,8 +873,8 @@ ibs_status ibs_plan_export(ibs_plan plan, int32_t table, double *out, size_t *n)
     const std::vector<double> *v = nullptr;
     switch (table) {
     case 0: v = &p.yf; break;
-    case 1: v = &p.qx[XK_P]; break;
-    case 2: v = &p.qz[XK_P]; break;
+    case 1: v = p.qx[XK_P].get(); break;
+    case 2: v = p.qz[XK_P].get(); break;
     case 3: v = &p.lam_x[XK_P]; break;
     case 4: v = &p.lam_z[XK_P]; break;
     default:
@@ -887,11 +887,11 @@ ibs_status ibs_plan_export(ibs_plan plan, int32_t table, double *out, size_t *n)
             const int t = (table - 5 - 3 * NUM_KINDS) % 4;
             const bool zax = table - 5 - 3 * NUM_KINDS >= 4;
             const int k = (t % 2 == 0) ? XK_C : XK_F;
-            v = t < 2 ? (zax ? &p.qz[k] : &p.qx[k]) : (zax ? &p.lam_z[k] : &p.lam_x[k]);
+            v = t < 2 ? (zax ? p.qz[k].get() : p.qx[k].get()) : (zax ? &p.lam_z[k] : &p.lam_x[k]);
         } else if (table >= 25 && table < 25 + 2 * NUM_XK) {
             // the inverse bases of kind XK_P, XK_C, XK_F: x, then z
             const int k = (table - 25) % NUM_XK;
-            v = table - 25 < NUM_XK ? &p.gx[k] : &p.gz[k];
+            v = table - 25 < NUM_XK ? p.gx[k].get() : p.gz[k].get();
         } else if (table == 31) {
             v = &p.xf;
         } else if (table == 32) {

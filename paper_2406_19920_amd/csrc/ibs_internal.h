@@ -4,6 +4,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -164,9 +165,10 @@ struct Plan {
     double hx, hz;
     std::vector<double> yf, yc, dyc, dyf;          // grid
     std::vector<double> xf, zf;                    // x / z faces [n+1] (uniform: i h)
-    std::vector<double> qx[NUM_XK], qz[NUM_XK];    // Q[i][a], row-major n x n, per x / z kind
+    typedef std::shared_ptr<const std::vector<double>> Basis;   // shared with the axis cache
+    Basis qx[NUM_XK], qz[NUM_XK];                  // Q[i][a], row-major n x n, per x / z kind
                                                    // (forward: xhat_a = sum_i Q[i][a] x_i)
-    std::vector<double> gx[NUM_XK], gz[NUM_XK];    // inverse bases: x_i = sum_a G[i][a] xhat_a
+    Basis gx[NUM_XK], gz[NUM_XK];                  // inverse bases: x_i = sum_a G[i][a] xhat_a
                                                    // (G = Q unless stretched)
     std::vector<double> lam_x[NUM_XK], lam_z[NUM_XK];
     std::vector<double> lo[NUM_KINDS], di[NUM_KINDS], up[NUM_KINDS];

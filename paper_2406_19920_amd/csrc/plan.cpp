@@ -557,8 +557,8 @@ static std::shared_ptr<const AxisTables> build_axis(int n, double h, bool z_axis
 void plain_transform_table(const Plan &p, bool z_axis, int kind, bool inverse, std::vector<double> &out)
 {
     const int n = z_axis ? p.nz : p.nx;
-    const std::vector<double> &Q = z_axis ? p.qz[kind] : p.qx[kind];
-    const std::vector<double> &G = z_axis ? p.gz[kind] : p.gx[kind];
+    const std::vector<double> &Q = z_axis ? *p.qz[kind] : *p.qx[kind];
+    const std::vector<double> &G = z_axis ? *p.gz[kind] : *p.gx[kind];
     out.assign(size_t(n) * n, 0.0);
     std::vector<double> t(size_t(n) * n);
     const std::vector<double> &M = inverse ? G : Q;
@@ -838,11 +838,11 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
             return IBS_ERR_INVALID_ARG;
         }
     for (int k = 0; k < NUM_XK; ++k) {
-        p->qx[k] = ax[k]->Q;
-        p->gx[k] = ax[k]->Qi.empty() ? ax[k]->Q : ax[k]->Qi;
+        p->qx[k] = Plan::Basis(ax[k], &ax[k]->Q);
+        p->gx[k] = Plan::Basis(ax[k], ax[k]->Qi.empty() ? &ax[k]->Q : &ax[k]->Qi);
         p->lam_x[k] = ax[k]->lam;
-        p->qz[k] = az[k]->Q;
-        p->gz[k] = az[k]->Qi.empty() ? az[k]->Q : az[k]->Qi;
+        p->qz[k] = Plan::Basis(az[k], &az[k]->Q);
+        p->gz[k] = Plan::Basis(az[k], az[k]->Qi.empty() ? &az[k]->Q : &az[k]->Qi);
         p->lam_z[k] = az[k]->lam;
     }
     const int nxk = p->wx ? NUM_XK : 1;   // distinct x tables

@@ -36,7 +36,7 @@ static void check(const Plan &p, int basis)
         return reinterpret_cast<const fft::Cpx<T> *>(p.blob.data() + off);
     };
     const fft::Cpx<T> *twf = tab(p.lay.ftx_fwd), *twi = tab(p.lay.ftx_inv), *rf = tab(p.lay.frx_fwd), *ri = tab(p.lay.frx_inv);
-    const std::vector<double> &Q = p.qx[basis < 0 ? 0 : basis];
+    const std::vector<double> &Q = *p.qx[basis < 0 ? 0 : basis];
     std::mt19937_64 g(N);
     std::normal_distribution<double> nd;
     double worst_f = 0, worst_i = 0;
