@@ -124,9 +124,11 @@ static size_t red_doubles(const Plan &p, int op, int ncomp)
     return n;
 }
 
+static size_t state_bmax(const Plan &p) { return p.desc.precision == IBS_FP64 ? 0 : bmax_slots(p); }
+
 // State layout (after the fields, 256-byte aligned): bmean[4], done[4],
 // incompat[4], xsum[4][XSUM_SLOTS], compat[2 COMPAT_SLOTS], red[...],
-// bmax[4][BMAX_SLOTS], scale[4].
+// bmax[4][bmax_slots], refined path, scale[4].
 size_t state_bytes_for(const Plan &p, int op, int ncomp)
 {
     size_t o = align256(STATE_JOBS * sizeof(double));
@@ -134,7 +136,7 @@ size_t state_bytes_for(const Plan &p, int op, int ncomp)
     o += align256((size_t)STATE_JOBS * XSUM_SLOTS * sizeof(double));
     o += align256(2 * (size_t)COMPAT_SLOTS * sizeof(double));
     o += align256(red_doubles(p, op, ncomp) * sizeof(double));
-    o += align256((size_t)STATE_JOBS * BMAX_SLOTS * sizeof(double));
+    o += align256((size_t)STATE_JOBS * state_bmax(p) * sizeof(double));
     o += align256(STATE_JOBS * sizeof(double));
     return o;
 }
@@ -157,7 +159,7 @@ State state_in(const Plan &p, void *work, int op, int ncomp)
     st.upd_region = p.desc.precision == IBS_FP64 ? 0 : update_region(p, op == IBS_OP_POISSON ? 1 : ncomp);
     b += align256(st.red_count * sizeof(double));
     st.bmax = reinterpret_cast<double *>(b);
-    b += align256((size_t)STATE_JOBS * BMAX_SLOTS * sizeof(double));
+    b += align256((size_t)STATE_JOBS * state_bmax(p) * sizeof(double));
     st.scale = reinterpret_cast<double *>(b);
     return st;
 }
@@ -340,7 +342,7 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
             ss.j[q].xs = xs32 ? static_cast<void *>(W3[q]) : static_cast<void *>(ss.j[q].x);
         if (pass > 0) {
             if (pass == 1) {
-                e = launch_residual_scale(ss, st, s);
+                e = launch_residual_scale(ss, p, st, s);
                 if (e != hipSuccess) return hip_fail(e, "residual scale");
             }
             for (int q = 0; q < ss.n; ++q) ss.j[q].r = W2[q];

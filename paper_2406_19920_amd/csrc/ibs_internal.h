@@ -74,7 +74,6 @@ constexpr int RESID_SLOTS = 4096;    // max blocks of the residual() norm reduct
 constexpr int FFT_RW = 16;           // rows per block of the fast x transforms
 constexpr int MAX_PASSES = 8;        // most refinement passes a solve may take (max_iter)
 constexpr int MAX_PLANES = 1024;     // largest nz a plan accepts
-constexpr int BMAX_SLOTS = 2048;     // partial maxima per job (two halves of 1024 blocks)
 // Smallest cell width a plan accepts, as a fraction of the domain length
 // along that axis.  The operators' condition numbers grow as the inverse
 // square of it: below about 1e-7 (tanh stretching beyond beta = 8 at 64
@@ -106,8 +105,8 @@ struct State {
     double *red = nullptr;     // refinement update partials, then residual() partials
     size_t red_count = 0;      // doubles in red
     size_t upd_region = 0;     // doubles of red one refinement pass takes
-    double *bmax = nullptr;    // per job: partial maxima of the first pass's pencil data
-                               // (BMAX_SLOTS each: the FP32 tiles' blocks, then the FP64 lane's)
+    double *bmax = nullptr;    // per job: largest magnitude of the first pass's pencil data
+                               // per z-mode and 16-wide x-tile (bmax_slots() each)
     double *scale = nullptr;   // per job: power of two sigma the refinement passes scale
                                // their FP32 residuals by
 };
@@ -235,6 +234,8 @@ inline int comp_zkind(const Plan &p, int comp)
     return !p.wz ? XK_P : (comp == 2 ? XK_F : XK_C);
 }
 
+inline int bmax_slots(const Plan &p) { return p.nz * (p.nx / 16); }
+
 // Workspace of one solve call: the work fields and the state after them.
 size_t field_bytes_for(const Plan &p, int op, int ncomp);
 size_t state_bytes_for(const Plan &p, int op, int ncomp);
@@ -356,7 +357,7 @@ int residual_tiles(const Plan &p);   // residual blocks (x-sum partials) per job
 // After pass >= 1: predict the error, write the report, set the stop flag.
 // pass 0 (a one-pass solve): no estimate exists; the report says so.
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s);
-hipError_t launch_residual_scale(const SplitSet &ss, const State &st, hipStream_t s);
+hipError_t launch_residual_scale(const SplitSet &ss, const Plan &p, const State &st, hipStream_t s);
 
 // ---- fast transforms (k_fft.h; p.fx / p.fz kinds only) ---------------------
 // One pass over each job's field, js.j[q].in to .out (which may be the same

@@ -1080,20 +1080,20 @@ int residual_tiles(const Plan &p)
 
 // Power-of-two scale sigma of each job's FP32 residuals (refinement
 // passes): from the largest magnitude of the first pass's pencil data (the
-// block maxima its tridiagonal launches recorded; an orthonormal transform
+// tile maxima its tridiagonal launches recorded; an orthonormal transform
 // of the rhs, within a factor sqrt(n) of its largest entry), sigma =
 // 2^-e with 2^e <= that maximum < 2^(e+1), so the residuals, about the
 // first pass's relative error times the rhs, stay far inside the FP32 and
 // bfloat16 exponent range whatever the rhs's own magnitude.  Scaling by a
 // power of two is exact: it changes no rounding unless a value would
 // otherwise leave that range.  One block per job, a fixed reduction order.
-__global__ __launch_bounds__(256) void residual_scale_kernel(const double *__restrict__ bmax,
+__global__ __launch_bounds__(256) void residual_scale_kernel(const double *__restrict__ bmax, int slots,
                                                              double *__restrict__ scale)
 {
     __shared__ double sm[4];
     const int job = blockIdx.x;
     double m = 0.0;
-    for (int q = threadIdx.x; q < BMAX_SLOTS; q += blockDim.x) m = fmax(m, bmax[(size_t)job * BMAX_SLOTS + q]);
+    for (int q = threadIdx.x; q < slots; q += blockDim.x) m = fmax(m, bmax[(size_t)job * slots + q]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = fmax(m, __shfl_xor(m, d, 64));
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
@@ -1109,9 +1109,9 @@ __global__ __launch_bounds__(256) void residual_scale_kernel(const double *__res
     }
 }
 
-hipError_t launch_residual_scale(const SplitSet &ss, const State &st, hipStream_t s)
+hipError_t launch_residual_scale(const SplitSet &ss, const Plan &p, const State &st, hipStream_t s)
 {
-    hipLaunchKernelGGL(residual_scale_kernel, dim3(ss.n), dim3(256), 0, s, st.bmax, st.scale);
+    hipLaunchKernelGGL(residual_scale_kernel, dim3(ss.n), dim3(256), 0, s, st.bmax, bmax_slots(p), st.scale);
     return hipGetLastError();
 }
 

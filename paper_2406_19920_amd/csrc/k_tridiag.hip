@@ -9,20 +9,33 @@ namespace ibs {
 template <typename T, typename R>
 static hipError_t launch_by_rows(const JobSet &js, const TriParams &tp, int n, hipStream_t s)
 {
-    // lanes per pencil and rows per lane: short chunks keep the per-lane
-    // arrays in registers
-    if (n <= 48) return launch_pm<T, R, 16, 3>(js, tp, s);
-    if (n <= 80) return launch_pm<T, R, 16, 5>(js, tp, s);
-    if (n <= 112) return launch_pm<T, R, 16, 7>(js, tp, s);
-    if (n <= 144) return launch_pm<T, R, 16, 9>(js, tp, s);
-    if (n <= 224) return launch_pm<T, R, 32, 7>(js, tp, s);
-    if (n <= 256) return launch_pm<T, R, 32, 8>(js, tp, s);
-    if (n <= 288) return launch_pm<T, R, 32, 9>(js, tp, s);
-    if (n <= 352) return launch_pm<T, R, 32, 11>(js, tp, s);
-    if (n <= 416) return launch_pm<T, R, 32, 13>(js, tp, s);
-    if (n <= 544) return launch_pm<T, R, 32, 17>(js, tp, s);
-    if (n <= 672) return launch_pm<T, R, 32, 21>(js, tp, s);
-    if (n <= 800) return launch_pm<T, R, 32, 25>(js, tp, s);
+    // chunks per pencil and rows per chunk: 16 chunks while the rows of one
+    // fit the registers.  Beyond: FP32 more chunks of 16 rows; FP64 32 chunks,
+    // whose 12 or fewer rows leave two 8-wave blocks per CU (384 rows of
+    // 512x384x384: 733 us for three fields, 24 chunks of 16 rows 1069).
+    if (n <= 32) return launch_pm<T, R, 8, 4>(js, tp, s);
+    if (n <= 64) return launch_pm<T, R, 16, 4>(js, tp, s);
+    if (n <= 96) return launch_pm<T, R, 16, 6>(js, tp, s);
+    if (n <= 128) return launch_pm<T, R, 16, 8>(js, tp, s);
+    if (n <= 160) return launch_pm<T, R, 16, 10>(js, tp, s);
+    if (n <= 192) return launch_pm<T, R, 16, 12>(js, tp, s);
+    if constexpr (sizeof(R) == 4) {
+        // at most one tile per CU: nothing else hides a tile's own latency,
+        // so shorter chunks
+        if (n <= 256 && tp.nx / 32 * tp.nz * js.n <= 256) return launch_pm<T, R, 32, 8>(js, tp, s);
+        if (n <= 256) return launch_pm<T, R, 16, 16>(js, tp, s);
+        if (n <= 320) return launch_pm<T, R, 20, 16>(js, tp, s);
+        if (n <= 384) return launch_pm<T, R, 24, 16>(js, tp, s);
+        if (n <= 512) return launch_pm<T, R, 32, 16>(js, tp, s);
+        if (n <= 768) return launch_pm<T, R, 32, 24>(js, tp, s);
+    } else {
+        if (n <= 224) return launch_pm<T, R, 16, 14>(js, tp, s);
+        if (n <= 256) return launch_pm<T, R, 16, 16>(js, tp, s);
+        if (n <= 320) return launch_pm<T, R, 32, 10>(js, tp, s);
+        if (n <= 384) return launch_pm<T, R, 32, 12>(js, tp, s);
+        if (n <= 512) return launch_pm<T, R, 32, 16>(js, tp, s);
+        if (n <= 768) return launch_pm<T, R, 48, 16>(js, tp, s);
+    }
     return hipErrorInvalidValue;
 }
 

@@ -11,16 +11,20 @@ template <typename T, typename R>
 static hipError_t launch_cyclic(const JobSet &js, const TriParams &tp, int n, hipStream_t s)
 {
     switch (n) {
-    case 48: return launch_pm<T, R, 16, 3, true>(js, tp, s);
+    case 48: return launch_pm<T, R, 12, 4, true>(js, tp, s);
     case 64: return launch_pm<T, R, 16, 4, true>(js, tp, s);
-    case 80: return launch_pm<T, R, 16, 5, true>(js, tp, s);
-    case 96: return launch_pm<T, R, 32, 3, true>(js, tp, s);
-    case 128: return launch_pm<T, R, 32, 4, true>(js, tp, s);
-    case 160: return launch_pm<T, R, 32, 5, true>(js, tp, s);
-    case 192: return launch_pm<T, R, 32, 6, true>(js, tp, s);
-    case 256: return launch_pm<T, R, 32, 8, true>(js, tp, s);
-    case 320: return launch_pm<T, R, 32, 10, true>(js, tp, s);
-    case 384: return launch_pm<T, R, 32, 12, true>(js, tp, s);
+    case 80: return launch_pm<T, R, 20, 4, true>(js, tp, s);
+    case 96: return launch_pm<T, R, 12, 8, true>(js, tp, s);
+    case 128: return launch_pm<T, R, 16, 8, true>(js, tp, s);
+    case 160: return launch_pm<T, R, 20, 8, true>(js, tp, s);
+    case 192: return launch_pm<T, R, 16, 12, true>(js, tp, s);
+    case 256: return launch_pm<T, R, 16, 16, true>(js, tp, s);
+    case 320:
+        if constexpr (sizeof(R) == 4) return launch_pm<T, R, 20, 16, true>(js, tp, s);
+        else return launch_pm<T, R, 32, 10, true>(js, tp, s);
+    case 384:
+        if constexpr (sizeof(R) == 4) return launch_pm<T, R, 24, 16, true>(js, tp, s);
+        else return launch_pm<T, R, 32, 12, true>(js, tp, s);
     case 512: return launch_pm<T, R, 32, 16, true>(js, tp, s);
     default: return hipErrorInvalidValue;
     }

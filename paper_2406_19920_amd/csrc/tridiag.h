@@ -9,22 +9,33 @@
 //   Helmholtz : -c lo_j x_{j-1} + (1 - c s - c di_j) x_j - c up_j x_{j+1} = r_j
 // The Neumann (0,0) pressure pencil is singular: its right-hand side is
 // first made compatible (its volume-weighted mean removed), its first point
-// is pinned to zero (as in Section 2.3.3, item S2.1), and after the solve
-// the weighted mean is removed, which fixes the null mode at zero mean.
+// is pinned to zero (as in Section 2.3.3, item S2.1) and the rest follows by
+// summing fluxes, and after the solve the weighted mean is removed, which
+// fixes the null mode at zero mean.
 //
 // Layout and parallel scheme (an MI355X design, not the paper's
-// thread-per-pencil Thomas sweep): a tile is 16 (8 or 32, by arithmetic
-// type) consecutive x-modes of one z-plane, all rows.  Persistent workgroups walk the tiles in
-// adjacent pairs; each tile is read row by row into registers while the
-// previous tile is being solved, then staged through LDS.  Each pencil is
-// split into P (16 or 32) chunks of M consecutive rows, one lane per chunk.
-// Every lane eliminates its chunk with two local sweeps (down and up),
-// leaving one equation per lane that couples the last unknowns of
-// neighbouring chunks; that reduced tridiagonal system of P equations is
-// solved by parallel cyclic reduction with wavefront shuffles; the lanes
-// then back-substitute their interiors.  Rows beyond the system size are
-// identity rows.  The arithmetic is FP64, or FP32 for Helmholtz launches
-// whose pencil condition numbers are provably small (refined path).
+// thread-per-pencil Thomas sweep): a block solves a tile of TA consecutive
+// x-modes (one 128-byte line of a row) of one z-plane, all rows.  Each pencil
+// is split into P chunks of M consecutive rows, one thread per chunk, lanes
+// along the pencils: a thread reads its M rows straight into registers (whole
+// lines per row, all loads in flight together) and writes them back from
+// there; no staging.  It eliminates its chunk with two local sweeps (down and
+// up), leaving one equation that couples the last unknowns of neighbouring
+// chunks.  The reduced tridiagonal system of P equations per pencil goes
+// through LDS to two lanes per pencil, which eliminate it from both ends,
+// meet in the middle and substitute back (P/2 dependent steps; cyclic
+// systems: with a second right-hand side for the unknown the ring is cut
+// at); then every thread back-substitutes its interior.  Rows beyond the
+// system size are identity rows.
+//
+// Bound by memory (each value read and written once) and, where few blocks
+// fit a CU, by a tile's own latency.  Measured, us per launch, against lanes
+// along the rows with the tile staged through LDS and the reduced system by
+// parallel cyclic reduction: FP64 three 256^3 fields 200 (228), one 61 (77);
+// 512x384x384 three fields 733 (912), 4.9 TB/s; 176x101x208 three 35 (50);
+// FP32 arithmetic, three 256^3 fields 75 (122).
+// The arithmetic is FP64, or FP32 for Helmholtz launches whose pencil
+// condition numbers are provably small (refined path).
 #pragma once
 #include "ibs_internal.h"
 
@@ -42,36 +53,6 @@ static __device__ __forceinline__ double rcp64(double d)
     x = fma(x, e, x);
     e = fma(-d, x, 1.0);
     return fma(x, e, x);
-}
-
-// Raw buffer access with the hardware range check: offsets at or beyond the
-// resource's byte count load 0 and drop stores.  The whole offset goes in
-// the vector operand (the scalar offset is outside the range check).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <typename T>
-static __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff);
-template <>
-__device__ __forceinline__ double buf_load<double>(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, 0));
-}
-template <>
-__device__ __forceinline__ float buf_load<float>(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
-}
-static __device__ __forceinline__ void buf_store_raw(double v, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, voff, soff, 0);
-}
-static __device__ __forceinline__ void buf_store_raw(float v, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rs, voff, soff, 0);
-}
-template <typename T>
-static __device__ __forceinline__ void buf_store(T v, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    buf_store_raw(v, rs, voff, soff);
 }
 
 // 1/d in the arithmetic type: FP64 as above; FP32 from the hardware
@@ -107,14 +88,77 @@ struct TriParams {
     const int *lane_list;        // FP64-lane tiles as (c << 8) | t
     int lane_len;
     int lane_mode;
-    // refined path: the first pass's launches record per-job partial maxima
-    // of their pencil data (BMAX_SLOTS per job, one per block: the FP32
-    // tiles' launch the first half, the FP64 lane's the second), from which
-    // the refinement passes take the power of two sigma that scales their
-    // FP32 residuals; those passes then steer the mean in sigma units
-    double *bmax;          // first pass: partial maxima, or null
+    // refined path: the first pass's launches record the largest magnitude of
+    // their pencil data per 16-wide x-tile and z-mode (bmax_slots() per job;
+    // the FP64 lane's tiles by its own launch), from which the refinement
+    // passes take the power of two sigma that scales their FP32 residuals;
+    // those passes then steer the mean in sigma units
+    double *bmax;          // first pass: the maxima, or null
     const double *scale;   // later passes: per job sigma, or null (1)
 };
+
+// The singular pressure pencil, in LDS, by one wave: y holds n right-hand
+// side values on entry and the solution on return.  The volume-weighted mean
+// of the right-hand side is removed (and returned); the rest is solved by
+// summing fluxes, not by elimination (which loses digits with the square of
+// the row count on a singular matrix): the flux through the face above row j
+// is F_j = sum_{i <= j} Delta_i (b_i - mean), and x rises by delta_{j+1} F_j
+// across it (wt: Delta_j, dl: delta_{j+1} = 1/(up_j Delta_j); 0 past the last
+// row of a walled system), from x_0 = 0; cyclic: plus the constant flux that
+// closes the ring.  Then the weighted mean of x is removed, and steer with it
+// (refinement: so that x + d has zero weighted mean, in this pencil's
+// normalisation).
+template <int NR, bool CYC>
+static __device__ __forceinline__ double singular_pencil(double *y, int n, const double *wt, const double *dl,
+                                                         double steer)
+{
+    constexpr int RL = (NR + 63) / 64;   // rows per lane
+    const int lane = threadIdx.x, j0 = lane * RL, j1 = min(n, j0 + RL);
+    auto total = [](double v) {
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+        return v;
+    };
+    auto below = [&](double v) {   // sum over the lanes below this one
+        double t = v;
+        for (int d = 1; d < 64; d <<= 1) {
+            const double o = __shfl_up(t, d, 64);
+            if (lane >= d) t += o;
+        }
+        return t - v;
+    };
+    double sv = 0.0, sw = 0.0;
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) {
+        sv += wt[j] * y[j];
+        sw += wt[j];
+    }
+    sw = total(sw);
+    const double mean = total(sv) / sw;
+    double f = 0.0, d = 0.0, ds = 0.0;
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) f += wt[j] * (y[j] - mean);
+    f = below(f);
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) {
+        f += wt[j] * (y[j] - mean);
+        y[j] = dl[j] * f;
+        d += y[j];
+        ds += dl[j];
+    }
+    const double f0 = CYC ? -total(d) / total(ds) : 0.0;
+    double x = below(d) + f0 * below(ds), sx = 0.0;
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) {
+        const double rise = y[j] + (CYC ? f0 * dl[j] : 0.0);
+        y[j] = x;
+        sx += wt[j] * x;
+        x += rise;
+    }
+    const double mx = total(sx) / sw + steer;
+#pragma unroll 1
+    for (int j = j0; j < j1; ++j) y[j] -= mx;
+    return mean;
+}
 
 // T: storage type of the field (double, or float on the refined path);
 // R: arithmetic type (double; float only for well-conditioned Helmholtz
@@ -122,394 +166,273 @@ struct TriParams {
 // CYC: cyclic systems (periodic y: row 0 couples to row n-1 and row n-1 to
 // row 0 through the operator's corner coefficients lo[0], up[n-1]); the
 // system then fills the P chunks exactly (n = P M, no padding rows) and the
-// reduced system of the chunk ends is itself cyclic: its parallel cyclic
-// reduction takes the neighbours at distance d modulo P, and after the last
-// step (d = P/2, where both neighbours are the lane itself) each equation
-// reads (EA + EB + EC) z = ED.
-// BMX: this launch records the partial maxima (the refined path's first
-// pass); a separate instantiation, so that no other launch carries the
-// tracking.
-// Registers: FP32 arithmetic is held to four waves per SIMD up to 9 rows per
-// lane, and up to 13 for the non-cyclic systems (a few registers spill
-// there, but two 8-wave blocks per CU instead of one: the 384-row pencils
-// of 512x384x384 run 4 % faster); the rest is left to the compiler.
-template <typename T, typename R, int P, int M, int TA, bool CYC = false, bool BMX = false>
-__global__ __launch_bounds__(TA * P, (sizeof(R) == 4 && (M <= 9 || (!CYC && M <= 13))) ? 4 : 1) void tridiag_kernel(JobSet js, TriParams tp, int ntx,
-                                                         int ntiles)
+// reduced system of the chunk ends is itself cyclic.
+// BMX: this launch records the maxima (the refined path's first pass).
+// Waves per SIMD the registers are held to: what the three per-chunk arrays
+// leave room for (16 rows: a dozen values spill, and the third 8-wave block
+// per CU in FP32, the fourth 4-wave one in FP64, pays for them: 75 instead of
+// 87 us for three 256^3 FP32 fields).  16-wave blocks: one per CU.
+template <typename R, int P, int M, int TA> constexpr int tri_waves()
 {
-    // TA: pencils per tile
-    constexpr int NT = TA * P;             // threads
-    constexpr int NR = P * M;              // padded rows
-    // LDS row of system row j: for even M each chunk of M rows is followed
-    // by one unused row, so the P lanes of a pencil, which walk rows M
-    // apart, hit distinct banks
-    constexpr int MS = M + (M % 2 == 0 ? 1 : 0);
-    constexpr int NRS = P * MS;            // LDS rows
-    auto lr = [](int j) {
-        if constexpr (MS == M) return j;
-        else return (j / M) * MS + j % M;
+    if (P * TA > 512 && sizeof(R) == 4) return M >= 16 && P * TA <= 768 ? 6 : 4;
+    return sizeof(R) == 4 ? (M <= 8 ? 8 : M <= 12 ? 7 : 6) : (M <= 4 ? 8 : M <= 6 ? 6 : M <= 8 ? 5 : 4);
+}
+template <typename T, typename R, int P, int M, int TA, bool CYC = false, bool BMX = false>
+__global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())) void tridiag_kernel(JobSet js, TriParams tp)
+{
+    static_assert(P % 2 == 0 && M >= 2 && 64 % TA == 0, "two solver lanes per pencil in one wave");
+    constexpr int NT = (TA * P + 63) / 64 * 64, NW = NT / 64;
+    struct alignas(4 * sizeof(R)) Row { R a, b, c, m; };   // row without the pencil shift; m: 1 if it takes one
+    __shared__ Row rows_sm[P * M];
+    __shared__ R ex[3][P][TA];    // chunk tops (lam, mu, sig); later z
+    __shared__ R eq[4][P][TA];    // reduced equations
+    __shared__ double xs_sm[NW];        // per-wave sums of the x-sum partials
+    // the singular pencil: right-hand side, then solution; weights Delta_j;
+    // distances delta_{j+1}
+    __shared__ double pin_sm[P * M], wt_sm[P * M], dl_sm[P * M];
+
+    const int tid = threadIdx.x, nx = tp.nx, job = blockIdx.y;
+    if (tp.skip && tp.skip[job]) return;   // converged (later refinement passes)
+    int c, a0;
+    if (tp.lane_mode == 2) {
+        constexpr int per = 32 / TA;
+        const int e = tp.lane_list[blockIdx.x / per];
+        c = e >> 8;
+        a0 = (e & 0xff) * 32 + (blockIdx.x % per) * TA;
+    } else {
+        const int ntx = nx / TA;
+        c = blockIdx.x / ntx;
+        a0 = (blockIdx.x - c * ntx) * TA;
+        // tiles left to the FP64 lane
+        if (tp.lane_mode == 1 && ((tp.lane_mask[c] >> (a0 >> 5)) & 1u)) return;
+    }
+    const FieldJob &jb = js.j[job];
+    // the v systems leave out the first wall row (kept at zero below)
+    const int kind = jb.kind, sys0 = skip_first_row(kind), n = jb.rows - sys0;
+    const bool walls = kind == KIND_F, pois = tp.poisson != 0;
+    const int p = tid % TA, k = tid / TA, s = k * M;
+    const bool act = k < P;
+    T *x = reinterpret_cast<T *>(jb.out) + ((size_t)c * jb.rows + sys0) * nx + a0 + p;
+    T raw[M];
+    if (act) {
+#pragma unroll
+        for (int t = 0; t < M; ++t) raw[t] = x[(size_t)min(s + t, n - 1) * nx];
+    }
+    const R cj = (R)jb.c;
+    const R sh = (R)(tp.lam_x[jb.xk][a0 + p] + tp.lam_z[jb.zk][c]);
+    const R sadd = pois ? sh : -cj * sh;               // pencil shift of the diagonal
+    const bool pt = pois && a0 == 0 && c == 0;         // block-uniform: the tile of the singular pencil
+    const bool pinned = pt && p == 0;
+    // rows of the job's operator without the pencil shift: Poisson (lo, di,
+    // up); Helmholtz (-c lo, 1 - c di, -c up); identity beyond the system
+    for (int j = tid; j < P * M; j += NT) {
+        Row w = {R(0), R(1), R(0), R(0)};
+        if (j < n) {
+            const R lo = (R)tp.lo[kind][j + sys0], di = (R)tp.di[kind][j + sys0], up = (R)tp.up[kind][j + sys0];
+            w = pois ? Row{lo, di, up, R(1)} : Row{-cj * lo, R(1) - cj * di, -cj * up, R(1)};
+        }
+        rows_sm[j] = w;
+        if (pt) {
+            wt_sm[j] = j < n ? tp.wy[j] : 0.0;
+            dl_sm[j] = j < (CYC ? n : n - 1) ? 1.0 / (tp.up[kind][j] * tp.wy[j]) : 0.0;
+        }
+    }
+    if (pt && tp.xsum) {
+        // refinement passes: the residual's partial sums of Delta_j x, summed
+        // by the whole block for the pinned pencil (fixed order: strided per
+        // thread, a butterfly per wave, the waves in order)
+        const double *xsp = tp.xsum + (size_t)job * XSUM_SLOTS;
+        double part = 0.0;
+        for (int q = tid; q < tp.nxsum; q += NT) part += xsp[q];
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
+        if ((tid & 63) == 0) xs_sm[tid >> 6] = part;
+    }
+    R r[M];
+#pragma unroll
+    for (int t = 0; t < M; ++t) r[t] = act && s + t < (walls ? n - 1 : n) ? (R)raw[t] : R(0);
+    if constexpr (BMX) {
+        float m = 0.f;
+#pragma unroll
+        for (int t = 0; t < M; ++t) m = fmaxf(m, fabsf((float)r[t]));
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+        __shared__ float mx_sm[NW];
+        if ((tid & 63) == 0) mx_sm[tid >> 6] = m;
+        __syncthreads();
+        if (tid < TA / 16) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m = fmaxf(m, mx_sm[w]);
+            tp.bmax[((size_t)job * tp.nz + c) * (nx / 16) + a0 / 16 + tid] = (double)m;
+        }
+    }
+    __syncthreads();
+    if (pinned && act)
+#pragma unroll
+        for (int t = 0; t < M; ++t) pin_sm[s + t] = (double)r[t];
+    auto coef = [&](int t, R &A, R &B, R &C) {
+        const Row w = rows_sm[(act ? s : 0) + t];
+        A = w.a;
+        B = w.b + w.m * sadd;
+        C = w.c;
     };
-    constexpr int LDR = TA + 1;            // LDS row stride (elements)
-    // Two staging buffers (alternate tiles) where they fit: a tile's
-    // staging then needs no barrier against the previous tile's write-back,
-    // which reads the other buffer (the barriers of the tile in between
-    // order it after the write-back of the tile before).
-    constexpr bool DB = P == 32 && M <= 9;
-    __shared__ R sx[(DB ? 2 : 1) * NRS * LDR];
-    __shared__ R slo[NRS], sdi[NRS], sup[NRS], sw[NRS];
-    __shared__ double xs_sm[NT / 64];   // per-wave sums of the x-sum partials
 
-    const int tid = threadIdx.x;
-    const int nx = tp.nx;
-    // staging role: thread loads rows lrow + P*r (r < M) of column lcol
-    const int lcol = tid % TA, lrow = tid / TA;
-    // solving role: pencil p (column), chunk k of M rows
-    const int p = tid / P, k = tid % P;
-    const int s = k * M;
-    const bool pois = tp.poisson != 0;
-    const uint32_t row_bytes = (uint32_t)nx * sizeof(T);
-
-    // converged jobs (later refinement passes): read once, block-uniform
-    int skipmask = 0;
-    if (tp.skip)
-        for (int q = 0; q < js.n; ++q) skipmask |= tp.skip[q] ? (1 << q) : 0;
-
-    // Every fetch issues the same M + 2 loads and every write-back the same
-    // M stores, whatever the tile: rows beyond the system, tiles beyond the
-    // last and tiles of converged jobs are handled by the buffer range check
-    // (loads return 0, stores are dropped).  With no loads or stores under
-    // branches, the wait before a tile is used covers only that tile's data
-    // and leaves the next tile's loads in flight.
-    auto plane_rsrc = [&](int job, int c, bool live) {
-        const FieldJob &jb = js.j[job];
-        const T *base = reinterpret_cast<const T *>(jb.out) + (size_t)c * jb.rows * nx;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), (short)0,
-                                                 live ? (int)(jb.rows * row_bytes) : 0, 0x00020000);
-    };
-    auto decode = [&](int tile, int &job, int &c, int &a0) {
-        if (tp.lane_mode == 2) {
-            // the listed 32-wide tiles, each as 32 / TA tiles of TA pencils
-            constexpr int per = 32 / TA;
-            const int per_job = tp.lane_len * per;
-            job = tile / per_job;
-            const int rem = tile - job * per_job;
-            const int e = tp.lane_list[rem / per];
-            c = e >> 8;
-            a0 = (e & 0xff) * 32 + (rem % per) * TA;
+    // down-sweep: rows s+1 .. s+M-1 in the form al x_s + x_j + ga x_{j+1} = rho
+    R al[M], ga[M];
+    {
+        R A, B, C;
+        coef(1, A, B, C);
+        R inv = rcpr(B);
+        al[1] = A * inv; ga[1] = C * inv; r[1] = r[1] * inv;
+#pragma unroll
+        for (int t = 2; t < M; ++t) {
+            coef(t, A, B, C);
+            inv = rcpr(B - A * ga[t - 1]);
+            al[t] = -A * al[t - 1] * inv;
+            ga[t] = C * inv;
+            r[t] = (r[t] - A * r[t - 1]) * inv;
+        }
+    }
+    // interior rows in terms of the chunk ends, x_j = bp + bq x_s + br x_e,
+    // by back-substitution (no divisions), then the top row
+    //   lam x_{s-1} + x_s + mu x_e = sig
+    R lam_u, mu_u, sig_u;
+    {
+        R A, B, C;
+        coef(0, A, B, C);
+        if (pinned && k == 0) { A = 0.0; B = 1.0; C = 0.0; }
+        if constexpr (M == 2) {
+            const R inv = rcpr(B);
+            lam_u = A * inv;
+            mu_u = C * inv;
+            sig_u = r[0] * inv;
         } else {
-            job = tile / (tp.nz * ntx);
-            const int rem = tile - job * tp.nz * ntx;
-            c = rem / ntx;
-            a0 = (rem - c * ntx) * TA;
+            R bp = r[M - 2], bq = -al[M - 2], br = -ga[M - 2];
+#pragma unroll
+            for (int t = M - 3; t >= 1; --t) {
+                bp = r[t] - ga[t] * bp;
+                bq = -al[t] - ga[t] * bq;
+                br = -ga[t] * br;
+            }
+            const R inv = rcpr(B + C * bq);
+            lam_u = A * inv;
+            mu_u = C * br * inv;
+            sig_u = (r[0] - C * bp) * inv;
         }
-    };
-    // maxima of |staged value| per job (BMX): each thread keeps a running
-    // maximum for the job of its current tiles and folds it into the job's
-    // LDS slot when the job changes (rarely: tiles run job by job) and at
-    // the end, by an integer max on the bit patterns (non-negative floats
-    // order as their patterns do)
-    __shared__ unsigned bmx_sm[BMX ? STATE_JOBS : 1];
-    float tmax = 0.f;
-    int tjob = -1;
-    if constexpr (BMX) {
-        if (tid < STATE_JOBS) bmx_sm[tid] = 0u;
-        __syncthreads();
     }
-    // tiles left to the FP64 lane (lane_mode 1): block-uniform
-    auto lane_skipped = [&](int c, int a0) {
-        return tp.lane_mode == 1 && ((tp.lane_mask[c] >> (a0 >> 5)) & 1u);
-    };
-    // raw values only: conversion and wall rows are applied when the tile is
-    // staged, so that nothing here waits for the loads
-    auto fetch = [&](int tile, T (&pf)[M], double &plx, double &plz) {
-        int job, c, a0;
-        decode(tile < ntiles ? tile : ntiles - 1, job, c, a0);
-        const bool live = tile < ntiles && !((skipmask >> job) & 1) && !lane_skipped(c, a0);
-        plx = tp.lam_x[js.j[job].xk][a0 + p];
-        plz = tp.lam_z[js.j[job].zk][c];
-        const auto rs = plane_rsrc(job, c, live);
-        const uint32_t sys0 = skip_first_row(js.j[job].kind);   // first row of the system
-        const uint32_t voff = (uint32_t)(a0 + lcol) * sizeof(T) + (lrow + sys0) * row_bytes;
-#pragma unroll
-        for (int r = 0; r < M; ++r) pf[r] = buf_load<T>(rs, voff + r * P * row_bytes, 0);
-    };
-
-    // two register buffers: the tile two steps ahead is in flight while the
-    // current one is solved (HBM latency is long next to one tile's work)
-    T pfa[M], pfb[M];
-    double lxa, lza, lxb, lzb;
-    int cur_job = -1;
-    auto process = [&](const int tile, T (&pf)[M], double &plx, double &plz, R *sx) {
-        int job, c, a0;
-        decode(tile, job, c, a0);
-        const FieldJob &jb = js.j[job];
-        // the v systems leave out the first wall row (kept at zero below)
-        const int kind = jb.kind, sys0 = skip_first_row(kind), n = jb.rows - sys0;
-        const bool live = !((skipmask >> job) & 1) && !lane_skipped(c, a0);   // block-uniform
-        // the previous tile's staging buffer is no longer read (the
-        // coefficient rows below are free once its solve, which ends with a
-        // barrier, is done)
-        if constexpr (!DB) __syncthreads();
-        if (live && job != cur_job) {
-            // rows of the job's operator without the pencil shift:
-            // Poisson (lo, di, up); Helmholtz (-c lo, 1 - c di, -c up)
-            const R cj = (R)jb.c;
-            for (int j = tid; j < NR; j += NT) {
-                const bool real = j < n;
-                const R lo = real ? (R)tp.lo[kind][j + sys0] : R(0);
-                const R di = real ? (R)tp.di[kind][j + sys0] : R(0);
-                const R up = real ? (R)tp.up[kind][j + sys0] : R(0);
-                slo[lr(j)] = pois ? lo : -cj * lo;
-                sdi[lr(j)] = pois ? di : R(1) - cj * di;
-                sup[lr(j)] = pois ? up : -cj * up;
-                sw[lr(j)] = (real && pois) ? (R)tp.wy[j] : R(0);
-            }
-            cur_job = job;
-        }
-        const bool walls = kind == KIND_F;
-#pragma unroll
-        for (int r = 0; r < M; ++r) {
-            const int j = lrow + P * r;
-            sx[lr(j) * LDR + lcol] = (walls && j == n - 1) ? R(0) : (R)pf[r];
-        }
-        if constexpr (BMX) {
-            if (live) {   // block-uniform
-                if (job != tjob) {
-                    if (tjob >= 0) atomicMax(&bmx_sm[tjob], __float_as_uint(tmax));
-                    tjob = job;
-                    tmax = 0.f;
-                }
-#pragma unroll
-                for (int r = 0; r < M; ++r) {
-                    const int j = lrow + P * r;
-                    if (!(walls && j == n - 1)) tmax = fmaxf(tmax, fabsf((float)pf[r]));
-                }
-            }
-        }
-        const R sh = (R)(plx + plz);
-        if (live && tp.xsum && pois && a0 == 0 && c == 0) {
-            // refinement passes: the residual's partial sums of Delta_j x,
-            // summed by the whole block for the pinned pencil (fixed order:
-            // strided per thread, a butterfly per wave, the waves in order)
-            const double *xsp = tp.xsum + (size_t)job * XSUM_SLOTS;
-            double part = 0.0;
-            for (int q = tid; q < tp.nxsum; q += NT) part += xsp[q];
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
-            if ((tid & 63) == 0) xs_sm[tid >> 6] = part;
-        }
-        __syncthreads();
-        fetch(tile + 2 * (int)gridDim.x, pf, plx, plz);  // this buffer's next tile
-        if (live) {
-            const int a = a0 + p;
-            const R sadd = pois ? sh : -(R)jb.c * sh;   // pencil shift of the diagonal
-            const bool pinned = pois && a == 0 && c == 0;
-
-            R r[M];
-#pragma unroll
-            for (int t = 0; t < M; ++t) r[t] = sx[(k * MS + t) * LDR + p];
-
-            R removed = 0.0;
-            if (pinned) {
-                // compatibility: remove the volume-weighted mean of this pencil's rhs
-                R swr = 0.0, sww = 0.0;
-#pragma unroll
-                for (int t = 0; t < M; ++t) {
-                    swr += sw[k * MS + t] * r[t];
-                    sww += sw[k * MS + t];
-                }
-#pragma unroll
-                for (int d = 1; d < P; d <<= 1) {
-                    swr += __shfl_xor(swr, d, P);
-                    sww += __shfl_xor(sww, d, P);
-                }
-                const R mean = swr / sww;
-                removed = mean;
-#pragma unroll
-                for (int t = 0; t < M; ++t)
-                    if (s + t < n) r[t] -= mean;
-                if (k == 0) r[0] = 0.0;  // pin the first point
-            }
-
-            auto coef = [&](int j, R &A, R &B, R &C) {
-                const bool real = j < n && !(pinned && j == 0);
-                A = real ? slo[lr(j)] : 0.0;
-                B = real ? sdi[lr(j)] + sadd : 1.0;
-                C = real ? sup[lr(j)] : 0.0;
-            };
-
-            // down-sweep: rows s+1 .. s+M-1 in the form al x_s + x_j + ga x_{j+1} = rho
-            R al[M], ga[M];
-            {
-                R A, B, C;
-                coef(s + 1, A, B, C);
-                R inv = rcpr(B);
-                al[1] = A * inv; ga[1] = C * inv; r[1] = r[1] * inv;
-#pragma unroll
-                for (int t = 2; t < M; ++t) {
-                    coef(s + t, A, B, C);
-                    inv = rcpr(B - A * ga[t - 1]);
-                    al[t] = -A * al[t - 1] * inv;
-                    ga[t] = C * inv;
-                    r[t] = (r[t] - A * r[t - 1]) * inv;
-                }
-            }
-            // interior rows in terms of the chunk ends, x_j = bp + bq x_s + br x_e,
-            // by back-substitution (no divisions), then the top row
-            //   lam x_{s-1} + x_s + mu x_e = sig
-            R lam_u, mu_u, sig_u;
-            {
-                R bp = r[M - 2], bq = -al[M - 2], br = -ga[M - 2];
-#pragma unroll
-                for (int t = M - 3; t >= 1; --t) {
-                    bp = r[t] - ga[t] * bp;
-                    bq = -al[t] - ga[t] * bq;
-                    br = -ga[t] * br;
-                }
-                R A, B, C;
-                coef(s, A, B, C);
-                const R inv = rcpr(B + C * bq);
-                lam_u = A * inv;
-                mu_u = C * br * inv;
-                sig_u = (r[0] - C * bp) * inv;
-            }
-
-            // reduced system in z_k = x_{last row of chunk k}
-            R lam1, mu1, sig1;
-            if constexpr (CYC) {
-                const int kn = (k + 1) % P;   // chunk 0 follows chunk P-1
-                lam1 = __shfl(lam_u, kn, P);
-                mu1 = __shfl(mu_u, kn, P);
-                sig1 = __shfl(sig_u, kn, P);
-            } else {
-                lam1 = __shfl_down(lam_u, 1, P);
-                mu1 = __shfl_down(mu_u, 1, P);
-                sig1 = __shfl_down(sig_u, 1, P);
-                if (k == P - 1) { lam1 = 0.0; mu1 = 0.0; sig1 = 0.0; }
-            }
-            const R ae = al[M - 1], ge = ga[M - 1], re = r[M - 1];
-            R EA = -ae * lam_u;
-            R EB = 1.0 - ae * mu_u - ge * lam1;
-            R EC = -ge * mu1;
-            R ED = re - ae * sig_u - ge * sig1;
-#pragma unroll
-            for (int d = 1; d < P; d <<= 1) {
-                // each lane scales its row to a unit diagonal (one division)
-                // and the neighbours at distance d eliminate with it: three
-                // values cross lanes each way instead of four
-                const R ib = rcpr(EB);
-                const R ua = EA * ib, uc = EC * ib, ud = ED * ib;
-                R am, cm, dm, ap, cp, dp;
-                if constexpr (CYC) {
-                    const int km = (k - d + P) % P, kp = (k + d) % P;
-                    am = __shfl(ua, km, P); cm = __shfl(uc, km, P); dm = __shfl(ud, km, P);
-                    ap = __shfl(ua, kp, P); cp = __shfl(uc, kp, P); dp = __shfl(ud, kp, P);
-                } else {
-                    am = __shfl_up(ua, d, P); cm = __shfl_up(uc, d, P); dm = __shfl_up(ud, d, P);
-                    ap = __shfl_down(ua, d, P); cp = __shfl_down(uc, d, P); dp = __shfl_down(ud, d, P);
-                    if (k < d) { am = 0.0; cm = 0.0; dm = 0.0; }
-                    if (k + d >= P) { ap = 0.0; cp = 0.0; dp = 0.0; }
-                }
-                const R nA = -EA * am, nC = -EC * cp;
-                const R nB = EB - EA * cm - EC * ap;
-                const R nD = ED - EA * dm - EC * dp;
-                EA = nA; EB = nB; EC = nC; ED = nD;
-            }
-            R z, zm;
-            if constexpr (CYC) {
-                z = ED * rcpr(EA + EB + EC);
-                zm = __shfl(z, (k - 1 + P) % P, P);
-            } else {
-                z = ED * rcpr(EB);
-                zm = __shfl_up(z, 1, P);
-                if (k == 0) zm = 0.0;
-            }
-            const R xs = sig_u - lam_u * zm - mu_u * z;
-
-            // interior back-substitution, in place: r[t] becomes x[t]
-            r[M - 1] = z;
-#pragma unroll
-            for (int t = M - 2; t >= 1; --t) r[t] = r[t] - al[t] * xs - ga[t] * r[t + 1];
-            r[0] = xs;
-
-            if (pinned) {
-                // null mode: zero volume-weighted mean
-                R swx = 0.0, sww = 0.0;
-#pragma unroll
-                for (int t = 0; t < M; ++t) {
-                    swx += sw[k * MS + t] * r[t];
-                    sww += sw[k * MS + t];
-                }
-#pragma unroll
-                for (int d = 1; d < P; d <<= 1) {
-                    swx += __shfl_xor(swx, d, P);
-                    sww += __shfl_xor(sww, d, P);
-                }
-                R mx = swx / sww;
-                if (tp.xsum) {
-                    // refinement: steer the correction so that x + d has zero
-                    // weighted mean (in this pencil's normalisation)
-                    double part = 0.0;
-#pragma unroll
-                    for (int w = 0; w < NT / 64; ++w) part += xs_sm[w];
-                    const double sgj = tp.scale ? tp.scale[job] : 1.0;
-                    mx += sgj * part * tp.inv_sqrt_nxnz / tp.wsum_y;
-                }
-#pragma unroll
-                for (int t = 0; t < M; ++t)
-                    if (s + t < n) r[t] -= mx;
-            }
-#pragma unroll
-            for (int t = 0; t < M; ++t) sx[(k * MS + t) * LDR + p] = r[t];
-
-            if (pinned && k == 0 && tp.record_mean) tp.bmean[job] = removed * tp.inv_sqrt_nxnz;
-            if (a0 == 0 && c == 0 && tid == 0 && jb.info) {
-                ibs_solve_info *inf = static_cast<ibs_solve_info *>(jb.info);
-                const double rm = removed * tp.inv_sqrt_nxnz;
-                inf->iters = 1;
-                inf->status = IBS_OK;
-                inf->rel_residual = 0.0;
-                inf->rel_correction = 0.0;
-                inf->removed_mean = pois ? rm : 0.0;
-            }
-        }  // live
-        __syncthreads();
-        const auto rs = plane_rsrc(job, c, live);
-        const uint32_t voff = (uint32_t)(a0 + lcol) * sizeof(T) + (lrow + sys0) * row_bytes;
-#pragma unroll
-        for (int r2 = 0; r2 < M; ++r2)
-            buf_store<T>((T)sx[lr(lrow + P * r2) * LDR + lcol], rs, voff + r2 * P * row_bytes, 0);
-        // the left-out wall row holds zeros (an offset past the range drops
-        // the store of every other lane)
-        buf_store<T>(T(0), rs, (sys0 && lrow == 0) ? (uint32_t)(a0 + lcol) * sizeof(T) : 0xFFFFFFF0u, 0);
-    };
-    // A block takes tiles in adjacent pairs (2b, 2b+1: neighbouring x-modes
-    // of one z-plane), so the two halves of each 128-byte line of a 4-byte
-    // field are read by the same block, back to back, through one L2.
-    const int G = gridDim.x;
-    fetch(2 * blockIdx.x, pfa, lxa, lza);
-    fetch(2 * blockIdx.x + 1, pfb, lxb, lzb);
-    for (int tile = 2 * blockIdx.x; tile < ntiles; tile += 2 * G) {
-        process(tile, pfa, lxa, lza, sx);
-        if (tile + 1 < ntiles) process(tile + 1, pfb, lxb, lzb, DB ? sx + NRS * LDR : sx);
+    if (act) { ex[0][k][p] = lam_u; ex[1][k][p] = mu_u; ex[2][k][p] = sig_u; }
+    __syncthreads();
+    if (act) {
+        // reduced system in z_k = x_{last row of chunk k}
+        R lam1 = 0.0, mu1 = 0.0, sig1 = 0.0;
+        const int kn = k + 1 < P ? k + 1 : 0;   // cyclic: chunk 0 follows chunk P-1
+        if (CYC || k + 1 < P) { lam1 = ex[0][kn][p]; mu1 = ex[1][kn][p]; sig1 = ex[2][kn][p]; }
+        const R ae = al[M - 1], ge = ga[M - 1], re = r[M - 1];
+        eq[0][k][p] = -ae * lam_u;
+        eq[1][k][p] = R(1) - ae * mu_u - ge * lam1;
+        eq[2][k][p] = -ge * mu1;
+        eq[3][k][p] = re - ae * sig_u - ge * sig1;
     }
-    if constexpr (BMX) {
-        // block maxima per job, written to slot blockIdx.x of this launch's
-        // half (the FP64 lane's launch: the second); the block also zeroes
-        // its other slots of the half (blockIdx.x + k G), and a launch of
-        // the first half the same slots of the second, which the lane's
-        // launch, if any, then fills
-        if (tjob >= 0) atomicMax(&bmx_sm[tjob], __float_as_uint(tmax));
-        __syncthreads();
-        constexpr int HALF = BMAX_SLOTS / 2;
-        const int base = tp.lane_mode == 2 ? HALF : 0;
-        for (int q = 0; q < js.n; ++q) {
-            const double m = (double)__uint_as_float(bmx_sm[q]);
-            double *dst = tp.bmax + (size_t)q * BMAX_SLOTS;
-            for (int sl = (int)blockIdx.x + G * tid; sl < HALF; sl += G * NT) {
-                dst[base + sl] = sl == (int)blockIdx.x ? m : 0.0;
-                if (tp.lane_mode != 2) dst[HALF + sl] = 0.0;
+    __syncthreads();
+    if (tid < 2 * TA) {
+        // two lanes per pencil: side 0 eliminates downwards from chunk 0, side
+        // 1 upwards from the last; in: the coefficient towards the side's own
+        // end, out: towards the middle.  z_i + cp_i z_{i+1} = dp_i (+ qp_i w)
+        const int side = tid / TA, q = tid % TA;
+        constexpr int LEN = CYC ? P - 1 : P;          // cyclic: cut at w = z_{P-1}
+        constexpr int H0 = (LEN + 1) / 2, H1 = LEN / 2;
+        const int cnt = side ? H1 : H0;
+        auto at = [&](int i) { return side ? LEN - 1 - i : i; };
+        R cp = 0.0, dp = 0.0, qp = 1.0;               // "z_{-1} = w"
+#pragma unroll 2
+        for (int i = 0; i < H0; ++i) {
+            if (H0 != H1 && i >= cnt) break;
+            const int e = at(i);
+            const R in = eq[side ? 2 : 0][e][q], out = eq[side ? 0 : 2][e][q];
+            const R inv = rcpr(eq[1][e][q] - in * cp);
+            cp = out * inv;
+            dp = (eq[3][e][q] - in * dp) * inv;
+            eq[side ? 0 : 2][e][q] = cp;
+            eq[3][e][q] = dp;
+            if constexpr (CYC) {
+                qp = -in * qp * inv;
+                ex[1][e][q] = qp;
             }
+        }
+        if (P == 2 && CYC && side) { cp = 0.0; dp = 0.0; qp = 0.0; }
+        const R cpo = __shfl_xor(cp, TA, 64), dpo = __shfl_xor(dp, TA, 64), qpo = __shfl_xor(qp, TA, 64);
+        const R det = rcpr(R(1) - cp * cpo);
+        R z = (dp - cp * dpo) * det, g = CYC ? (qp - cp * qpo) * det : R(0);
+        if (cnt > 0) {
+            ex[0][at(cnt - 1)][q] = z;
+            if (CYC) ex[1][at(cnt - 1)][q] = g;
+        }
+#pragma unroll 4
+        for (int ii = 0; ii < H0 - 1; ++ii) {
+            const int i = cnt - 2 - ii;
+            if (i < 0) break;
+            const int e = at(i);
+            const R ci = eq[side ? 0 : 2][e][q];
+            z = eq[3][e][q] - ci * z;
+            ex[0][e][q] = z;
+            if constexpr (CYC) {
+                g = ex[1][e][q] - ci * g;
+                ex[1][e][q] = g;
+            }
+        }
+        if constexpr (CYC) {
+            // z, g now stand for the chunk next to the cut on this side (0 or
+            // P-2); the last equation gives w
+            const R zo = __shfl_xor(z, TA, 64), go = __shfl_xor(g, TA, 64);
+            const R EA = eq[0][P - 1][q], EB = eq[1][P - 1][q], EC = eq[2][P - 1][q], ED = eq[3][P - 1][q];
+            const R z0 = side ? zo : z, zl = side ? z : zo, g0 = side ? go : g, gl = side ? g : go;
+            const R w = (ED - EA * zl - EC * z0) * rcpr(EB + EA * gl + EC * g0);
+            for (int i = 0; i < cnt; ++i) {
+                const int e = at(i);
+                ex[0][e][q] += ex[1][e][q] * w;
+            }
+            if (side == 0) ex[0][P - 1][q] = w;
+        }
+    }
+    __syncthreads();
+    if (act) {
+        const R z = ex[0][k][p];
+        const R zm = k > 0 ? ex[0][k - 1][p] : (CYC ? ex[0][P - 1][p] : R(0));
+        const R xs = sig_u - lam_u * zm - mu_u * z;
+        // interior back-substitution, in place: r[t] becomes x[t]
+        r[M - 1] = z;
+#pragma unroll
+        for (int t = M - 2; t >= 1; --t) r[t] = r[t] - al[t] * xs - ga[t] * r[t + 1];
+        r[0] = xs;
+    }
+    double removed = 0.0;
+    if (pt) {
+        double xpart = 0.0;
+        if (tp.xsum)
+            for (int w = 0; w < NW; ++w) xpart += xs_sm[w];
+        const double steer = (tp.scale ? tp.scale[job] : 1.0) * xpart * tp.inv_sqrt_nxnz / tp.wsum_y;
+        if (tid < 64) removed = singular_pencil<P * M, CYC>(pin_sm, n, wt_sm, dl_sm, steer);
+        __syncthreads();
+        if (pinned && act)
+#pragma unroll
+            for (int t = 0; t < M; ++t) r[t] = (R)pin_sm[s + t];
+    }
+    if (act) {
+#pragma unroll
+        for (int t = 0; t < M; ++t)
+            if (s + t < n) x[(size_t)(s + t) * nx] = (T)r[t];
+        if (sys0 && k == 0) *(x - nx) = T(0);   // the left-out wall row holds zeros
+    }
+    if (tid == 0 && a0 == 0 && c == 0) {
+        const double rm = removed * tp.inv_sqrt_nxnz;
+        if (pois && tp.record_mean) tp.bmean[job] = rm;
+        if (jb.info) {
+            ibs_solve_info *inf = static_cast<ibs_solve_info *>(jb.info);
+            inf->iters = 1;
+            inf->status = IBS_OK;
+            inf->rel_residual = 0.0;
+            inf->rel_correction = 0.0;
+            inf->removed_mean = pois ? rm : 0.0;
         }
     }
 }
@@ -517,34 +440,13 @@ __global__ __launch_bounds__(TA * P, (sizeof(R) == 4 && (M <= 9 || (!CYC && M <=
 template <typename T, typename R, int P, int M, bool CYC, bool BMX>
 static hipError_t launch_pm_k(const JobSet &js, const TriParams &tp, hipStream_t s)
 {
-    // pencils per tile: 16; 8 for FP32 data with FP64 arithmetic, whose
-    // registers allow fewer waves per SIMD (blocks of 4 waves then still
-    // fill them; with FP64 data the 16-wide tiles measured as fast with
-    // less traffic); 32 for FP32 arithmetic over 32 lanes of up to 9 rows
-    // (a tile row is one whole 128-byte line; 16-wave blocks, 5 % faster)
-    constexpr int TA = sizeof(R) == 8 && sizeof(T) == 4 && P == 32 ? 8
-                       : (sizeof(R) == 4 && P == 32 && M <= 9) ? 32 : 16;
-    // persistent blocks walk the tiles (job, z-mode, TA x-modes) in order;
-    // as many blocks as are resident at once, so that every block's tiles
-    // run back to back
-    static const int resident = [] {
-        int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tridiag_kernel<T, R, P, M, TA, CYC, BMX>, TA * P, 0) !=
-                hipSuccess ||
-            hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            return 1024;
-        return per_cu * cus > 0 ? per_cu * cus : 1024;
-    }();
-    static_assert(32 % TA == 0, "FP64-lane tiles are 32 pencils wide");
-    const int ntx = tp.nx / TA;
-    const int ntiles = tp.lane_mode == 2 ? js.n * tp.lane_len * (32 / TA) : ntx * tp.nz * js.n;
-    if (ntiles == 0) return hipSuccess;
-    const int pairs = (ntiles + 1) / 2;
-    int grid = pairs < resident ? pairs : resident;
-    if (BMX && grid > BMAX_SLOTS / 2) grid = BMAX_SLOTS / 2;   // one slot per block
-    hipLaunchKernelGGL((tridiag_kernel<T, R, P, M, TA, CYC, BMX>), dim3(grid), dim3(TA * P), 0, s, js, tp, ntx,
-                       ntiles);
+    // pencils per tile: one 128-byte line of a row of FP64 data, or of FP32
+    // data in FP32 arithmetic; FP32 data in FP64 arithmetic (the few tiles of
+    // the FP64 lane) take 16, so that their registers hold two blocks per CU
+    constexpr int TA = sizeof(R) == 8 ? 16 : 32;
+    const int tiles = tp.lane_mode == 2 ? tp.lane_len * (32 / TA) : tp.nx / TA * tp.nz;
+    if (tiles == 0) return hipSuccess;
+    tridiag_kernel<T, R, P, M, TA, CYC, BMX><<<dim3(tiles, js.n), dim3((TA * P + 63) / 64 * 64), 0, s>>>(js, tp);
     return hipGetLastError();
 }
 
