@@ -393,14 +393,15 @@ ibs_status ibs_batch_build_sched(const ibs_batch_job *jobs, int32_t njobs, int32
  * those of any schedule.  Errors as ibs_batch_build(), IBS_ERR_HIP. */
 ibs_status ibs_batch_autotune(const ibs_batch_job *jobs, int32_t njobs, int32_t reps, int32_t *nlanes,
                               int32_t *policy, float *ms, void *stream);
-/* Multi-grid batch (the many-grid configuration through persistent
- * work-queue kernels): every field of every job is listed in one device job
- * table, and each stage of the separable solve (x transform, z transform,
- * y tridiagonal, inverse z, inverse x; Section 2.3.3, items S2.1-S2.2) is
- * ONE persistent launch whose waves walk a device work list of tiles drawn
- * from all grids, so a batch of G grids of any sizes replays as 5 kernel
- * launches in one graph.  FP64 arithmetic throughout (plain FP64
- * matrix-core transforms against each grid's eigenbases, Thomas pencils):
+/* Multi-grid batch (the many-grid configuration: launches over fields of
+ * many grids): the stages of the separable solve (x transform, z transform,
+ * y tridiagonal, inverse z, inverse x; Section 2.3.3, items S2.1-S2.2) run
+ * over device tables of fields.  Fields of equal grids with fast transforms
+ * are chained through the single-grid kernels, five launches per up to 128 MB
+ * of fields; the rest (stretched axes, the face-normal component along a
+ * walled axis, few or short fields) share ONE persistent launch per stage,
+ * whose waves walk a device work list of tiles drawn from all grids (plain
+ * FP64 matrix-core transforms, Thomas pencils).  FP64 arithmetic throughout:
  * results agree with solve_poisson / solve_helmholtz_batch to rounding, not
  * bitwise.  Jobs: plans uploaded, precision IBS_FP64, walls in y (not
  * periodic y), strict_compat 0, any x / z conditions (uniform or
@@ -408,10 +409,10 @@ ibs_status ibs_batch_autotune(const ibs_batch_job *jobs, int32_t njobs, int32_t 
  * one of its own per job (jobs run side by side); rhs, x and work 32-byte
  * aligned, as for the single solves; rhs may alias x.  info
  * reports as the FP64 solves do.  The builder allocates one device buffer
- * (job table, work lists, transform tables, and the tridiagonal pencils'
- * forward factors, which depend on the systems only: one field's size per
- * field, about as much device memory again as the fields themselves; freed
- * by ibs_batch_destroy()) and computes those factors once on the device
+ * (tables, work lists, transform matrices, and the tridiagonal pencils'
+ * forward factors of the fields in the shared launches, which depend on the
+ * systems only: one field's size per such field; freed by
+ * ibs_batch_destroy()) and computes those factors once on the device
  * before capturing the graph (synchronously).  Errors: IBS_ERR_INVALID_ARG (bad job, shared
  * workspace), IBS_ERR_UNSUPPORTED (refined or periodic-y plan, strict
  * compatibility), IBS_ERR_NOT_UPLOADED, IBS_ERR_WORKSPACE_TOO_SMALL,

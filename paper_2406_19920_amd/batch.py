@@ -5,8 +5,9 @@ Helmholtz components (one batched call) and one pressure Poisson solve.
 The library records all jobs into one graph (ibs_batch_build) whose
 independent branches let small grids overlap on the device; a replay is one
 hipGraphLaunch.  mode="multigrid" (FP64 plans) builds the batch with
-ibs_batch_build_multigrid instead: each solve stage is one persistent
-launch over every grid, five launches per replay whatever the job count.  Buffers are torch allocations that live as long as the
+ibs_batch_build_multigrid instead: each solve stage is one launch over the
+fields of all equal grids (or of all grids), a few launches per replay whatever
+the job count.  Buffers are torch allocations that live as long as the
 batch.
 """
 from __future__ import annotations
@@ -82,7 +83,7 @@ class Batch:
     library's schedule autotuner, timed on the device at set-up (the jobs
     run during tuning); self.schedule records (nlanes, policy, ms).
     mode: "graph" (per-grid launch sequences on graph lanes), "multigrid"
-    (FP64: one persistent launch per stage over all grids) or "auto" (FP64:
+    (FP64: stage launches over many fields) or "auto" (FP64:
     both timed at set-up, the faster kept; self.mode names it and
     self.timings holds both ms per replay)."""
 

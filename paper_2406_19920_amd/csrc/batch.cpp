@@ -196,11 +196,21 @@ ibs_status ibs_batch_destroy(ibs_batch batch)
     return IBS_OK;
 }
 
-// Multi-grid batch: the fields of every job in one device job table, one
-// work list per stage kind (x transforms: 64 x 64 tiles of rows x modes; z
-// transforms: 64 x 64 tiles of modes x columns; pencils: 64-pencil runs of
-// a plane), the plain transform tables of every (plan, axis, kind,
-// direction) used, and a graph of the five stage launches.
+// Multi-grid batch.  Fields with fast transforms in x and z are grouped by
+// grid size and boundary conditions; a group is one chain of five launches
+// (x, z, pencils, inverse z, inverse x, in place on the solutions) over a
+// device table of its fields, cut so that a chain's fields (MG_CHAIN_BYTES)
+// stay in the 256 MB Infinity Cache from stage to stage.  The rest (other
+// transforms; groups of less than MG_GROUP_BYTES, whose chain would be mostly
+// launch time; systems of up to MG_THOMAS_ROWS rows, which pad the pencils'
+// chunks) goes through the persistent stage kernels: one device job table,
+// one work list per stage kind (x transforms: tiles of rows x modes; z
+// transforms: tiles of modes x columns; pencils: 64-pencil runs of a plane),
+// the plain transform tables of every (plan, axis, kind, direction) used.
+constexpr size_t MG_CHAIN_BYTES = size_t(128) << 20;
+constexpr size_t MG_GROUP_BYTES = size_t(8) << 20;
+constexpr int MG_THOMAS_ROWS = 16;
+
 ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, ibs_batch *out)
 {
     if (!jobs || njobs < 1 || !out) {
@@ -263,16 +273,78 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
     };
     struct Pending { MgField f; size_t xf, xi, zf, zi; };
     std::vector<Pending> fields;
+    // fast fields by grid: nx, ny, nz, walls in x, z
+    struct Fast { const Plan *p; FieldJob job; bool poisson; };
+    typedef std::tuple<int, int, int, bool, bool> Key;
+    std::map<Key, std::vector<Fast>> groups;
+    std::map<Key, size_t> group_bytes;
+    auto key_of = [](const Plan &p) { return Key(p.nx, p.ny, p.nz, p.wx, p.wz); };
+    auto fast_field = [](const Plan &p, int xk, int zk) { return p.fx[xk] && p.fz[zk] && p.ny > MG_THOMAS_ROWS; };
+    auto kinds_of = [&](const ibs_batch_job &j, int k, int &kind, int &xk, int &zk) {
+        const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
+        const bool pois = j.op == IBS_OP_POISSON;
+        kind = pois ? KIND_P : comp_kind(p, j.comp[k]);
+        xk = pois ? XK_P : comp_xkind(p, j.comp[k]);
+        zk = pois ? XK_P : comp_zkind(p, j.comp[k]);
+    };
+    // The stage kernels read every right-hand side before any solution is
+    // written; chains do not.  A batch in which one field's solution overlaps
+    // another's right-hand side therefore takes the stage kernels alone.
+    bool chains_ok = true;
+    {
+        struct Range { uintptr_t at, end; size_t field; };
+        std::vector<Range> xs, rs;
+        for (int q = 0; q < njobs; ++q) {
+            const ibs_batch_job &j = jobs[q];
+            const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
+            for (int k = 0; k < (j.op == IBS_OP_POISSON ? 1 : j.ncomp); ++k) {
+                int kind, xk, zk;
+                kinds_of(j, k, kind, xk, zk);
+                const size_t n = (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double), f = xs.size();
+                xs.push_back({reinterpret_cast<uintptr_t>(j.x[k]), reinterpret_cast<uintptr_t>(j.x[k]) + n, f});
+                rs.push_back({reinterpret_cast<uintptr_t>(j.rhs[k]), reinterpret_cast<uintptr_t>(j.rhs[k]) + n, f});
+            }
+        }
+        std::sort(xs.begin(), xs.end(), [](const Range &a, const Range &c) { return a.at < c.at; });
+        for (size_t i = 1; i < xs.size(); ++i) chains_ok = chains_ok && xs[i].at >= xs[i - 1].end;
+        for (const Range &r : rs) {
+            if (!chains_ok) break;
+            // solutions are disjoint and in order: the first one ending beyond r.at
+            auto it = std::upper_bound(xs.begin(), xs.end(), r.at, [](uintptr_t a, const Range &x) { return a < x.end; });
+            for (; chains_ok && it != xs.end() && it->at < r.end; ++it)
+                if (it->field != r.field) chains_ok = false;
+        }
+    }
+    for (int q = 0; q < njobs && chains_ok; ++q) {
+        const ibs_batch_job &j = jobs[q];
+        const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
+        for (int k = 0; k < (j.op == IBS_OP_POISSON ? 1 : j.ncomp); ++k) {
+            int kind, xk, zk;
+            kinds_of(j, k, kind, xk, zk);
+            if (fast_field(p, xk, zk)) group_bytes[key_of(p)] += (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double);
+        }
+    }
     for (int q = 0; q < njobs; ++q) {
         const ibs_batch_job &j = jobs[q];
         const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
         const bool pois = j.op == IBS_OP_POISSON;
         const int nc = pois ? 1 : j.ncomp;
         for (int k = 0; k < nc; ++k) {
-            const int comp = pois ? -1 : j.comp[k];
-            const int kind = pois ? KIND_P : comp_kind(p, comp);
-            const int xk = pois ? XK_P : comp_xkind(p, comp);
-            const int zk = pois ? XK_P : comp_zkind(p, comp);
+            int kind, xk, zk;
+            kinds_of(j, k, kind, xk, zk);
+            if (fast_field(p, xk, zk) && group_bytes[key_of(p)] >= MG_GROUP_BYTES) {
+                Fast f{&p, FieldJob{}, pois};
+                f.job.in = j.rhs[k];
+                f.job.out = j.x[k];
+                f.job.rows = p.rows[kind];
+                f.job.kind = kind;
+                f.job.xk = xk;
+                f.job.zk = zk;
+                f.job.c = pois ? 0.0 : j.c[k];
+                f.job.info = j.info ? j.info + k : nullptr;
+                groups[key_of(p)].push_back(f);
+                continue;
+            }
             Pending e{};
             MgField &f = e.f;
             f.in = j.rhs[k];
@@ -316,13 +388,42 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         for (int c = 0; c < f.nz; ++c)
             for (int a = 0; a < f.nx; a += 64) titems.push_back(make_int4((int)fi, c, a, 0));
     }
+    // the groups' tables: per field the four transforms and the pencils
+    const size_t fe = fft_entry_bytes(), te = tri_entry_bytes();
+    std::vector<unsigned char> fast_img;
+    struct Chain { int nx, ny, nz, n; bool wx, wz; size_t at[5]; };   // x, z forward, z, x inverse, pencils
+    std::vector<Chain> chains;
+    for (const auto &g : groups) {
+        const std::vector<Fast> &all = g.second;
+        const Plan &p0 = *all[0].p;
+        const size_t per = std::max<size_t>(1, MG_CHAIN_BYTES / ((size_t)p0.nz * (p0.ny + 1) * p0.nx * sizeof(double)));
+        for (size_t first = 0; first < all.size(); first += per) {
+            const size_t n = std::min(per, all.size() - first);
+            Chain c{p0.nx, p0.ny, p0.nz, (int)n, p0.wx, p0.wz, {}};
+            for (int stage = 0; stage < 5; ++stage) {
+                c.at[stage] = (fast_img.size() + 255) & ~size_t(255);
+                const size_t sz = stage < 4 ? fe : te;
+                fast_img.resize(c.at[stage] + n * sz);
+                for (size_t q = 0; q < n; ++q) {
+                    const Fast &f = all[first + q];
+                    FieldJob job = f.job;
+                    if (stage != 0) job.in = job.out;   // in place after the first stage
+                    void *to = fast_img.data() + c.at[stage] + q * sz;
+                    if (stage < 4) fft_entry_fill(to, *f.p, job, stage == 1 || stage == 2, stage >= 2);
+                    else tri_entry_fill(to, *f.p, job, f.poisson);
+                }
+            }
+            chains.push_back(c);
+        }
+    }
     auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
     const size_t o_tab = 0;
     const size_t o_fld = al(o_tab + tables.size() * sizeof(double));
     const size_t o_x = al(o_fld + fields.size() * sizeof(MgField));
     const size_t o_z = al(o_x + xitems.size() * sizeof(int4));
     const size_t o_t = al(o_z + zitems.size() * sizeof(int4));
-    const size_t o_cp = al(o_t + titems.size() * sizeof(int4));
+    const size_t o_fast = al(o_t + titems.size() * sizeof(int4));
+    const size_t o_cp = al(o_fast + fast_img.size());
     const size_t total = al(o_cp + cpt_doubles * sizeof(double));
     const size_t upload = o_cp;   // the factor region is filled on the device
 
@@ -331,10 +432,12 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
     hipError_t e;
     ibs_status st = IBS_OK;
     std::vector<unsigned char> img(upload, 0);
+    auto copy_in = [&](size_t at, const void *src, size_t n) { if (n) std::memcpy(img.data() + at, src, n); };
     unsigned char *dev = nullptr;
     if ((e = hipMalloc(&b->dev, total)) != hipSuccess) { st = fail_hip(e, "multi-grid buffer"); goto fail; }
     dev = static_cast<unsigned char *>(b->dev);
-    std::memcpy(img.data() + o_tab, tables.data(), tables.size() * sizeof(double));
+    copy_in(o_tab, tables.data(), tables.size() * sizeof(double));
+    copy_in(o_fast, fast_img.data(), fast_img.size());
     for (size_t fi = 0; fi < fields.size(); ++fi) {
         MgField f = fields[fi].f;
         f.xfwd = reinterpret_cast<const double *>(dev + o_tab) + fields[fi].xf;
@@ -344,9 +447,9 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         f.cpt = reinterpret_cast<double *>(dev + o_cp) + cpt_at[fi];
         std::memcpy(img.data() + o_fld + fi * sizeof(MgField), &f, sizeof(MgField));
     }
-    std::memcpy(img.data() + o_x, xitems.data(), xitems.size() * sizeof(int4));
-    std::memcpy(img.data() + o_z, zitems.data(), zitems.size() * sizeof(int4));
-    std::memcpy(img.data() + o_t, titems.data(), titems.size() * sizeof(int4));
+    copy_in(o_x, xitems.data(), xitems.size() * sizeof(int4));
+    copy_in(o_z, zitems.data(), zitems.size() * sizeof(int4));
+    copy_in(o_t, titems.data(), titems.size() * sizeof(int4));
     if ((e = hipMemcpy(b->dev, img.data(), upload, hipMemcpyHostToDevice)) != hipSuccess) { st = fail_hip(e, "multi-grid upload"); goto fail; }
     if ((e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking)) != hipSuccess) { st = fail_hip(e, "capture stream"); goto fail; }
     // the pencils' factors, once (they depend on the systems, not the data)
@@ -363,7 +466,20 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         const int4 *zi = reinterpret_cast<const int4 *>(dev + o_z);
         const int4 *ti = reinterpret_cast<const int4 *>(dev + o_t);
         const int nx_ = (int)xitems.size(), nz_ = (int)zitems.size(), nt_ = (int)titems.size();
-        hipError_t le = launch_multigrid_stage(MG_X_FWD, fl, xi, nx_, cap);
+        hipError_t le = hipSuccess;
+        for (const Chain &c : chains) {
+            const unsigned char *t = dev + o_fast;
+            auto fft = [&](int stage, bool z_axis, bool inverse) {
+                if (le == hipSuccess)
+                    le = launch_fft_table(t + c.at[stage], c.n, c.nx, c.ny, c.nz, z_axis, inverse, z_axis ? c.wz : c.wx, cap);
+            };
+            fft(0, false, false);
+            fft(1, true, false);
+            if (le == hipSuccess) le = launch_tridiag_table(t + c.at[4], c.n, c.nx, c.ny, c.nz, cap);
+            fft(2, true, true);
+            fft(3, false, true);
+        }
+        if (le == hipSuccess) le = launch_multigrid_stage(MG_X_FWD, fl, xi, nx_, cap);
         if (le == hipSuccess) le = launch_multigrid_stage(MG_Z_FWD, fl, zi, nz_, cap);
         if (le == hipSuccess) le = launch_multigrid_stage(MG_TRI, fl, ti, nt_, cap);
         if (le == hipSuccess) le = launch_multigrid_stage(MG_Z_INV, fl, zi, nz_, cap);

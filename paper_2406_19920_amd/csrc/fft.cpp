@@ -33,6 +33,23 @@ hipError_t launch_fft_f64(const JobSet &js, const Plan &p, bool z_axis, bool inv
                   : launch_fft_x64(f, p.nx, p.ny, p.nz, inverse, p.wx, s);
 }
 
+size_t fft_entry_bytes() { return sizeof(FftJob); }
+
+void fft_entry_fill(void *to, const Plan &p, const FieldJob &job, bool z_axis, bool inverse)
+{
+    FftJob &f = *static_cast<FftJob *>(to);
+    f = fft_job(p, z_axis, inverse, job.rows, job.kind, z_axis ? job.zk : job.xk, 0);
+    f.in = job.in;
+    f.out = job.out;
+}
+
+hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, bool z_axis, bool inverse, bool walls,
+                            hipStream_t s)
+{
+    const FftTable t{static_cast<const FftJob *>(entries), n};
+    return z_axis ? launch_fft_z64(t, nz, ny, nx, inverse, walls, s) : launch_fft_x64(t, nx, ny, nz, inverse, walls, s);
+}
+
 hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
                           int pass, hipStream_t s)
 {

@@ -273,6 +273,11 @@ hipError_t launch_zgemm_f64(const JobSet &js, int M, int K, int nx,
 // poisson: pressure operator (pin + weighted-mean handling of pencil 0,0).
 hipError_t launch_tridiag_f64(const JobSet &js, const Plan &p, const State &st, bool poisson,
                               hipStream_t s);
+// Multi-grid batches: the FP64 pencils of n fields of one grid size, each
+// with its plan's tables, from a table of entries in device memory.
+size_t tri_entry_bytes();
+void tri_entry_fill(void *to, const Plan &p, const FieldJob &job, bool poisson);
+hipError_t launch_tridiag_table(const void *entries, int n, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_divergence(const Plan &p, const double *u, const double *v,
                              const double *w, double *b, double scale, hipStream_t s);
 hipError_t launch_correct(const Plan &p, const double *phi, double *u, double *v,
@@ -363,6 +368,12 @@ hipError_t launch_residual_scale(const SplitSet &ss, const Plan &p, const State 
 // One pass over each job's field, js.j[q].in to .out (which may be the same
 // field); the jobs of one call share the axis's boundary conditions.
 hipError_t launch_fft_f64(const JobSet &js, const Plan &p, bool z_axis, bool inverse, hipStream_t s);
+// The same over a table in device memory (multi-grid batches: n fields of one
+// grid size, walls: of that axis).
+size_t fft_entry_bytes();
+void fft_entry_fill(void *to, const Plan &p, const FieldJob &job, bool z_axis, bool inverse);
+hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, bool z_axis, bool inverse, bool walls,
+                            hipStream_t s);
 // Refined path: in64, mode and pass as launch_split_xgemm().
 hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
                           int pass, hipStream_t s);

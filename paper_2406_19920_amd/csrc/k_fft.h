@@ -55,6 +55,13 @@ struct FftSet {
     int n;
 };
 
+// The jobs of a launch as a table in device memory (any number of fields of
+// one grid size).
+struct FftTable {
+    const FftJob *j;
+    int n;
+};
+
 namespace fft {
 
 static __device__ __forceinline__ double lanes_sum(double v)
@@ -112,8 +119,8 @@ static __device__ __forceinline__ void rows_out(const T *lds, const int *prow, T
 // LDS [k1][n2][column], a pad line per k1 so that the two halves of a wave
 // (k1 apart) use different banks.
 // TS: stored type, T: arithmetic.
-template <typename TS, typename T, int R1, int R2, bool INV, bool WALL>
-__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) void fft_z_kernel(FftSet js, int nx,
+template <typename TS, typename T, int R1, int R2, bool INV, bool WALL, typename Set>
+__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) void fft_z_kernel(Set js, int nx,
                                                                                     const int *skip)
 {
     using namespace fft;
@@ -199,8 +206,8 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) vo
 // result in FP32; 2 x += result / sigma; 4 x = xs + result / sigma; 2 and 4
 // also write the block's sums of (result / sigma)^2 and x^2 to red.  TIN:
 // stored type of the forward input, TS of the spectrum, T: arithmetic.
-template <typename TIN, typename TS, typename T, int R1, int R2, bool INV, bool WALL, int MODE>
-__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_kernel(FftSet js, int nz, double *red, int red_stride,
+template <typename TIN, typename TS, typename T, int R1, int R2, bool INV, bool WALL, int MODE, typename Set>
+__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_kernel(Set js, int nz, double *red, int red_stride,
                                                                                  const int *skip, const double *scale)
 {
     using namespace fft;
@@ -405,6 +412,8 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
 // One launch over the jobs of a set.  walls: their axis has walls (the jobs
 // of one call agree); rows: transform rows per plane.  Sizes of the lists
 // above only (fft_size()).
+hipError_t launch_fft_z64(const FftTable &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s);
+hipError_t launch_fft_x64(const FftTable &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s);
 hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s);
 hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, const int *skip,
                           hipStream_t s);

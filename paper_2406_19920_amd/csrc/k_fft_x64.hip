@@ -3,8 +3,8 @@
 
 namespace ibs {
 
-template <int R1, int R2>
-static void go(const FftSet &js, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+template <int R1, int R2, typename Set>
+static void go(const Set &js, int rows, int nz, bool inverse, bool walls, hipStream_t s)
 {
     const dim3 grid(nz * rows / FFT_RW, js.n), blk(fft::Shape<R1, R2>::threads(FFT_RW));
     if (inverse && walls)
@@ -17,7 +17,8 @@ static void go(const FftSet &js, int rows, int nz, bool inverse, bool walls, hip
         fft_x_kernel<double, double, double, R1, R2, false, false, 0><<<grid, blk, 0, s>>>(js, nz, nullptr, 0, nullptr, nullptr);
 }
 
-hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+template <typename Set>
+static hipError_t by_size(const Set &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s)
 {
     if (js.n == 0) return hipSuccess;
     switch (n) {
@@ -27,6 +28,15 @@ hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool invers
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+{
+    return by_size(js, n, rows, nz, inverse, walls, s);
+}
+hipError_t launch_fft_x64(const FftTable &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s)
+{
+    return by_size(js, n, rows, nz, inverse, walls, s);
 }
 
 }  // namespace ibs

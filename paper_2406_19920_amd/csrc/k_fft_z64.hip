@@ -3,8 +3,8 @@
 
 namespace ibs {
 
-template <int R1, int R2>
-static void go(const FftSet &js, int rows, int nx, bool inverse, bool walls, hipStream_t s)
+template <int R1, int R2, typename Set>
+static void go(const Set &js, int rows, int nx, bool inverse, bool walls, hipStream_t s)
 {
     constexpr int CW = 128 / sizeof(double);
     const dim3 grid(rows * nx / CW, js.n), blk(fft::Shape<R1, R2>::threads(CW));
@@ -14,7 +14,8 @@ static void go(const FftSet &js, int rows, int nx, bool inverse, bool walls, hip
     else fft_z_kernel<double, double, R1, R2, false, false><<<grid, blk, 0, s>>>(js, nx, nullptr);
 }
 
-hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s)
+template <typename Set>
+static hipError_t by_size(const Set &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s)
 {
     if (js.n == 0) return hipSuccess;
     switch (n) {
@@ -24,6 +25,15 @@ hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool invers
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s)
+{
+    return by_size(js, n, rows, nx, inverse, walls, s);
+}
+hipError_t launch_fft_z64(const FftTable &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s)
+{
+    return by_size(js, n, rows, nx, inverse, walls, s);
 }
 
 }  // namespace ibs

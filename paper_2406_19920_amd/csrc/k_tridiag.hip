@@ -6,35 +6,36 @@
 
 namespace ibs {
 
-template <typename T, typename R>
-static hipError_t launch_by_rows(const JobSet &js, const TriParams &tp, int n, hipStream_t s)
+template <typename T, typename R, typename Src>
+static hipError_t launch_by_rows(const Src &src, int n, hipStream_t s)
 {
-    // chunks per pencil and rows per chunk: 16 chunks while the rows of one
-    // fit the registers.  Beyond: FP32 more chunks of 16 rows; FP64 32 chunks,
+    // chunks per pencil and rows per chunk: up to 16 chunks while the rows of
+    // one fit the registers (64 rows: 8 x 8 takes 61 us for 63 fields of 64^3,
+    // 16 x 4 70).  Beyond: FP32 more chunks of 16 rows; FP64 32 chunks,
     // whose 12 or fewer rows leave two 8-wave blocks per CU (384 rows of
     // 512x384x384: 733 us for three fields, 24 chunks of 16 rows 1069).
-    if (n <= 32) return launch_pm<T, R, 8, 4>(js, tp, s);
-    if (n <= 64) return launch_pm<T, R, 16, 4>(js, tp, s);
-    if (n <= 96) return launch_pm<T, R, 16, 6>(js, tp, s);
-    if (n <= 128) return launch_pm<T, R, 16, 8>(js, tp, s);
-    if (n <= 160) return launch_pm<T, R, 16, 10>(js, tp, s);
-    if (n <= 192) return launch_pm<T, R, 16, 12>(js, tp, s);
+    if (n <= 32) return launch_pm<T, R, 8, 4>(src, s);
+    if (n <= 64) return launch_pm<T, R, 8, 8>(src, s);
+    if (n <= 96) return launch_pm<T, R, 16, 6>(src, s);
+    if (n <= 128) return launch_pm<T, R, 16, 8>(src, s);
+    if (n <= 160) return launch_pm<T, R, 16, 10>(src, s);
+    if (n <= 192) return launch_pm<T, R, 16, 12>(src, s);
     if constexpr (sizeof(R) == 4) {
         // at most one tile per CU: nothing else hides a tile's own latency,
         // so shorter chunks
-        if (n <= 256 && tp.nx / 32 * tp.nz * js.n <= 256) return launch_pm<T, R, 32, 8>(js, tp, s);
-        if (n <= 256) return launch_pm<T, R, 16, 16>(js, tp, s);
-        if (n <= 320) return launch_pm<T, R, 20, 16>(js, tp, s);
-        if (n <= 384) return launch_pm<T, R, 24, 16>(js, tp, s);
-        if (n <= 512) return launch_pm<T, R, 32, 16>(js, tp, s);
-        if (n <= 768) return launch_pm<T, R, 32, 24>(js, tp, s);
+        if (n <= 256 && src.width() <= 256) return launch_pm<T, R, 32, 8>(src, s);
+        if (n <= 256) return launch_pm<T, R, 16, 16>(src, s);
+        if (n <= 320) return launch_pm<T, R, 20, 16>(src, s);
+        if (n <= 384) return launch_pm<T, R, 24, 16>(src, s);
+        if (n <= 512) return launch_pm<T, R, 32, 16>(src, s);
+        if (n <= 768) return launch_pm<T, R, 32, 24>(src, s);
     } else {
-        if (n <= 224) return launch_pm<T, R, 16, 14>(js, tp, s);
-        if (n <= 256) return launch_pm<T, R, 16, 16>(js, tp, s);
-        if (n <= 320) return launch_pm<T, R, 32, 10>(js, tp, s);
-        if (n <= 384) return launch_pm<T, R, 32, 12>(js, tp, s);
-        if (n <= 512) return launch_pm<T, R, 32, 16>(js, tp, s);
-        if (n <= 768) return launch_pm<T, R, 48, 16>(js, tp, s);
+        if (n <= 224) return launch_pm<T, R, 16, 14>(src, s);
+        if (n <= 256) return launch_pm<T, R, 16, 16>(src, s);
+        if (n <= 320) return launch_pm<T, R, 32, 10>(src, s);
+        if (n <= 384) return launch_pm<T, R, 32, 12>(src, s);
+        if (n <= 512) return launch_pm<T, R, 32, 16>(src, s);
+        if (n <= 768) return launch_pm<T, R, 48, 16>(src, s);
     }
     return hipErrorInvalidValue;
 }
@@ -66,17 +67,17 @@ static double helmholtz_kappa(const JobSet &js, const Plan &p)
 template <typename T, typename R>
 static hipError_t launch_rows(const Plan &p, const JobSet &js, const TriParams &tp, int n, hipStream_t s)
 {
+    const TriSet src{js, tp};
     if (p.py) {
-        if constexpr (sizeof(T) == 8) return launch_cyclic_dd(js, tp, n, s);
-        else if constexpr (sizeof(R) == 8) return launch_cyclic_fd(js, tp, n, s);
-        else return launch_cyclic_ff(js, tp, n, s);
+        if constexpr (sizeof(T) == 8) return launch_cyclic_dd(src, n, s);
+        else if constexpr (sizeof(R) == 8) return launch_cyclic_fd(src, n, s);
+        else return launch_cyclic_ff(src, n, s);
     }
-    return launch_by_rows<T, R>(js, tp, n, s);
+    return launch_by_rows<T, R>(src, n, s);
 }
 
-template <typename T>
-static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &st, bool poisson, int pass,
-                                 hipStream_t s)
+// What every launch on a plan shares: its tables and sizes, no state.
+static TriParams tri_params(const Plan &p, bool poisson)
 {
     TriParams tp;
     for (int xk = 0; xk < NUM_XK; ++xk) tp.lam_x[xk] = blob_ptr(p, p.lay.lam_x[xk]);
@@ -87,7 +88,7 @@ static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &s
         tp.up[kd] = blob_ptr(p, p.lay.up[kd]);
     }
     tp.wy = blob_ptr(p, p.lay.wy);
-    tp.bmean = st.bmean;
+    tp.bmean = nullptr;
     tp.xsum = nullptr;
     tp.record_mean = 1;
     tp.skip = nullptr;
@@ -96,17 +97,29 @@ static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &s
     tp.nx = p.nx;
     tp.nz = p.nz;
     tp.poisson = poisson ? 1 : 0;
+    tp.nxsum = 0;
+    tp.inv_sqrt_nxnz = 1.0 / std::sqrt((double)p.nx * (double)p.nz);
+    tp.lane_mask = nullptr;
+    tp.lane_list = nullptr;
+    tp.lane_len = 0;
+    tp.lane_mode = 0;
+    tp.bmax = nullptr;
+    tp.scale = nullptr;
+    return tp;
+}
+
+template <typename T>
+static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &st, bool poisson, int pass,
+                                 hipStream_t s)
+{
+    TriParams tp = tri_params(p, poisson);
+    tp.bmean = st.bmean;
     tp.nxsum = residual_tiles(p);
     if (pass > 0) {
         tp.record_mean = 0;
         tp.xsum = st.xsum;
     }
     if (pass >= 2) tp.skip = st.done;
-    tp.inv_sqrt_nxnz = 1.0 / std::sqrt((double)p.nx * (double)p.nz);
-    tp.lane_mask = nullptr;
-    tp.lane_list = nullptr;
-    tp.lane_len = 0;
-    tp.lane_mode = 0;
     // refined path (FP32 data): the first pass records the partial maxima
     // the residual scale is taken from; later passes steer in its units
     tp.bmax = (sizeof(T) == 4 && pass == 0) ? st.bmax : nullptr;
@@ -137,6 +150,21 @@ static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &s
         }
     }
     return launch_rows<T, double>(p, js, tp, n, s);
+}
+
+size_t tri_entry_bytes() { return sizeof(TriEntry); }
+
+void tri_entry_fill(void *to, const Plan &p, const FieldJob &job, bool poisson)
+{
+    TriEntry &e = *static_cast<TriEntry *>(to);
+    e.job = job;
+    e.tp = tri_params(p, poisson);
+    e.tp.record_mean = 0;
+}
+
+hipError_t launch_tridiag_table(const void *entries, int n, int nx, int ny, int nz, hipStream_t s)
+{
+    return launch_by_rows<double, double>(TriTable{static_cast<const TriEntry *>(entries), n, nx, nz}, ny, s);
 }
 
 hipError_t launch_tridiag_f64(const JobSet &js, const Plan &p, const State &st, bool poisson, hipStream_t s)

@@ -97,6 +97,31 @@ struct TriParams {
     const double *scale;   // later passes: per job sigma, or null (1)
 };
 
+// Where a launch takes its fields from: a few jobs of one plan by value, or a
+// table in device memory (fields of many plans, all of one grid size).
+struct TriSet {
+    JobSet js;
+    TriParams tp;
+    __device__ __forceinline__ const FieldJob &job(int q) const { return js.j[q]; }
+    __device__ __forceinline__ const TriParams &params(int) const { return tp; }
+    int count() const { return js.n; }
+    int tiles(int TA) const { return tp.lane_mode == 2 ? tp.lane_len * (32 / TA) : tp.nx / TA * tp.nz; }
+    int width() const { return tp.nx / 32 * tp.nz * js.n; }
+};
+struct TriEntry {
+    FieldJob job;
+    TriParams tp;
+};
+struct TriTable {
+    const TriEntry *e;
+    int n, nx, nz;
+    __device__ __forceinline__ const FieldJob &job(int q) const { return e[q].job; }
+    __device__ __forceinline__ const TriParams &params(int q) const { return e[q].tp; }
+    int count() const { return n; }
+    int tiles(int TA) const { return nx / TA * nz; }
+    int width() const { return nx / 32 * nz * n; }
+};
+
 // The singular pressure pencil, in LDS, by one wave: y holds n right-hand
 // side values on entry and the solution on return.  The volume-weighted mean
 // of the right-hand side is removed (and returned); the rest is solved by
@@ -177,8 +202,8 @@ template <typename R, int P, int M, int TA> constexpr int tri_waves()
     if (P * TA > 512 && sizeof(R) == 4) return M >= 16 && P * TA <= 768 ? 6 : 4;
     return sizeof(R) == 4 ? (M <= 8 ? 8 : M <= 12 ? 7 : 6) : (M <= 4 ? 8 : M <= 6 ? 6 : M <= 8 ? 5 : 4);
 }
-template <typename T, typename R, int P, int M, int TA, bool CYC = false, bool BMX = false>
-__global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())) void tridiag_kernel(JobSet js, TriParams tp)
+template <typename T, typename R, int P, int M, int TA, bool CYC = false, bool BMX = false, typename Src = TriSet>
+__global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())) void tridiag_kernel(Src src)
 {
     static_assert(P % 2 == 0 && M >= 2 && 64 % TA == 0, "two solver lanes per pencil in one wave");
     constexpr int NT = (TA * P + 63) / 64 * 64, NW = NT / 64;
@@ -191,7 +216,9 @@ __global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())
     // distances delta_{j+1}
     __shared__ double pin_sm[P * M], wt_sm[P * M], dl_sm[P * M];
 
-    const int tid = threadIdx.x, nx = tp.nx, job = blockIdx.y;
+    const int tid = threadIdx.x, job = blockIdx.y;
+    const TriParams &tp = src.params(job);
+    const int nx = tp.nx;
     if (tp.skip && tp.skip[job]) return;   // converged (later refinement passes)
     int c, a0;
     if (tp.lane_mode == 2) {
@@ -206,7 +233,7 @@ __global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())
         // tiles left to the FP64 lane
         if (tp.lane_mode == 1 && ((tp.lane_mask[c] >> (a0 >> 5)) & 1u)) return;
     }
-    const FieldJob &jb = js.j[job];
+    const FieldJob &jb = src.job(job);
     // the v systems leave out the first wall row (kept at zero below)
     const int kind = jb.kind, sys0 = skip_first_row(kind), n = jb.rows - sys0;
     const bool walls = kind == KIND_F, pois = tp.poisson != 0;
@@ -437,25 +464,26 @@ __global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())
     }
 }
 
-template <typename T, typename R, int P, int M, bool CYC, bool BMX>
-static hipError_t launch_pm_k(const JobSet &js, const TriParams &tp, hipStream_t s)
+template <typename T, typename R, int P, int M, bool CYC, bool BMX, typename Src>
+static hipError_t launch_pm_k(const Src &src, hipStream_t s)
 {
     // pencils per tile: one 128-byte line of a row of FP64 data, or of FP32
     // data in FP32 arithmetic; FP32 data in FP64 arithmetic (the few tiles of
     // the FP64 lane) take 16, so that their registers hold two blocks per CU
     constexpr int TA = sizeof(R) == 8 ? 16 : 32;
-    const int tiles = tp.lane_mode == 2 ? tp.lane_len * (32 / TA) : tp.nx / TA * tp.nz;
+    const int tiles = src.tiles(TA);
     if (tiles == 0) return hipSuccess;
-    tridiag_kernel<T, R, P, M, TA, CYC, BMX><<<dim3(tiles, js.n), dim3((TA * P + 63) / 64 * 64), 0, s>>>(js, tp);
+    tridiag_kernel<T, R, P, M, TA, CYC, BMX, Src>
+        <<<dim3(tiles, src.count()), dim3((TA * P + 63) / 64 * 64), 0, s>>>(src);
     return hipGetLastError();
 }
 
-template <typename T, typename R, int P, int M, bool CYC = false>
-static hipError_t launch_pm(const JobSet &js, const TriParams &tp, hipStream_t s)
+template <typename T, typename R, int P, int M, bool CYC = false, typename Src>
+static hipError_t launch_pm(const Src &src, hipStream_t s)
 {
     if constexpr (sizeof(T) == 4)
-        if (tp.bmax) return launch_pm_k<T, R, P, M, CYC, true>(js, tp, s);
-    return launch_pm_k<T, R, P, M, CYC, false>(js, tp, s);
+        if (src.tp.bmax) return launch_pm_k<T, R, P, M, CYC, true>(src, s);
+    return launch_pm_k<T, R, P, M, CYC, false>(src, s);
 }
 
 }  // namespace ibs
@@ -463,7 +491,7 @@ static hipError_t launch_pm(const JobSet &js, const TriParams &tp, hipStream_t s
 namespace ibs {
 // Cyclic launches (periodic y), k_tridiag_cyc.hip: n must be one of the
 // sizes cyclic_rows_supported() accepts (n = P M exactly).
-hipError_t launch_cyclic_dd(const JobSet &js, const TriParams &tp, int n, hipStream_t s);
-hipError_t launch_cyclic_fd(const JobSet &js, const TriParams &tp, int n, hipStream_t s);
-hipError_t launch_cyclic_ff(const JobSet &js, const TriParams &tp, int n, hipStream_t s);
+hipError_t launch_cyclic_dd(const TriSet &src, int n, hipStream_t s);
+hipError_t launch_cyclic_fd(const TriSet &src, int n, hipStream_t s);
+hipError_t launch_cyclic_ff(const TriSet &src, int n, hipStream_t s);
 }  // namespace ibs
