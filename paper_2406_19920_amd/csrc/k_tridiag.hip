@@ -134,7 +134,13 @@ static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &s
     // condition numbers bounded by FP32_KAPPA.
     if constexpr (sizeof(T) == 4) {
         if (!poisson && helmholtz_kappa(js, p) <= FP32_KAPPA) return launch_rows<T, float>(p, js, tp, n, s);
-        if (poisson && p.lane_len > 0) {
+        // few tiles: FP64 arithmetic on all of them in one launch costs less
+        // than the lane's launch on top of the FP32 one (us per pass, one
+        // launch against both: 64^3 7 / 13, 128^3 15 / 17, 192x128x192 23 / 26,
+        // 192x256x192 32 / 33, 256^3 49 / 42; side by side with other
+        // work, where only the throughput counts, the larger ones do not gain)
+        constexpr int ONE_LAUNCH_TILES = 4 * 256;   // 16-wide tiles, four per CU
+        if (poisson && p.lane_len > 0 && p.nx / 16 * p.nz * js.n > ONE_LAUNCH_TILES) {
             // pressure pencils: FP32 arithmetic on every tile but the FP64
             // lane's, then FP64 arithmetic on the lane's tiles (disjoint
             // pencils; the lane holds the singular (0,0) pencil and every
