@@ -182,26 +182,16 @@ template <typename Set> static double transform_flops(const Plan &p, const Set &
 {
     const int n = z_axis ? p.nz : p.nx;
     const bool folds = z_axis ? z_folds(p) : x_folds(p);
+    const bool fast = z_axis ? p.fz : p.fx;
     double f = 0;
-    for (int q = 0; q < js.n; ++q) {
-        const bool fast = z_axis ? p.fz[js.j[q].zk] : p.fx[js.j[q].xk];
+    for (int q = 0; q < js.n; ++q)
         f += (fast ? 2.5 * std::log2((double)n) : (folds ? 1.0 : 2.0) * n) * (double)p.nz * js.j[q].rows * p.nx;
-    }
     return f;
 }
 
-// The jobs of a set for which pick(job) holds.
-template <typename Set, typename F> static Set jobs_where(const Set &all, F pick)
-{
-    Set s{};
-    for (int q = 0; q < all.n; ++q)
-        if (pick(all.j[q])) s.j[s.n++] = all.j[q];
-    return s;
-}
-
 // The five FP64 stages.  js.j[q].in holds the right-hand side; W[q] is the
-// job's scratch field and X[q] its output.  A job whose x and z transforms
-// are both fast ones works in place on X (its stages after the first touch
+// job's scratch field and X[q] its output.  Where the x and z transforms are
+// both fast ones the jobs work in place on X (the stages after the first touch
 // one field, which for fields up to the 256 MB Infinity Cache then stays
 // there); the dense products need a second field and alternate X and W.
 static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, double *const *X,
@@ -217,34 +207,25 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, 
         za[0][k] = blob_ptr(p, p.lay.az_fwd[k]);
         za[1][k] = blob_ptr(p, p.lay.az_inv[k]);
     }
-    bool in_place[4];
-    for (int q = 0; q < js.n; ++q) in_place[q] = p.fx[js.j[q].xk] && p.fz[js.j[q].zk];
+    const bool in_place = p.fx && p.fz;
     // in, out of every job for a stage; b: the right-hand side
-    enum Buf { RHS, PING, PONG };   // PING: X; PONG: W, or X for an in-place job
+    enum Buf { RHS, PING, PONG };   // PING: X; PONG: W, or X in place
     auto bind = [&](Buf in, Buf out) {
         for (int q = 0; q < js.n; ++q) {
-            auto at = [&](Buf f) { return f == PONG && !in_place[q] ? W[q] : X[q]; };
+            auto at = [&](Buf f) { return f == PONG && !in_place ? W[q] : X[q]; };
             if (in != RHS) js.j[q].in = at(in);
             js.j[q].out = at(out);
         }
     };
     auto xform = [&](bool inverse) {
-        const JobSet fast = jobs_where(js, [&](const FieldJob &j) { return p.fx[j.xk]; });
-        const JobSet rest = jobs_where(js, [&](const FieldJob &j) { return !p.fx[j.xk]; });
-        if (fast.n)
-            if (hipError_t r = launch_fft_f64(fast, p, false, inverse, s); r != hipSuccess) return r;
-        if (!rest.n) return hipSuccess;
-        return x_folds(p) ? launch_xfold_f64(rest, p, inverse, s)
-                          : launch_xgemm_f64(rest, p.nz, p.nx, p.nx, xb[inverse], s);
+        if (p.fx) return launch_fft_f64(js, p, false, inverse, s);
+        return x_folds(p) ? launch_xfold_f64(js, p, inverse, s)
+                          : launch_xgemm_f64(js, p.nz, p.nx, p.nx, xb[inverse], s);
     };
     auto zform = [&](bool inverse) {
-        const JobSet fast = jobs_where(js, [&](const FieldJob &j) { return p.fz[j.zk]; });
-        const JobSet rest = jobs_where(js, [&](const FieldJob &j) { return !p.fz[j.zk]; });
-        if (fast.n)
-            if (hipError_t r = launch_fft_f64(fast, p, true, inverse, s); r != hipSuccess) return r;
-        if (!rest.n) return hipSuccess;
-        return z_folds(p) ? launch_zfold_f64(rest, p, inverse, s)
-                          : launch_zgemm_f64(rest, p.nz, p.nz, p.nx, za[inverse], s);
+        if (p.fz) return launch_fft_f64(js, p, true, inverse, s);
+        return z_folds(p) ? launch_zfold_f64(js, p, inverse, s)
+                          : launch_zgemm_f64(js, p.nz, p.nz, p.nx, za[inverse], s);
     };
     const double xflop = transform_flops(p, js, false), zflop = transform_flops(p, js, true);
     bind(RHS, PONG);
@@ -299,26 +280,20 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
     double cells = 0;
     for (int q = 0; q < ss.n; ++q) cells += (double)p.nz * ss.j[q].rows * p.nx;
     const double xfl = transform_flops(p, ss, false), zfl = transform_flops(p, ss, true);
-    // a job whose transforms are both fast ones works in place on its second
+    // with both transforms fast ones the jobs work in place on their second
     // field; the dense products alternate between the two
     float *D1[4];
     for (int q = 0; q < ss.n; ++q) {
         ss.j[q].slot = q;
-        D1[q] = p.fx[ss.j[q].xk] && p.fz[ss.j[q].zk] ? W2[q] : W1[q];
+        D1[q] = p.fx && p.fz ? W2[q] : W1[q];
     }
     auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
-        const SplitSet fast = jobs_where(all, [&](const SplitJob &j) { return p.fx[j.xk]; });
-        const SplitSet rest = jobs_where(all, [&](const SplitJob &j) { return !p.fx[j.xk]; });
-        hipError_t r = fast.n ? launch_fft_x32(fast, p, st, inverse, in64, mode, pass, s) : hipSuccess;
-        if (r != hipSuccess || !rest.n) return r;
-        return launch_split_xgemm(rest, p, st, inverse, in64, mode, pass, s);
+        return p.fx ? launch_fft_x32(all, p, st, inverse, in64, mode, pass, s)
+                    : launch_split_xgemm(all, p, st, inverse, in64, mode, pass, s);
     };
     auto zform = [&](const SplitSet &all, bool inverse, int pass) {
-        const SplitSet fast = jobs_where(all, [&](const SplitJob &j) { return p.fz[j.zk]; });
-        const SplitSet rest = jobs_where(all, [&](const SplitJob &j) { return !p.fz[j.zk]; });
-        hipError_t r = fast.n ? launch_fft_z32(fast, p, st, inverse, pass, s) : hipSuccess;
-        if (r != hipSuccess || !rest.n) return r;
-        return launch_split_zgemm(rest, p, st, inverse, pass, s);
+        return p.fz ? launch_fft_z32(all, p, st, inverse, pass, s)
+                    : launch_split_zgemm(all, p, st, inverse, pass, s);
     };
     JobSet js{};
     js.n = ss.n;
@@ -817,7 +792,7 @@ ibs_status ibs_autotune(ibs_plan plan, void *scratch, size_t scratch_bytes, int3
         if (!k.applies) {
             // walls: no tiles at all; a fast transform has one shape and
             // reports the first choice
-            p.tune[k.id] = k.id == TUNE_XFOLD ? (p.fx[XK_P] && !p.wx ? 0 : -1) : (p.fz[XK_P] && !p.wz ? 0 : -1);
+            p.tune[k.id] = k.id == TUNE_XFOLD ? (p.fx && !p.wx ? 0 : -1) : (p.fz && !p.wz ? 0 : -1);
             continue;
         }
         std::vector<float> cand_ms(fold_candidates(), 0.f);

@@ -273,13 +273,16 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
     };
     struct Pending { MgField f; size_t xf, xi, zf, zi; };
     std::vector<Pending> fields;
-    // fast fields by grid: nx, ny, nz, walls in x, z
+    // fast fields by grid (nx, ny, nz, walls in x, z) and by being the one on
+    // the x or z faces
     struct Fast { const Plan *p; FieldJob job; bool poisson; };
-    typedef std::tuple<int, int, int, bool, bool> Key;
+    typedef std::tuple<int, int, int, bool, bool, bool, bool> Key;
     std::map<Key, std::vector<Fast>> groups;
     std::map<Key, size_t> group_bytes;
-    auto key_of = [](const Plan &p) { return Key(p.nx, p.ny, p.nz, p.wx, p.wz); };
-    auto fast_field = [](const Plan &p, int xk, int zk) { return p.fx[xk] && p.fz[zk] && p.ny > MG_THOMAS_ROWS; };
+    auto key_of = [](const Plan &p, int xk, int zk) {
+        return Key(p.nx, p.ny, p.nz, p.wx, p.wz, xk == XK_F, zk == XK_F);
+    };
+    auto fast_plan = [](const Plan &p) { return p.fx && p.fz && p.ny > MG_THOMAS_ROWS; };
     auto kinds_of = [&](const ibs_batch_job &j, int k, int &kind, int &xk, int &zk) {
         const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
         const bool pois = j.op == IBS_OP_POISSON;
@@ -321,7 +324,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         for (int k = 0; k < (j.op == IBS_OP_POISSON ? 1 : j.ncomp); ++k) {
             int kind, xk, zk;
             kinds_of(j, k, kind, xk, zk);
-            if (fast_field(p, xk, zk)) group_bytes[key_of(p)] += (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double);
+            if (fast_plan(p)) group_bytes[key_of(p, xk, zk)] += (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double);
         }
     }
     for (int q = 0; q < njobs; ++q) {
@@ -332,7 +335,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         for (int k = 0; k < nc; ++k) {
             int kind, xk, zk;
             kinds_of(j, k, kind, xk, zk);
-            if (fast_field(p, xk, zk) && group_bytes[key_of(p)] >= MG_GROUP_BYTES) {
+            if (fast_plan(p) && group_bytes[key_of(p, xk, zk)] >= MG_GROUP_BYTES) {
                 Fast f{&p, FieldJob{}, pois};
                 f.job.in = j.rhs[k];
                 f.job.out = j.x[k];
@@ -342,7 +345,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
                 f.job.zk = zk;
                 f.job.c = pois ? 0.0 : j.c[k];
                 f.job.info = j.info ? j.info + k : nullptr;
-                groups[key_of(p)].push_back(f);
+                groups[key_of(p, xk, zk)].push_back(f);
                 continue;
             }
             Pending e{};
@@ -391,7 +394,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
     // the groups' tables: per field the four transforms and the pencils
     const size_t fe = fft_entry_bytes(), te = tri_entry_bytes();
     std::vector<unsigned char> fast_img;
-    struct Chain { int nx, ny, nz, n; bool wx, wz; size_t at[5]; };   // x, z forward, z, x inverse, pencils
+    struct Chain { int nx, ny, nz, n; bool wx, wz; int xk, zk; size_t at[5]; };   // x, z forward, z, x inverse, pencils
     std::vector<Chain> chains;
     for (const auto &g : groups) {
         const std::vector<Fast> &all = g.second;
@@ -399,7 +402,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         const size_t per = std::max<size_t>(1, MG_CHAIN_BYTES / ((size_t)p0.nz * (p0.ny + 1) * p0.nx * sizeof(double)));
         for (size_t first = 0; first < all.size(); first += per) {
             const size_t n = std::min(per, all.size() - first);
-            Chain c{p0.nx, p0.ny, p0.nz, (int)n, p0.wx, p0.wz, {}};
+            Chain c{p0.nx, p0.ny, p0.nz, (int)n, p0.wx, p0.wz, all[first].job.xk, all[first].job.zk, {}};
             for (int stage = 0; stage < 5; ++stage) {
                 c.at[stage] = (fast_img.size() + 255) & ~size_t(255);
                 const size_t sz = stage < 4 ? fe : te;
@@ -471,7 +474,8 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
             const unsigned char *t = dev + o_fast;
             auto fft = [&](int stage, bool z_axis, bool inverse) {
                 if (le == hipSuccess)
-                    le = launch_fft_table(t + c.at[stage], c.n, c.nx, c.ny, c.nz, z_axis, inverse, z_axis ? c.wz : c.wx, cap);
+                    le = launch_fft_table(t + c.at[stage], c.n, c.nx, c.ny, c.nz, z_axis, inverse, z_axis ? c.wz : c.wx,
+                                          z_axis ? c.zk : c.xk, cap);
             };
             fft(0, false, false);
             fft(1, true, false);

@@ -5,11 +5,19 @@ namespace ibs {
 
 static const void *table(const Plan &p, size_t off) { return blob_ptr(p, off); }
 
+// form of an axis's transform for a field of kind xk along it
+static int axis_form(bool walls, int xk)
+{
+    return !walls ? fft::AX_PERIODIC : (xk == XK_F ? fft::AX_FACES : fft::AX_CENTRES);
+}
+
 static FftJob fft_job(const Plan &p, bool z_axis, bool inverse, int rows, int ykind, int kind, int slot)
 {
     const BlobLayout &L = p.lay;
     FftJob f{};
-    f.tw = table(p, z_axis ? (inverse ? L.ftz_inv : L.ftz_fwd) : (inverse ? L.ftx_inv : L.ftx_fwd));
+    const bool faces = axis_form(z_axis ? p.wz : p.wx, kind) == fft::AX_FACES;
+    if (faces) f.tw = table(p, z_axis ? L.ftz_face : L.ftx_face);
+    else f.tw = table(p, z_axis ? (inverse ? L.ftz_inv : L.ftz_fwd) : (inverse ? L.ftx_inv : L.ftx_fwd));
     f.rot = table(p, z_axis ? (inverse ? L.frz_inv : L.frz_fwd) : (inverse ? L.frx_inv : L.frx_fwd));
     f.rows = rows;
     f.skip = skip_first_row(ykind);
@@ -21,16 +29,22 @@ static FftJob fft_job(const Plan &p, bool z_axis, bool inverse, int rows, int yk
 // every component has ny transform rows per plane
 hipError_t launch_fft_f64(const JobSet &js, const Plan &p, bool z_axis, bool inverse, hipStream_t s)
 {
-    FftSet f{};
-    f.n = js.n;
-    for (int q = 0; q < js.n; ++q) {
-        const FieldJob &j = js.j[q];
-        f.j[q] = fft_job(p, z_axis, inverse, j.rows, j.kind, z_axis ? j.zk : j.xk, q);
-        f.j[q].in = j.in;
-        f.j[q].out = j.out;
+    for (int ax = 0; ax < 3; ++ax) {   // the jobs by form: at most two launches
+        FftSet f{};
+        for (int q = 0; q < js.n; ++q) {
+            const FieldJob &j = js.j[q];
+            const int kind = z_axis ? j.zk : j.xk;
+            if (axis_form(z_axis ? p.wz : p.wx, kind) != ax) continue;
+            FftJob &to = f.j[f.n++];
+            to = fft_job(p, z_axis, inverse, j.rows, j.kind, kind, q);
+            to.in = j.in;
+            to.out = j.out;
+        }
+        const hipError_t e = z_axis ? launch_fft_z64(f, p.nz, p.ny, p.nx, inverse, ax, s)
+                                    : launch_fft_x64(f, p.nx, p.ny, p.nz, inverse, ax, s);
+        if (e != hipSuccess) return e;
     }
-    return z_axis ? launch_fft_z64(f, p.nz, p.ny, p.nx, inverse, p.wz, s)
-                  : launch_fft_x64(f, p.nx, p.ny, p.nz, inverse, p.wx, s);
+    return hipSuccess;
 }
 
 size_t fft_entry_bytes() { return sizeof(FftJob); }
@@ -44,46 +58,59 @@ void fft_entry_fill(void *to, const Plan &p, const FieldJob &job, bool z_axis, b
 }
 
 hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, bool z_axis, bool inverse, bool walls,
-                            hipStream_t s)
+                            int kind, hipStream_t s)
 {
     const FftTable t{static_cast<const FftJob *>(entries), n};
-    return z_axis ? launch_fft_z64(t, nz, ny, nx, inverse, walls, s) : launch_fft_x64(t, nx, ny, nz, inverse, walls, s);
+    const int ax = axis_form(walls, kind);
+    return z_axis ? launch_fft_z64(t, nz, ny, nx, inverse, ax, s) : launch_fft_x64(t, nx, ny, nz, inverse, ax, s);
 }
 
 hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
                           int pass, hipStream_t s)
 {
     const int *skip = pass >= 2 ? st.done : nullptr;
-    FftSet f{};
-    f.n = ss.n;
-    for (int q = 0; q < ss.n; ++q) {
-        const SplitJob &j = ss.j[q];
-        f.j[q] = fft_job(p, false, inverse, j.rows, j.kind, j.xk, j.slot);
-        f.j[q].in = j.in;
-        f.j[q].out = !inverse ? static_cast<void *>(j.out) : (mode == 3 ? j.xs : static_cast<void *>(j.x));
-        f.j[q].xs = j.xs;
-        f.j[q].x0 = j.x;
-    }
-    if (!inverse) return launch_fft_x32_fwd(f, p.nx, p.ny, p.nz, p.wx, in64, skip, s);
     const bool upd = mode == 2 || mode == 4;
     double *red = upd ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
     const double *scale = upd ? st.scale : nullptr;
     const int stride = (int)update_slots(p);
-    return p.wx ? launch_fft_x32_wall(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s)
-                : launch_fft_x32_inv(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
+    for (int ax = 0; ax < 3; ++ax) {
+        FftSet f{};
+        for (int q = 0; q < ss.n; ++q) {
+            const SplitJob &j = ss.j[q];
+            if (axis_form(p.wx, j.xk) != ax) continue;
+            FftJob &to = f.j[f.n++];
+            to = fft_job(p, false, inverse, j.rows, j.kind, j.xk, j.slot);
+            to.in = j.in;
+            to.out = !inverse ? static_cast<void *>(j.out) : (mode == 3 ? j.xs : static_cast<void *>(j.x));
+            to.xs = j.xs;
+            to.x0 = j.x;
+        }
+        hipError_t e;
+        if (!inverse) e = launch_fft_x32_fwd(f, p.nx, p.ny, p.nz, ax, in64, skip, s);
+        else if (ax == fft::AX_FACES) e = launch_fft_x32_face(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
+        else if (ax) e = launch_fft_x32_wall(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
+        else e = launch_fft_x32_inv(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s)
 {
-    FftSet f{};
-    f.n = ss.n;
-    for (int q = 0; q < ss.n; ++q) {
-        const SplitJob &j = ss.j[q];
-        f.j[q] = fft_job(p, true, inverse, j.rows, j.kind, j.zk, j.slot);
-        f.j[q].in = j.in;
-        f.j[q].out = j.out;
+    for (int ax = 0; ax < 3; ++ax) {
+        FftSet f{};
+        for (int q = 0; q < ss.n; ++q) {
+            const SplitJob &j = ss.j[q];
+            if (axis_form(p.wz, j.zk) != ax) continue;
+            FftJob &to = f.j[f.n++];
+            to = fft_job(p, true, inverse, j.rows, j.kind, j.zk, j.slot);
+            to.in = j.in;
+            to.out = j.out;
+        }
+        if (hipError_t e = launch_fft_z32(f, p.nz, p.ny, p.nx, inverse, ax, pass >= 2 ? st.done : nullptr, s); e != hipSuccess)
+            return e;
     }
-    return launch_fft_z32(f, p.nz, p.ny, p.nx, inverse, p.wz, pass >= 2 ? st.done : nullptr, s);
+    return hipSuccess;
 }
 
 }  // namespace ibs

@@ -6,15 +6,22 @@
 namespace ibs {
 namespace fft {
 
+// What an axis's transform is: the periodic Fourier basis, a basis of a walled
+// axis on cell centres (cosine, sine), or the sine basis on its inner faces.
+enum { AX_PERIODIC = 0, AX_CENTRES = 1, AX_FACES = 2 };
+
 template <typename T> struct Cpx { T x, y; };
 
 template <int R1, int R2> struct Shape {
     static constexpr int N = R1 * R2, H = N / 2, K1 = R1 / 2 + 1;   // K1 values of k1
-    static constexpr int W = K1 > R2 ? K1 : R2;                     // work items per line
-    static constexpr int threads(int lines) { return (W * lines + 63) / 64 * 64; }   // whole waves
+    // stage A's items n2 (faces: one more), threads for the items of `lines`
+    // lines, whole waves
+    static constexpr int items(int ax) { return ax == AX_FACES ? R2 + 1 : R2; }
+    static constexpr int threads(int ax, int lines)
+    {
+        return ((K1 > items(ax) ? K1 : items(ax)) * lines + 63) / 64 * 64;
+    }
     static constexpr int LOW = (R2 + 1) / 2;                        // k2 < LOW: k <= N/2
-    // x kernel: LDS line of one row, odd strides against bank conflicts
-    static constexpr int KS = R2 | 1, RS = (K1 * KS) | 1;
     static_assert(R1 % 2 == 0, "stage A needs an even size");
 };
 
@@ -122,6 +129,43 @@ template <int R1, int R2, bool WALL> IBS_FFT_FN int line_index(int n2, int n1)
     const int n = n2 + R2 * n1;
     if (!WALL) return n;
     return 2 * n1 < R1 ? 2 * n : 2 * R1 * R2 - 1 - 2 * n;
+}
+
+// Sine basis on the inner faces 1 .. N-1 of a walled axis, its own inverse
+// (slot 0, the wall face, counts as zero and becomes zero).  The line's odd
+// extension e to length L = 2N = R1 (2 R2) has a purely imaginary spectrum,
+// and stage A's results, twiddle included, are anti-Hermitian in n2: stage A
+// runs for n2 = 0 .. R2 only and stage B is a Hermitian-to-real transform of
+// length 2 R2, as much work as a periodic line of N.  Twiddle factors
+// [k1][n2 <= R2] e^{-2 pi i k1 n2 / L} sqrt(2/N) / 2.
+//
+// e_n, n = n2 + 2 R2 n1, is the value of slot face_slot, negated for 2 n1 >=
+// R1, times zero where face_wall (not left out: a NaN there stays one).
+template <int R1> IBS_FFT_FN bool face_wall(int n2, int n1) { return n2 == 0 && (n1 == 0 || 2 * n1 == R1); }
+template <int R1, int R2> IBS_FFT_FN int face_slot(int n2, int n1)
+{
+    const int n = n2 + 2 * R2 * n1;
+    return face_wall<R1>(n2, n1) ? 0 : (2 * n1 < R1 ? n : 2 * R1 * R2 - n);
+}
+template <int R1, typename T> IBS_FFT_FN T face_value(T v, int n2, int n1)
+{
+    if (face_wall<R1>(n2, n1)) v *= (T)0;
+    return 2 * n1 >= R1 ? -v : v;
+}
+// Stage B of item k1, re, im its R2 + 1 values: put(slot, value) for every
+// coefficient the item owns.
+template <int R1, int R2, typename T, typename F>
+IBS_FFT_FN void face_emit(const T (&re)[R2 + 1], const T (&im)[R2 + 1], int k1, F put)
+{
+    T v[2 * R2];
+    hdft<2 * R2, T>(im, re, v);   // anti-Hermitian: v the spectrum's imaginary part
+    const bool ends = k1 == 0 || 2 * k1 == R1;
+#pragma unroll
+    for (int k2 = 0; k2 < 2 * R2; ++k2) {
+        const int k = k1 + R1 * k2;
+        if (k2 < R2) put(k, k ? -v[k2] : (T)0 * v[k2]);
+        else if (!ends) put(2 * R1 * R2 - k, v[k2]);   // the odd partner
+    }
 }
 
 }  // namespace fft

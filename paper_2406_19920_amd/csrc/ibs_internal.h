@@ -44,9 +44,9 @@ struct BlobLayout {
     size_t fz_fwd_c, fz_fwd_s, fz_inv_c, fz_inv_s;   // A-operand swizzle
     // fast transforms (complex, in the transform's arithmetic type): twiddle
     // factors [k1][n2] forward / inverse, and with walls the rotations of the
-    // N/2 + 1 coefficient pairs
-    size_t ftx_fwd, ftx_inv, frx_fwd, frx_inv;
-    size_t ftz_fwd, ftz_inv, frz_fwd, frz_inv;
+    // N/2 + 1 coefficient pairs and the twiddle factors of the faces' lines
+    size_t ftx_fwd, ftx_inv, frx_fwd, frx_inv, ftx_face;
+    size_t ftz_fwd, ftz_inv, frz_fwd, frz_inv, ftz_face;
     size_t lam_x[NUM_XK], lam_z[NUM_XK];   // eigenvalues (double) per x / z kind
     size_t lo[NUM_KINDS], di[NUM_KINDS], up[NUM_KINDS];  // y operator rows
     size_t wy;               // Delta_j (pressure weights), ny doubles
@@ -158,7 +158,7 @@ struct Plan {
     bool wx = false;                               // walls at x = 0 and x = lx
     bool wz = false;                               // walls at z = 0 and z = lz
     bool sx = false, sz = false;                   // stretched (wall-bounded) x / z
-    bool fx[NUM_XK] = {}, fz[NUM_XK] = {};         // the x / z kind has a fast transform
+    bool fx = false, fz = false;                   // the x / z axis has fast transforms
     int tune[NUM_TUNE] = {-1, -1};   // candidate index per knob; -1 = default
     int nx, ny, nz;
     double hx, hz;
@@ -250,11 +250,10 @@ hipError_t launch_xgemm_f64(const JobSet &js, int nz, int K, int N,
                             const double *const bs[NUM_XK], hipStream_t s);
 // C[M x Ncol] = As * B, As the swizzled M x K matrix, B row-major (K x Ncol),
 // Ncol = rows * nx per job.
-// Lengths the fast transforms are built for (fft_sizes.h), and whether basis
-// (-1 periodic, else XK_*) on an axis of n points takes them: uniform
-// spacing, and not the face-normal sine basis (n - 1 unknowns).
+// Lengths the fast transforms are built for (fft_sizes.h); an axis takes them
+// if its spacing is uniform.
 bool fft_size(int n);
-inline bool fft_axis(int n, int basis, bool stretched) { return !stretched && basis != XK_F && fft_size(n); }
+inline bool fft_axis(int n, bool stretched) { return !stretched && fft_size(n); }
 // Folded FP64 transforms (valid when can_fold(n)).
 bool can_fold(int n);
 int fold_candidates();
@@ -262,9 +261,9 @@ int fold_candidates();
 inline bool can_fold_split(int n) { return n % 64 == 0; }
 // The folds use the Fourier basis's mirror symmetry: a direction folds only
 // when it is periodic (and has no fast transform).
-inline bool x_folds(const Plan &p) { return !p.wx && can_fold(p.nx) && !p.fx[XK_P]; }
-inline bool z_folds(const Plan &p) { return !p.wz && can_fold(p.nz) && !p.fz[XK_P]; }
-inline bool z_folds_split(const Plan &p) { return !p.wz && can_fold_split(p.nz) && !p.fz[XK_P]; }
+inline bool x_folds(const Plan &p) { return !p.wx && can_fold(p.nx) && !p.fx; }
+inline bool z_folds(const Plan &p) { return !p.wz && can_fold(p.nz) && !p.fz; }
+inline bool z_folds_split(const Plan &p) { return !p.wz && can_fold_split(p.nz) && !p.fz; }
 hipError_t launch_xfold_f64(const JobSet &js, const Plan &p, bool inverse, hipStream_t s);
 hipError_t launch_zfold_f64(const JobSet &js, const Plan &p, bool inverse, hipStream_t s);
 hipError_t launch_zgemm_f64(const JobSet &js, int M, int K, int nx,
@@ -343,12 +342,10 @@ struct SplitSet {
 // Kernels of pass >= 2 return at once for jobs whose stop flag is set.
 hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64,
                               int mode, int pass, hipStream_t s);
-// Update partials (pairs) one job may write per refinement pass, and the
+// Update partials (pairs) one job writes per refinement pass, and the
 // doubles one pass of ncomp jobs takes (jobs update_slots() apart).
 size_t update_slots(const Plan &p);
 inline size_t update_region(const Plan &p, int ncomp) { return 2 * update_slots(p) * ncomp; }
-// Pairs a job of x kind xk writes.
-size_t update_used(const Plan &p, int xk);
 hipError_t launch_split_zgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass,
                               hipStream_t s);
 // pass: refinement pass (0 records the rhs mean; later passes steer the
@@ -364,16 +361,16 @@ int residual_tiles(const Plan &p);   // residual blocks (x-sum partials) per job
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s);
 hipError_t launch_residual_scale(const SplitSet &ss, const Plan &p, const State &st, hipStream_t s);
 
-// ---- fast transforms (k_fft.h; p.fx / p.fz kinds only) ---------------------
+// ---- fast transforms (k_fft.h; plans with p.fx / p.fz only) ---------------------
 // One pass over each job's field, js.j[q].in to .out (which may be the same
-// field); the jobs of one call share the axis's boundary conditions.
+// field).
 hipError_t launch_fft_f64(const JobSet &js, const Plan &p, bool z_axis, bool inverse, hipStream_t s);
 // The same over a table in device memory (multi-grid batches: n fields of one
-// grid size, walls: of that axis).
+// grid size, walls: of that axis, kind: XK_F, or anything else for all others).
 size_t fft_entry_bytes();
 void fft_entry_fill(void *to, const Plan &p, const FieldJob &job, bool z_axis, bool inverse);
 hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, bool z_axis, bool inverse, bool walls,
-                            hipStream_t s);
+                            int kind, hipStream_t s);
 // Refined path: in64, mode and pass as launch_split_xgemm().
 hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
                           int pass, hipStream_t s);

@@ -19,7 +19,11 @@
 // reordered data v_n = x_{2n}, v_{N-1-n} = x_{2n+1} (the odd points negated
 // for the sine basis), its result turned by e^{-i pi k/2N}: the real part is
 // coefficient k, minus the imaginary part coefficient N - k (Makhoul, 1980);
-// the sine coefficients come in reverse order.
+// the sine coefficients come in reverse order.  The sine basis of the
+// component on the axis's faces is the transform of the line's odd extension
+// to 2N points, of which its symmetry leaves the work of N (fft_line.h).  As
+// dense products those two launches each took 47-54 of a 160x128x160 duct
+// step's 431 us; the step now takes 285 us, walls_x 256^3 refined 1920 -> 1717.
 //
 // Why this form: at 256 points it takes about 25 flops per value where the
 // folded dense product takes 256, so the pass is bound by HBM (the dense
@@ -47,7 +51,7 @@ struct FftJob {
     const void *tw;   // twiddle factors [k1][n2] (complex), normalisation included
     const void *rot;  // walls: e^{-+ i pi k/2N}, k = 0 .. N/2 (complex)
     int rows, skip;   // rows per plane; 1: the first row of a plane is left out
-    int kind;         // XK_P / XK_C (walls)
+    int kind;         // XK_P / XK_C / XK_F (walls)
     int slot;         // job number in the call's state (flags, scale, partial sums)
 };
 struct FftSet {
@@ -119,13 +123,14 @@ static __device__ __forceinline__ void rows_out(const T *lds, const int *prow, T
 // LDS [k1][n2][column], a pad line per k1 so that the two halves of a wave
 // (k1 apart) use different banks.
 // TS: stored type, T: arithmetic.
-template <typename TS, typename T, int R1, int R2, bool INV, bool WALL, typename Set>
-__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) void fft_z_kernel(Set js, int nx,
+template <typename TS, typename T, int R1, int R2, bool INV, int AX, typename Set>
+__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(AX, 128 / sizeof(TS)))) void fft_z_kernel(Set js, int nx,
                                                                                     const int *skip)
 {
     using namespace fft;
     typedef Shape<R1, R2> S;
-    constexpr int CW = 128 / sizeof(TS), KZ = (R2 | 1) * CW;
+    constexpr bool WALL = AX == AX_CENTRES;
+    constexpr int CW = 128 / sizeof(TS), NA = S::items(AX), KZ = (NA | 1) * CW;
     __shared__ T sre[S::K1 * KZ], sim[S::K1 * KZ];
     const FftJob &jb = js.j[blockIdx.y];
     if (skip && skip[jb.slot]) return;
@@ -139,11 +144,37 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) vo
     const Cpx<T> *tw = static_cast<const Cpx<T> *>(jb.tw), *rot = static_cast<const Cpx<T> *>(jb.rot);
     const bool sine = jb.kind == XK_C;
     const T flip = WALL && sine ? (T)-1 : (T)1;
-    if constexpr (!INV) {
+    if constexpr (AX == AX_FACES) {   // both directions
+        if (item <= R2) {
+            T x[R1], yr[S::K1], yi[S::K1];
+#pragma unroll
+            for (int n1 = 0; n1 < R1; ++n1) x[n1] = (T)in[(size_t)face_slot<R1, R2>(item, n1) * ldp];
+#pragma unroll
+            for (int n1 = 0; n1 < R1; ++n1) x[n1] = face_value<R1, T>(x[n1], item, n1);
+            rdft<R1, T>(x, yr, yi);
+#pragma unroll
+            for (int k1 = 0; k1 < S::K1; ++k1) {
+                const Cpx<T> w = tw[k1 * NA + item];
+                const int o = k1 * KZ + item * CW + col;
+                sre[o] = w.x * yr[k1] - w.y * yi[k1];
+                sim[o] = w.x * yi[k1] + w.y * yr[k1];
+            }
+        }
+        __syncthreads();
+        if (item < S::K1) {
+            T re[R2 + 1], im[R2 + 1];
+#pragma unroll
+            for (int n2 = 0; n2 <= R2; ++n2) {
+                re[n2] = sre[item * KZ + n2 * CW + col];
+                im[n2] = sim[item * KZ + n2 * CW + col];
+            }
+            face_emit<R1, R2, T>(re, im, item, [&](int a, T v) { out[(size_t)a * ldp] = (TS)v; });
+        }
+    } else if constexpr (!INV) {
         if (item < R2) {
             T x[R1], yr[S::K1], yi[S::K1];
 #pragma unroll
-            for (int n1 = 0; n1 < R1; ++n1) x[n1] = (T)in[(size_t)line_index<R1, R2, WALL>(item, n1) * ldp];
+            for (int n1 = 0; n1 < R1; ++n1) x[n1] = (T)in[(size_t)line_index<R1, R2, AX == AX_CENTRES>(item, n1) * ldp];
             if constexpr (WALL) {
 #pragma unroll
                 for (int n1 = R1 / 2; n1 < R1; ++n1) x[n1] *= flip;
@@ -166,12 +197,12 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) vo
                 im[n2] = sim[item * KZ + n2 * CW + col];
             }
             cdft<R2, -1, T>(re, im);
-            emit<R1, R2, WALL, T>(re, im, item, sine, rot, [&](int a, T v) { out[(size_t)a * ldp] = (TS)v; });
+            emit<R1, R2, AX == AX_CENTRES, T>(re, im, item, sine, rot, [&](int a, T v) { out[(size_t)a * ldp] = (TS)v; });
         }
     } else {
         if (item < S::K1) {
             T re[R2], im[R2];
-            gather<R1, R2, WALL, T>(re, im, item, sine, rot, [&](int a) { return (T)in[(size_t)a * ldp]; });
+            gather<R1, R2, AX == AX_CENTRES, T>(re, im, item, sine, rot, [&](int a) { return (T)in[(size_t)a * ldp]; });
             cdft<R2, 1, T>(re, im);
 #pragma unroll
             for (int n2 = 0; n2 < R2; ++n2) {
@@ -192,7 +223,7 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) vo
 #pragma unroll
             for (int n1 = 0; n1 < R1; ++n1) {
                 const T v = WALL && 2 * n1 >= R1 ? flip * x[n1] : x[n1];
-                out[(size_t)line_index<R1, R2, WALL>(item, n1) * ldp] = (TS)v;
+                out[(size_t)line_index<R1, R2, AX == AX_CENTRES>(item, n1) * ldp] = (TS)v;
             }
         }
     }
@@ -206,14 +237,17 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(128 / sizeof(TS)))) vo
 // result in FP32; 2 x += result / sigma; 4 x = xs + result / sigma; 2 and 4
 // also write the block's sums of (result / sigma)^2 and x^2 to red.  TIN:
 // stored type of the forward input, TS of the spectrum, T: arithmetic.
-template <typename TIN, typename TS, typename T, int R1, int R2, bool INV, bool WALL, int MODE, typename Set>
-__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_kernel(Set js, int nz, double *red, int red_stride,
+template <typename TIN, typename TS, typename T, int R1, int R2, bool INV, int AX, int MODE, typename Set>
+__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(AX, FFT_RW))) void fft_x_kernel(Set js, int nz, double *red, int red_stride,
                                                                                  const int *skip, const double *scale)
 {
     using namespace fft;
     typedef Shape<R1, R2> S;
-    constexpr int RW = FFT_RW, N = S::N, NT = S::threads(RW), LR = N + 1;
-    constexpr int EX = RW * S::RS, RL = RW * LR;
+    constexpr bool WALL = AX != AX_PERIODIC;   // the line goes through LDS on both sides
+    constexpr int RW = FFT_RW, N = S::N, NT = S::threads(AX, RW), LR = N + 1;
+    // LDS line of one row between the stages: odd strides against bank conflicts
+    constexpr int NA = S::items(AX), KS = NA | 1, RS = (S::K1 * KS) | 1;
+    constexpr int EX = RW * RS, RL = RW * LR;
     constexpr bool UPD = MODE == 2 || MODE == 4;
     typedef typename std::conditional<MODE == 1 || UPD, double, TS>::type Tout;
     __shared__ T sm[2 * EX > RL ? 2 * EX : RL];
@@ -230,11 +264,11 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
     const Cpx<T> *tw = static_cast<const Cpx<T> *>(jb.tw), *rot = static_cast<const Cpx<T> *>(jb.rot);
     if (tid < RW) prow[tid] = (int)phys_row(row0 + tid, trows, jb.skip);
     // stage A: row ra, point n2; stage B: row rb, index k1
-    const int ra = tid / R2, n2 = tid % R2;
+    const int ra = tid / NA, n2 = tid % NA;
     const int rb = tid % RW, k1b = tid / RW;
-    const bool actA = tid < R2 * RW, actB = k1b < S::K1;
+    const bool actA = tid < NA * RW, actB = k1b < S::K1;
 
-    if constexpr (!INV) {
+    if constexpr (!INV && AX != AX_FACES) {
         const TIN *in = static_cast<const TIN *>(jb.in);
         T x[R1];
         if constexpr (WALL) {
@@ -244,7 +278,7 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
             if (actA) {
 #pragma unroll
                 for (int n1 = 0; n1 < R1; ++n1) {
-                    const T v = sm[ra * LR + line_index<R1, R2, WALL>(n2, n1)];
+                    const T v = sm[ra * LR + line_index<R1, R2, AX == AX_CENTRES>(n2, n1)];
                     x[n1] = 2 * n1 >= R1 ? flip * v : v;
                 }
             }
@@ -260,7 +294,7 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
 #pragma unroll
             for (int k1 = 0; k1 < S::K1; ++k1) {
                 const Cpx<T> w = tw[k1 * R2 + n2];
-                const int o = ra * S::RS + k1 * S::KS + n2;
+                const int o = ra * RS + k1 * KS + n2;
                 sre[o] = w.x * yr[k1] - w.y * yi[k1];
                 sim[o] = w.x * yi[k1] + w.y * yr[k1];
             }
@@ -270,34 +304,69 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
         if (actB) {
 #pragma unroll
             for (int q = 0; q < R2; ++q) {
-                re[q] = sre[rb * S::RS + k1b * S::KS + q];
-                im[q] = sim[rb * S::RS + k1b * S::KS + q];
+                re[q] = sre[rb * RS + k1b * KS + q];
+                im[q] = sim[rb * RS + k1b * KS + q];
             }
         }
         __syncthreads();
         if (actB) {
             cdft<R2, -1, T>(re, im);
-            emit<R1, R2, WALL, T>(re, im, k1b, sine, rot, [&](int a, T v) { sm[rb * LR + a] = v; });
+            emit<R1, R2, AX == AX_CENTRES, T>(re, im, k1b, sine, rot, [&](int a, T v) { sm[rb * LR + a] = v; });
         }
         __syncthreads();
         rows_out<NT, RW, N, LR>(sm, prow, static_cast<TS *>(jb.out));
     } else {
-        const TS *in = static_cast<const TS *>(jb.in);
+        // the faces' forward transform is this one too, from TIN
+        typedef typename std::conditional<INV, TS, TIN>::type Tsrc;
+        const Tsrc *in = static_cast<const Tsrc *>(jb.in);
         Tout *out = static_cast<Tout *>(jb.out);
+        T x[R1];
         __syncthreads();
         rows_in<NT, RW, N, LR>(in, prow, sm);
         __syncthreads();
-        T re[R2], im[R2];
-        if (actB) gather<R1, R2, WALL, T>(re, im, k1b, sine, rot, [&](int a) { return sm[rb * LR + a]; });
-        __syncthreads();
-        if (actB) {
-            cdft<R2, 1, T>(re, im);
+        if constexpr (AX == AX_FACES) {
+            if (actA) {
 #pragma unroll
-            for (int q = 0; q < R2; ++q) {
-                const Cpx<T> w = tw[k1b * R2 + q];
-                const int o = rb * S::RS + k1b * S::KS + q;
-                sre[o] = w.x * re[q] - w.y * im[q];
-                sim[o] = w.x * im[q] + w.y * re[q];
+                for (int n1 = 0; n1 < R1; ++n1)
+                    x[n1] = face_value<R1, T>(sm[ra * LR + face_slot<R1, R2>(n2, n1)], n2, n1);
+            }
+            __syncthreads();
+            if (actA) {
+                T yr[S::K1], yi[S::K1];
+                rdft<R1, T>(x, yr, yi);
+#pragma unroll
+                for (int k1 = 0; k1 < S::K1; ++k1) {
+                    const Cpx<T> w = tw[k1 * NA + n2];
+                    const int o = ra * RS + k1 * KS + n2;
+                    sre[o] = w.x * yr[k1] - w.y * yi[k1];
+                    sim[o] = w.x * yi[k1] + w.y * yr[k1];
+                }
+            }
+            __syncthreads();
+            T re[NA], im[NA];
+            if (actB) {
+#pragma unroll
+                for (int q = 0; q < NA; ++q) {
+                    re[q] = sre[rb * RS + k1b * KS + q];
+                    im[q] = sim[rb * RS + k1b * KS + q];
+                }
+            }
+            __syncthreads();
+            if (actB) face_emit<R1, R2, T>(re, im, k1b, [&](int a, T v) { sm[rb * LR + a] = v; });
+        } else {
+            T re[R2], im[R2];
+            if (actB)
+                gather<R1, R2, AX == AX_CENTRES, T>(re, im, k1b, sine, rot, [&](int a) { return sm[rb * LR + a]; });
+            __syncthreads();
+            if (actB) {
+                cdft<R2, 1, T>(re, im);
+#pragma unroll
+                for (int q = 0; q < R2; ++q) {
+                    const Cpx<T> w = tw[k1b * R2 + q];
+                    const int o = rb * RS + k1b * KS + q;
+                    sre[o] = w.x * re[q] - w.y * im[q];
+                    sim[o] = w.x * im[q] + w.y * re[q];
+                }
             }
         }
         // the iterate's old values of this thread's points, in flight under
@@ -312,25 +381,28 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
                 for (int n1 = 0; n1 < R1; ++n1) old[n1] = xo[rowa + n2 + R2 * n1];
             }
         }
-        __syncthreads();
-        T x[R1];
-        if (actA) {
-            T yr[S::K1], yi[S::K1];
+        if constexpr (AX != AX_FACES) {
+            __syncthreads();
+            if (actA) {
+                T yr[S::K1], yi[S::K1];
 #pragma unroll
-            for (int k1 = 0; k1 < S::K1; ++k1) {
-                yr[k1] = sre[ra * S::RS + k1 * S::KS + n2];
-                yi[k1] = sim[ra * S::RS + k1 * S::KS + n2];
+                for (int k1 = 0; k1 < S::K1; ++k1) {
+                    yr[k1] = sre[ra * RS + k1 * KS + n2];
+                    yi[k1] = sim[ra * RS + k1 * KS + n2];
+                }
+                hdft<R1, T>(yr, yi, x);
             }
-            hdft<R1, T>(yr, yi, x);
         }
         double sd = 0.0, sx = 0.0;
         const double isg = UPD && scale ? 1.0 / scale[jb.slot] : 1.0;
         if constexpr (WALL) {
-            __syncthreads();
-            if (actA) {
+            if constexpr (AX == AX_CENTRES) {
+                __syncthreads();
+                if (actA) {
 #pragma unroll
-                for (int n1 = 0; n1 < R1; ++n1)
-                    sm[ra * LR + line_index<R1, R2, WALL>(n2, n1)] = 2 * n1 >= R1 ? flip * x[n1] : x[n1];
+                    for (int n1 = 0; n1 < R1; ++n1)
+                        sm[ra * LR + line_index<R1, R2, true>(n2, n1)] = 2 * n1 >= R1 ? flip * x[n1] : x[n1];
+                }
             }
             __syncthreads();
             if constexpr (UPD) {
@@ -409,21 +481,23 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(FFT_RW))) void fft_x_k
     }
 }
 
-// One launch over the jobs of a set.  walls: their axis has walls (the jobs
-// of one call agree); rows: transform rows per plane.  Sizes of the lists
+// One launch over the jobs of a set.  ax: form of their axis, the same for
+// all jobs (AX_*); rows: transform rows per plane.  Sizes of the lists
 // above only (fft_size()).
-hipError_t launch_fft_z64(const FftTable &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s);
-hipError_t launch_fft_x64(const FftTable &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s);
-hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, hipStream_t s);
-hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, const int *skip,
+hipError_t launch_fft_z64(const FftTable &js, int n, int rows, int nx, bool inverse, int ax, hipStream_t s);
+hipError_t launch_fft_x64(const FftTable &js, int n, int rows, int nz, bool inverse, int ax, hipStream_t s);
+hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, hipStream_t s);
+hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, const int *skip,
                           hipStream_t s);
-hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, bool walls, hipStream_t s);
+hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, int ax, hipStream_t s);
 // mode as fft_x_kernel's; in64: the forward input is FP64
-hipError_t launch_fft_x32_fwd(const FftSet &js, int n, int rows, int nz, bool walls, bool in64, const int *skip,
+hipError_t launch_fft_x32_fwd(const FftSet &js, int n, int rows, int nz, int ax, bool in64, const int *skip,
                               hipStream_t s);
 hipError_t launch_fft_x32_inv(const FftSet &js, int n, int rows, int nz, int mode, double *red, int red_stride,
                               const int *skip, const double *scale, hipStream_t s);
 hipError_t launch_fft_x32_wall(const FftSet &js, int n, int rows, int nz, int mode, double *red, int red_stride,
+                               const int *skip, const double *scale, hipStream_t s);
+hipError_t launch_fft_x32_face(const FftSet &js, int n, int rows, int nz, int mode, double *red, int red_stride,
                                const int *skip, const double *scale, hipStream_t s);
 
 }  // namespace ibs

@@ -3,23 +3,30 @@
 
 namespace ibs {
 
-template <int R1, int R2>
-static void go(const FftSet &js, int rows, int nx, bool inverse, bool walls, const int *skip, hipStream_t s)
+template <int R1, int R2, bool INV, int AX>
+static void one(const FftSet &js, int rows, int nx, const int *skip, hipStream_t s)
 {
     constexpr int CW = 128 / sizeof(float);
     typedef typename FftReal<R1 * R2>::type T;
-    const dim3 grid(rows * nx / CW, js.n), blk(fft::Shape<R1, R2>::threads(CW));
-    if (inverse && walls) fft_z_kernel<float, T, R1, R2, true, true><<<grid, blk, 0, s>>>(js, nx, skip);
-    else if (inverse) fft_z_kernel<float, T, R1, R2, true, false><<<grid, blk, 0, s>>>(js, nx, skip);
-    else if (walls) fft_z_kernel<float, T, R1, R2, false, true><<<grid, blk, 0, s>>>(js, nx, skip);
-    else fft_z_kernel<float, T, R1, R2, false, false><<<grid, blk, 0, s>>>(js, nx, skip);
+    const dim3 grid(rows * nx / CW, js.n), blk(fft::Shape<R1, R2>::threads(AX, CW));
+    fft_z_kernel<float, T, R1, R2, INV, AX><<<grid, blk, 0, s>>>(js, nx, skip);
 }
 
-hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, bool walls, const int *skip, hipStream_t s)
+template <int R1, int R2>
+static void go(const FftSet &js, int rows, int nx, bool inverse, int ax, const int *skip, hipStream_t s)
+{
+    if (ax == fft::AX_FACES) one<R1, R2, true, fft::AX_FACES>(js, rows, nx, skip, s);   // its own inverse
+    else if (inverse && ax) one<R1, R2, true, fft::AX_CENTRES>(js, rows, nx, skip, s);
+    else if (inverse) one<R1, R2, true, fft::AX_PERIODIC>(js, rows, nx, skip, s);
+    else if (ax) one<R1, R2, false, fft::AX_CENTRES>(js, rows, nx, skip, s);
+    else one<R1, R2, false, fft::AX_PERIODIC>(js, rows, nx, skip, s);
+}
+
+hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, const int *skip, hipStream_t s)
 {
     if (js.n == 0) return hipSuccess;
     switch (n) {
-#define IBS_CASE(N, R1, R2) case N: go<R1, R2>(js, rows, nx, inverse, walls, skip, s); break;
+#define IBS_CASE(N, R1, R2) case N: go<R1, R2>(js, rows, nx, inverse, ax, skip, s); break;
     IBS_FFT_SIZES_32(IBS_CASE)
 #undef IBS_CASE
     default: return hipErrorInvalidValue;

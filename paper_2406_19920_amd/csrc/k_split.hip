@@ -860,16 +860,13 @@ static __device__ double2 sum_pairs(const double *r, int n)
     return t;
 }
 
-struct CheckCounts {
-    int n[4];   // pairs written per job of the launch
-};
 __global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const double *__restrict__ red_last,
                                                            const double *__restrict__ red_prev,
-                                                           int stride, CheckCounts used, int pass, double tol,
+                                                           int count, int pass, double tol,
                                                            int *__restrict__ done)
 {
     const SplitJob &jb = ss.j[blockIdx.x];
-    const int job = jb.slot, count = used.n[blockIdx.x];
+    const int job = jb.slot;   // its pairs: count, jobs back to back
     if (pass == 0) {
         // one pass only: no correction was measured, so no error estimate
         // exists; the report says NOT_CONVERGED with unknown (NaN) error
@@ -886,7 +883,7 @@ __global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const do
         return;
     }
     if (pass >= 2 && done[job]) return;     // stopped earlier: report stands
-    const size_t off = (size_t)job * stride * 2;
+    const size_t off = (size_t)job * count * 2;
     const double2 last = sum_pairs(red_last + off, count);
     double rprev = 1.0;
     if (red_prev) {
@@ -1140,25 +1137,19 @@ hipError_t launch_residual_f32(const SplitSet &ss, const Plan &p, const State &s
 
 // Rows of the transform tiling are those of every component (ny; the v
 // component's first wall row is left out), so the update partials depend
-// only on the grid and the x kinds.
-size_t update_used(const Plan &p, int xk)
-{
-    if (p.fx[xk]) return (size_t)p.nz * p.ny / FFT_RW;   // one per block
-    const size_t rows = (size_t)8 * 16 * x_wm(x_nbt(p.nx));
-    return ((size_t)p.nz * p.ny + rows - 1) / rows * UPD_WAVES;
-}
+// only on the grid.
 size_t update_slots(const Plan &p)
 {
-    return std::max(update_used(p, XK_P), std::max(update_used(p, XK_C), update_used(p, XK_F)));
+    if (p.fx) return (size_t)p.nz * p.ny / FFT_RW;   // one per block
+    const size_t rows = (size_t)8 * 16 * x_wm(x_nbt(p.nx));
+    return ((size_t)p.nz * p.ny + rows - 1) / rows * UPD_WAVES;
 }
 
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s)
 {
-    CheckCounts used{};
-    for (int q = 0; q < ss.n; ++q) used.n[q] = (int)update_used(p, ss.j[q].xk);
     const double *last = pass >= 1 ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
     const double *prev = pass >= 2 ? st.red + (size_t)(pass - 2) * st.upd_region : nullptr;
-    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, last, prev, (int)update_slots(p), used,
+    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, last, prev, (int)update_slots(p),
                        pass, p.desc.tol, st.done);
     return hipGetLastError();
 }

@@ -436,7 +436,7 @@ struct AxisTables {
     std::vector<double> f64[4];        // folded: fwd_c, fwd_s, inv_c, inv_s; plain: fwd, inv
     std::vector<uint16_t> split[2];    // fwd, inv (folded pairs or plain); empty without split
     std::vector<double> fft[4];        // fast transform instead of all of these: twiddle factors fwd, inv;
-                                       // walls: pair rotations fwd, inv
+                                       // walls: pair rotations fwd, inv; faces: one table of factors
     size_t bytes() const
     {
         size_t b = (Q.size() + Qi.size() + lam.size()) * sizeof(double);
@@ -451,11 +451,19 @@ struct AxisTables {
 // k1 n2 / n} ([k1 <= R1/2][n2], s = sqrt(2/n) forward, half of it inverse)
 // and, with walls, the rotations e^{-+ i pi k / 2n}, k <= n/2 (k = 0 carries
 // the constant mode's normalisation).  Angles reduced exactly, long double.
-static void fft_tables(int n, bool walls, std::vector<double> (&out)[4])
+// Face-normal sine basis: the factors of the doubled line, n2 <= R2, alone.
+static void fft_tables(int n, bool walls, bool faces, std::vector<double> (&out)[4])
 {
     int r1 = 0, r2 = 0;
     fft_radices(n, r1, r2);
     const long double pi = 3.141592653589793238462643383279502884L, s = std::sqrt(2.0L / n), r = std::sqrt(2.0L);
+    for (int k1 = 0; faces && k1 <= r1 / 2; ++k1)
+        for (int n2 = 0; n2 <= r2; ++n2) {
+            const long double th = pi * (long double)((k1 * n2) % (2 * n)) / n;
+            out[0].push_back((double)(0.5L * s * std::cos(th)));
+            out[0].push_back((double)(-0.5L * s * std::sin(th)));
+        }
+    if (faces) return;
     for (int k1 = 0; k1 <= r1 / 2; ++k1)
         for (int n2 = 0; n2 < r2; ++n2) {
             const long double th = 2.0L * pi * (long double)((k1 * n2) % n) / n;
@@ -485,8 +493,8 @@ static std::shared_ptr<const AxisTables> build_axis(int n, double h, bool z_axis
     if (basis < 0) fourier_basis(n, h, t->Q, t->lam);
     else if (faces.empty()) wall_basis(n, h, basis, t->Q, t->lam);
     else if (!stretched_basis(n, faces, basis, t->Q, t->Qi, t->lam)) return nullptr;
-    if (fft_axis(n, basis, !faces.empty())) {
-        fft_tables(n, basis >= 0, t->fft);
+    if (fft_axis(n, !faces.empty())) {
+        fft_tables(n, basis >= 0, basis == XK_F, t->fft);
         return t;
     }
     const std::vector<double> &Q = t->Q;
@@ -847,10 +855,8 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     }
     const int nxk = p->wx ? NUM_XK : 1;   // distinct x tables
     const int nzk = p->wz ? NUM_XK : 1;   // distinct z tables
-    for (int k = 0; k < NUM_XK; ++k) {
-        p->fx[k] = !ax[k]->fft[0].empty();
-        p->fz[k] = !az[k]->fft[0].empty();
-    }
+    p->fx = !ax[0]->fft[0].empty();
+    p->fz = !az[0]->fft[0].empty();
 
     // blob layout
     BlobLayout &L = p->lay;
@@ -859,12 +865,12 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     const bool fold_x = x_folds(*p), fold_z = z_folds(*p);
     const size_t hx2 = size_t(nx / 2) * (nx / 2), hz2 = size_t(nz / 2) * (nz / 2);
     for (int k = 0; k < NUM_XK; ++k) {
-        const size_t dense = !fold_x && !p->fx[k] ? sizeof(double) * nx * nx : 0;
+        const size_t dense = !fold_x && !p->fx ? sizeof(double) * nx * nx : 0;
         L.bx_fwd[k] = k < nxk ? take(dense) : L.bx_fwd[0];
         L.bx_inv[k] = k < nxk ? take(dense) : L.bx_inv[0];
     }
     for (int k = 0; k < NUM_XK; ++k) {
-        const size_t dense = !fold_z && !p->fz[k] ? sizeof(double) * nz * nz : 0;
+        const size_t dense = !fold_z && !p->fz ? sizeof(double) * nz * nz : 0;
         L.az_fwd[k] = k < nzk ? take(dense) : L.az_fwd[0];
         L.az_inv[k] = k < nzk ? take(dense) : L.az_inv[0];
     }
@@ -876,11 +882,19 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.fz_fwd_s = take(fold_z ? sizeof(double) * hz2 : 0);
     L.fz_inv_c = take(fold_z ? sizeof(double) * hz2 : 0);
     L.fz_inv_s = take(fold_z ? sizeof(double) * hz2 : 0);
-    // fast transforms: one table set per axis (the wall kinds share it)
-    const bool f32[2] = {split && nx > FFT_F64_ARITH_MAX, split && nz > FFT_F64_ARITH_MAX};   // arithmetic of x, z
-    size_t *const fat[2][4] = {{&L.ftx_fwd, &L.ftx_inv, &L.frx_fwd, &L.frx_inv},
-                               {&L.ftz_fwd, &L.ftz_inv, &L.frz_fwd, &L.frz_inv}};
-    for (int i = 0; i < 8; ++i) *fat[i / 4][i % 4] = take((f32[i / 4] ? sizeof(float) : sizeof(double)) * (i < 4 ? ax : az)[0]->fft[i % 4].size());
+    // fast transforms: one table set per axis (the wall kinds on cell centres
+    // share it) and the faces' table; in FP32 where the arithmetic is
+    struct FastTable { size_t *at; const std::vector<double> *t; bool f32; };
+    const bool f32x = split && nx > FFT_F64_ARITH_MAX, f32z = split && nz > FFT_F64_ARITH_MAX;
+    const std::vector<double> none;
+    const FastTable fast[] = {
+        {&L.ftx_fwd, &ax[0]->fft[0], f32x}, {&L.ftx_inv, &ax[0]->fft[1], f32x},
+        {&L.frx_fwd, &ax[0]->fft[2], f32x}, {&L.frx_inv, &ax[0]->fft[3], f32x},
+        {&L.ftz_fwd, &az[0]->fft[0], f32z}, {&L.ftz_inv, &az[0]->fft[1], f32z},
+        {&L.frz_fwd, &az[0]->fft[2], f32z}, {&L.frz_inv, &az[0]->fft[3], f32z},
+        {&L.ftx_face, p->wx ? &ax[XK_F]->fft[0] : &none, f32x},
+        {&L.ftz_face, p->wz ? &az[XK_F]->fft[0] : &none, f32z}};
+    for (const FastTable &f : fast) *f.at = take((f.f32 ? sizeof(float) : sizeof(double)) * f.t->size());
     for (int k = 0; k < NUM_XK; ++k) L.lam_x[k] = k < nxk ? take(sizeof(double) * nx) : L.lam_x[0];
     for (int k = 0; k < NUM_XK; ++k) L.lam_z[k] = k < nzk ? take(sizeof(double) * nz) : L.lam_z[0];
     for (int kd = 0; kd < NUM_KINDS; ++kd) {
@@ -893,12 +907,12 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.dyf = take(sizeof(double) * (ny + 1));
     const bool sfold_z = split && z_folds_split(*p);
     for (int k = 0; k < NUM_XK; ++k) {
-        const size_t dense = split && !p->fx[k] ? sizeof(uint16_t) * 3 * nx * nx : 0;
+        const size_t dense = split && !p->fx ? sizeof(uint16_t) * 3 * nx * nx : 0;
         L.sx_fwd[k] = k < nxk ? take(dense) : L.sx_fwd[0];
         L.sx_inv[k] = k < nxk ? take(dense) : L.sx_inv[0];
     }
     for (int k = 0; k < NUM_XK; ++k) {
-        const size_t dense = split && !sfold_z && !p->fz[k] ? sizeof(uint16_t) * 3 * nz * nz : 0;
+        const size_t dense = split && !sfold_z && !p->fz ? sizeof(uint16_t) * 3 * nz * nz : 0;
         L.sz_fwd[k] = k < nzk ? take(dense) : L.sz_fwd[0];
         L.sz_inv[k] = k < nzk ? take(dense) : L.sz_inv[0];
     }
@@ -977,14 +991,13 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
             }
         }
     }
-    for (int i = 0; i < 8; ++i) {
-        const std::vector<double> &t = (i < 4 ? ax : az)[0]->fft[i % 4];
-        if (!f32[i / 4]) {
-            put(*fat[i / 4][i % 4], t.data(), t.size());
+    for (const FastTable &f : fast) {
+        if (!f.f32) {
+            put(*f.at, f.t->data(), f.t->size());
             continue;
         }
-        float *to = reinterpret_cast<float *>(p->blob.data() + *fat[i / 4][i % 4]);
-        for (size_t q = 0; q < t.size(); ++q) to[q] = (float)t[q];
+        float *to = reinterpret_cast<float *>(p->blob.data() + *f.at);
+        for (size_t q = 0; q < f.t->size(); ++q) to[q] = (float)(*f.t)[q];
     }
     if (!lane_mask.empty()) std::memcpy(p->blob.data() + L.lane_mask, lane_mask.data(), 4 * lane_mask.size());
     if (!lane_list.empty()) std::memcpy(p->blob.data() + L.lane_list, lane_list.data(), 4 * lane_list.size());

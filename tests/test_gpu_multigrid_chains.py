@@ -1,6 +1,7 @@
 """Multi-grid batches whose fields run as chains of the fast kernels (groups of
 8 MB and more): against the single-grid solves, which run the same arithmetic,
-with walls (the face-normal component takes the stage kernels), and the batch
+with walls (the face-normal components in chains of their own, or too few for
+one and so in the stage kernels), and the batch
 whose fields overlap, which keeps the order every right-hand side before any
 solution."""
 import pytest
@@ -24,7 +25,8 @@ def _randn(shape, seed):
 
 # 17 rows: the fewest a chain takes; 96x64x64: several fields of a chain; the
 # last one beside a group of its own size class too small for a chain
-@pytest.mark.parametrize("shape,walls,count", [((256, 17, 112), False, 1), ((96, 64, 64), True, 2), ((64, 33, 48), False, 3)])
+@pytest.mark.parametrize("shape,walls,count", [((256, 17, 112), False, 1), ((96, 64, 64), True, 2),
+                                                ((96, 64, 64), True, 3), ((64, 33, 48), False, 3)])
 def test_chains_match_single_solves(ibs, shape, walls, count):
     nx, ny, nz = shape
     print("case chains", shape, walls, count, flush=True)
