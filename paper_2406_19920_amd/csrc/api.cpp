@@ -189,11 +189,25 @@ template <typename Set> static double transform_flops(const Plan &p, const Set &
     return f;
 }
 
+// Whether a job's solution overlaps a right-hand side other than by being its
+// own one: then no solution may be written before all of them are read.
+static bool solutions_overlap(const Plan &p, const JobSet &js, double *const *X)
+{
+    auto bytes = [&](int q) { return (size_t)p.nz * js.j[q].rows * p.nx * sizeof(double); };
+    for (int q = 0; q < js.n; ++q)
+        for (int r = 0; r < js.n; ++r) {
+            const uintptr_t x = reinterpret_cast<uintptr_t>(X[q]), b = reinterpret_cast<uintptr_t>(js.j[r].in);
+            if (x < b + bytes(r) && b < x + bytes(q) && !(q == r && x == b)) return true;
+        }
+    return false;
+}
+
 // The five FP64 stages.  js.j[q].in holds the right-hand side; W[q] is the
 // job's scratch field and X[q] its output.  Where the x and z transforms are
 // both fast ones the jobs work in place on X (the stages after the first touch
 // one field, which for fields up to the 256 MB Infinity Cache then stays
-// there); the dense products need a second field and alternate X and W.
+// there), or on W if a solution overlaps another right-hand side; the dense
+// products need a second field and alternate X and W.
 static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, double *const *X,
                                           const State &st, bool poisson, hipStream_t s)
 {
@@ -209,10 +223,11 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, 
     }
     const bool in_place = p.fx && p.fz;
     // in, out of every job for a stage; b: the right-hand side
-    enum Buf { RHS, PING, PONG };   // PING: X; PONG: W, or X in place
+    enum Buf { RHS, PING, PONG, SOL };   // dense: PING is X, PONG W
+    const bool on_w = in_place && solutions_overlap(p, js, X);
     auto bind = [&](Buf in, Buf out) {
         for (int q = 0; q < js.n; ++q) {
-            auto at = [&](Buf f) { return f == PONG && !in_place ? W[q] : X[q]; };
+            auto at = [&](Buf f) { return f == SOL ? X[q] : (in_place ? on_w : f == PONG) ? W[q] : X[q]; };
             if (in != RHS) js.j[q].in = at(in);
             js.j[q].out = at(out);
         }
@@ -240,7 +255,7 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, 
     bind(PING, PONG);
     e = timed(p, PK_ZGEMM, zflop, rw, s, [&] { return zform(true); });
     if (e != hipSuccess) return hip_fail(e, "z inverse");
-    bind(PONG, PING);
+    bind(PONG, SOL);
     e = timed(p, PK_XGEMM, xflop, rw, s, [&] { return xform(true); });
     if (e != hipSuccess) return hip_fail(e, "x inverse");
     return IBS_OK;
@@ -479,9 +494,7 @@ ibs_status solve_poisson(ibs_plan plan, const double *b, double *phi, void *work
     js.j[0].kind = KIND_P;
     js.j[0].c = 0.0;
     js.j[0].info = info;
-    // x forward: b -> W; z forward: W -> phi; pencils in place on phi;
-    // z inverse: phi -> W; x inverse: W -> phi
-    js.j[0].in = b; js.j[0].out = W;
+    js.j[0].in = b;
     r = run_fp64_pipeline(p, js, W, phi, st, true, s);
     return r != IBS_OK ? r : compat_end(p, info, st, s);
 }
@@ -537,7 +550,7 @@ ibs_status solve_helmholtz_batch(ibs_plan plan, int32_t ncomp, const int32_t *co
         if (v != IBS_OK) return v;
         return run_refined(p, ss, W1, W2, W3, st, false, default_passes(p, false), s);
     }
-    for (int q = 0; q < ncomp; ++q) { js.j[q].in = r[q]; js.j[q].out = W + q * stride; }
+    for (int q = 0; q < ncomp; ++q) js.j[q].in = r[q];
     double *Ws[4], *Xs[4];
     for (int q = 0; q < ncomp; ++q) { Ws[q] = W + q * stride; Xs[q] = x[q]; }
     return run_fp64_pipeline_multi(p, js, Ws, Xs, st, false, s);

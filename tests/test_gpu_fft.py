@@ -50,3 +50,24 @@ def test_every_length(ibs, n, refined, walls):
         for comp in range(3):
             err = float((got[comp] - xs[comp]).norm() / xs[comp].norm())
             assert err < TOL[refined], (nx, nz, comp, err)
+
+
+def test_solutions_over_other_right_hand_sides(ibs):
+    """FP64 jobs work in place on their solutions: solutions that lie on another
+    component's right-hand side, or one plane into their own, end bitwise as
+    apart."""
+    print("case fft overlap", flush=True)
+    n = 64
+    S = ibs.Solver(n, n, n, beta=0.5)
+    c = [0.125 / n ** 2] * 3
+    flat = [torch.randn((n + 1) * n * n, generator=torch.Generator(device="cuda").manual_seed(q),
+                        dtype=torch.float64, device="cuda") for q in range(3)]
+    u, w = flat[0][:n ** 3].view(n, n, n), flat[1][:n ** 3].view(n, n, n)
+    want = S.helmholtz([0, 2], c[:2], [u.clone(), w.clone()])
+    S.helmholtz([0, 2], c[:2], [u, w], [w, u])
+    assert torch.equal(w, want[0]) and torch.equal(u, want[1])
+    b = flat[2][n * n:].view(n, n, n)
+    phi = flat[2][:n ** 3].view(n, n, n)
+    want = S.poisson(b.clone())
+    S.poisson(b, phi)
+    assert torch.equal(phi, want)
