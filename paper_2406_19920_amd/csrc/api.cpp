@@ -202,14 +202,20 @@ static bool solutions_overlap(const Plan &p, const JobSet &js, double *const *X)
     return false;
 }
 
+// Jobs [first, first + n) of a set.
+template <typename Set> static Set jobs_from(const Set &all, int first, int n)
+{
+    Set s{};
+    for (int q = first; q < first + n; ++q) s.j[s.n++] = all.j[q];
+    return s;
+}
+
 // The five FP64 stages.  js.j[q].in holds the right-hand side; W[q] is the
 // job's scratch field and X[q] its output.  Where the x and z transforms are
-// both fast ones the jobs work in place on X (the stages after the first touch
-// one field, which for fields up to the 256 MB Infinity Cache then stays
-// there), or on W if a solution overlaps another right-hand side; the dense
-// products need a second field and alternate X and W.
-static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, double *const *X,
-                                          const State &st, bool poisson, hipStream_t s)
+// both fast ones the jobs work in place (in_place) on X, or on W (on_w); the
+// dense products need a second field and alternate X and W.
+static ibs_status run_fp64_stages(Plan &p, JobSet js, double *const *W, double *const *X, bool in_place, bool on_w,
+                                  const State &st, bool poisson, hipStream_t s)
 {
     hipError_t e;
     const double cells = total_cells(js, p);
@@ -221,10 +227,8 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, 
         za[0][k] = blob_ptr(p, p.lay.az_fwd[k]);
         za[1][k] = blob_ptr(p, p.lay.az_inv[k]);
     }
-    const bool in_place = p.fx && p.fz;
     // in, out of every job for a stage; b: the right-hand side
     enum Buf { RHS, PING, PONG, SOL };   // dense: PING is X, PONG W
-    const bool on_w = in_place && solutions_overlap(p, js, X);
     auto bind = [&](Buf in, Buf out) {
         for (int q = 0; q < js.n; ++q) {
             auto at = [&](Buf f) { return f == SOL ? X[q] : (in_place ? on_w : f == PONG) ? W[q] : X[q]; };
@@ -258,6 +262,31 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, JobSet js, double *const *W, 
     bind(PONG, SOL);
     e = timed(p, PK_XGEMM, xflop, rw, s, [&] { return xform(true); });
     if (e != hipSuccess) return hip_fail(e, "x inverse");
+    return IBS_OK;
+}
+
+// Solves js stage by stage.  In place, components go one group after the
+// other, each as many as stay in the 256 MB Infinity Cache from one stage to
+// the next: a 256^3 step's three velocity solves took 827 us as one group
+// (z and y stages 4.1-4.6 TB/s) and take 720 us one by one.  Small groups end
+// in more half-empty launches (192^3, 57 MB each: 519 us as one group of
+// three, 530 as 2 + 1), so a group is filled up to 208 MB.  Larger fields run
+// one by one as well, which costs and gains nothing (512x384x384: 6.36 ms
+// both ways; in slabs of rows that fit the cache, x and z alternating, 6.55).
+static ibs_status run_fp64_pipeline_multi(Plan &p, const JobSet &js, double *const *W, double *const *X,
+                                          const State &st, bool poisson, hipStream_t s)
+{
+    constexpr size_t GROUP_BYTES = (size_t)208 << 20;
+    if (!(p.fx && p.fz)) return run_fp64_stages(p, js, W, X, false, false, st, poisson, s);
+    const bool on_w = solutions_overlap(p, js, X);
+    const size_t bytes = (size_t)p.nz * p.ny * p.nx * sizeof(double);
+    // a solution on another right-hand side: every one of those first
+    const int per = on_w ? js.n : (int)std::min<size_t>(js.n, std::max<size_t>(1, GROUP_BYTES / bytes));
+    for (int q = 0; q < js.n; q += per) {
+        const int n = std::min(per, js.n - q);
+        const ibs_status r = run_fp64_stages(p, jobs_from(js, q, n), W + q, X + q, true, on_w, st, poisson, s);
+        if (r != IBS_OK) return r;
+    }
     return IBS_OK;
 }
 

@@ -71,3 +71,17 @@ def test_solutions_over_other_right_hand_sides(ibs):
     want = S.poisson(b.clone())
     S.poisson(b, phi)
     assert torch.equal(phi, want)
+
+
+# 104 MB is half a group: two components and one, and one by one
+@pytest.mark.parametrize("ny", [192, 212])
+def test_component_groups(ibs, ny):
+    print("case fft groups", ny, flush=True)
+    S = ibs.Solver(256, ny, 256, beta=0.5)
+    c = [1e-6, 2e-6, 3e-6]
+    rs = [torch.randn(S.shape(op), generator=torch.Generator(device="cuda").manual_seed(op),
+                      dtype=torch.float64, device="cuda") for op in (1, 2, 3)]
+    got = S.helmholtz([0, 1, 2], c, rs)
+    for q in range(3):
+        assert torch.equal(got[q], S.helmholtz([q], c[q:q + 1], rs[q:q + 1])[0])
+        assert S.read_info(0).status == 0
