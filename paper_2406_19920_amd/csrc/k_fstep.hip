@@ -7,7 +7,7 @@
 // together with the Helmholtz right-hand side without the forcing,
 //   r = u^e - c L u,  c = beta dt / Re                             (eq. e)
 // and N(u) itself (kept for the next stage's zeta term); u^e is written only
-// when markers will interpolate it.  N is the
+// where markers interpolate it as a field (ibm_from_rhs()).  N is the
 // convective term in divergence form, each product formed on the face or
 // edge where its derivative needs it from arithmetic means of the
 // neighbouring values; with walls, v = 0 on the wall faces and no product
@@ -16,14 +16,17 @@
 // 0..ny with walls: the wall faces get zeros); neighbours from an LDS ring
 // of three planes.
 //
-// ibm_kernel (L1): one thread per marker: for each component, the 3 x 3 x 3
-// support of the Roma three-point kernel on that component's grid,
-// U^e(X) = sum u^e(x) w (eq. b), F = (U^d - U^e)/dt (eq. c), and
+// ibm_kernel (L1): 32 lanes per marker and component, 27 of them one point of
+// the 3 x 3 x 3 support of the Roma three-point kernel on that component's
+// grid: U^e(X) = sum u^e(x) w (eq. b), F = (U^d - U^e)/dt (eq. c), and
 // r += dt F w dV / (hx hy hz) at each support point (eq. d, the spreading
 // added straight into the Helmholtz right-hand side) by atomic adds, as
 // the paper's L1 does.  Needs a uniform spacing in y (as the paper's grid).
+// u^e = r + c L u is formed at the support points alone, from the right-hand
+// side and u, in a launch of its own before any marker adds to r.
 #include "ibs_internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace ibs {
@@ -257,60 +260,83 @@ static __device__ __forceinline__ double roma3(double r)
     return 0.0;
 }
 
-__global__ __launch_bounds__(64) void ibm_kernel(FsGeo g, double dt, int nm, const double *__restrict__ X,
-                                                 const double *__restrict__ ud,
-                                                 const double *__restrict__ dvol,
-                                                 const double *__restrict__ ue,
-                                                 const double *__restrict__ ve,
-                                                 const double *__restrict__ we, double *ru, double *rv,
-                                                 double *rw, double *force)
+// L u of a component at point (i, j, k) of its grid, as explicit_kernel forms
+// it (v's wall faces read as zero).
+static __device__ __forceinline__ double lap_at(const FsGeo &g, int comp, const double *__restrict__ f, int rows,
+                                                int i, int j, int k)
 {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= nm) return;
+    const int ie = i + 1 < g.nx ? i + 1 : 0, iw = i > 0 ? i - 1 : g.nx - 1;
+    const int kt = k + 1 < g.nz ? k + 1 : 0, kb = k > 0 ? k - 1 : g.nz - 1;
+    const int jn = g.py ? (j + 1 < g.ny ? j + 1 : 0) : j + 1, js = g.py ? (j > 0 ? j - 1 : g.ny - 1) : j - 1;
+    auto F = [&](int kk, int jj, int ii) { return f[((size_t)kk * rows + jj) * g.nx + ii]; };
+    const double ihx = 1.0 / g.hx, ihz = 1.0 / g.hz, fc = F(k, j, i);
+    const double xz = (F(k, j, ie) - 2.0 * fc + F(k, j, iw)) * ihx * ihx +
+                      (F(kt, j, i) - 2.0 * fc + F(kb, j, i)) * ihz * ihz;
+    if (comp == 1) {
+        const double fn = !g.py && jn == g.ny ? 0.0 : F(k, jn, i), fs = !g.py && js == 0 ? 0.0 : F(k, js, i);
+        const int jm = j > 0 ? j - 1 : g.ny - 1;
+        return xz + ((fn - fc) * (1.0 / g.dyc[j]) - (fc - fs) * (1.0 / g.dyc[jm])) * (1.0 / g.dyf[j]);
+    }
+    const double iD = 1.0 / g.dyc[j];
+    const double fu = g.py || j + 1 < g.ny ? (F(k, jn, i) - fc) * (1.0 / g.dyf[j + 1]) : -fc * (2.0 * iD);
+    const double fl = g.py || j > 0 ? (fc - F(k, js, i)) * (1.0 / g.dyf[j]) : fc * (2.0 * iD);
+    return xz + (fu - fl) * iD;
+}
+
+// The lanes of a marker share the three axes' divisions and weights; the two
+// launches take 31 + 31 us for 18 529 markers in 256^3 (one thread per marker
+// reading u^e fields: 76 us, and 400 MB more for the explicit kernel to store,
+// 482 us instead of 427), bound by scattered accesses: order over the XCDs or
+// fewer instructions no longer change it.
+// STEP 0: F of every marker (to F[3 m + comp]) from u^e = r + c L u; 1: the
+// spreading of F into r; 2: both at once, u^e a field of its own.
+struct IbmFields {
+    const double *u[3], *ue[3];
+    double *r[3];
+    double c;
+};
+constexpr int IBM_LANES = 32;
+template <int STEP>
+__global__ __launch_bounds__(256) void ibm_kernel(FsGeo g, double dt, int nm, const double *__restrict__ X,
+                                                  const double *__restrict__ ud,
+                                                  const double *__restrict__ dvol, IbmFields fd, double *F_)
+{
     const double vol = g.hx * g.hy * g.hz;
-    const double scale = dt * dvol[m] / vol;
-    for (int comp = 0; comp < 3; ++comp) {
-        // staggered offsets (x, y, z) of the component, in grid units
-        const double ox = comp == 0 ? 0.0 : 0.5, oy = comp == 1 ? 0.0 : 0.5, oz = comp == 2 ? 0.0 : 0.5;
-        const double px = X[3 * m] / g.hx - ox, py = X[3 * m + 1] / g.hy - oy, pz = X[3 * m + 2] / g.hz - oz;
-        const int bx = (int)floor(px + 0.5) - 1, by = (int)floor(py + 0.5) - 1, bz = (int)floor(pz + 0.5) - 1;
+    const int lane = threadIdx.x % IBM_LANES;
+    const int a = lane / 9, b = lane / 3 % 3, c = lane % 3;
+    const int comp = blockIdx.y;
+    const long groups = (long)gridDim.x * (256 / IBM_LANES);
+    for (long m = (long)blockIdx.x * (256 / IBM_LANES) + threadIdx.x / IBM_LANES; m < nm; m += groups) {
         const int rows = comp == 1 ? vrows(g) : g.ny;
-        const double *f = comp == 0 ? ue : (comp == 1 ? ve : we);
-        double *r = comp == 0 ? ru : (comp == 1 ? rv : rw);
-        double wx[3], wy[3], wz[3];
-        int ix[3], iy[3], iz[3];
-        bool oky[3];
-        for (int t = 0; t < 3; ++t) {
-            wx[t] = roma3(bx + t - px);
-            wy[t] = roma3(by + t - py);
-            wz[t] = roma3(bz + t - pz);
-            ix[t] = ((bx + t) % g.nx + g.nx) % g.nx;
-            iz[t] = ((bz + t) % g.nz + g.nz) % g.nz;
-            int jy = by + t;
-            if (g.py) {
-                jy = (jy % g.ny + g.ny) % g.ny;
-                oky[t] = true;
-            } else {
-                oky[t] = jy >= 0 && jy < rows;
+        // one axis's weight and index per lane, lanes 0-8 the x, y, z ones;
+        // grid units, staggered by half a cell except along the component
+        const int ax = lane / 3 % 3;
+        const double at = X[3 * m + ax] / (ax == 0 ? g.hx : (ax == 1 ? g.hy : g.hz)) - (ax == comp ? 0.0 : 0.5);
+        const int first = (int)floor(at + 0.5) - 1, pt = first + lane % 3;
+        const int n = ax == 0 ? g.nx : (ax == 1 ? g.ny : g.nz);
+        const double wt = roma3(pt - at);
+        const int it = ax == 1 && !g.py ? pt : (pt % n + n) % n;
+        const double w = __shfl(wt, 6 + a, IBM_LANES) * __shfl(wt, 3 + b, IBM_LANES) * __shfl(wt, c, IBM_LANES);
+        const int ix = __shfl(it, c, IBM_LANES), iy = __shfl(it, 3 + b, IBM_LANES), iz = __shfl(it, 6 + a, IBM_LANES);
+        const bool on = lane < 27 && iy >= 0 && iy < rows;
+        const size_t o = ((size_t)iz * rows + iy) * g.nx + ix;
+        double F;
+        if constexpr (STEP == 1) {
+            F = F_[3 * m + comp];
+        } else {
+            double U = 0.0;
+            if constexpr (STEP == 2) {
+                if (on) U = fd.ue[comp][o] * w;
+            } else if (on && (comp != 1 || g.py || (iy > 0 && iy < g.ny))) {   // u^e = 0 on v's wall faces
+                U = (fd.r[comp][o] + fd.c * lap_at(g, comp, fd.u[comp], rows, ix, iy, iz)) * w;
             }
-            iy[t] = jy;
+#pragma unroll
+            for (int d = IBM_LANES / 2; d >= 1; d >>= 1) U += __shfl_xor(U, d, IBM_LANES);
+            F = (ud[3 * m + comp] - U) / dt;
+            if (F_ && lane == 0) F_[3 * m + comp] = F;
         }
-        double U = 0.0;
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) {
-                if (!oky[b]) continue;
-                for (int c = 0; c < 3; ++c)
-                    U += f[((size_t)iz[a] * rows + iy[b]) * g.nx + ix[c]] * wz[a] * wy[b] * wx[c];
-            }
-        const double F = (ud[3 * m + comp] - U) / dt;
-        if (force) force[3 * m + comp] = F;
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) {
-                if (!oky[b]) continue;
-                for (int c = 0; c < 3; ++c)
-                    atomicAdd(&r[((size_t)iz[a] * rows + iy[b]) * g.nx + ix[c]],
-                              F * wz[a] * wy[b] * wx[c] * scale);
-            }
+        if constexpr (STEP != 0)
+            if (on) atomicAdd(&fd.r[comp][o], F * w * (dt * dvol[m] / vol));
     }
 }
 
@@ -322,6 +348,18 @@ static FsGeo fs_geo(const Plan &p)
     g.dyc = blob_ptr(p, p.lay.dyc);
     g.dyf = blob_ptr(p, p.lay.dyf);
     return g;
+}
+
+// Whether u^e at the markers comes from r + c L u instead of a field: that
+// saves the explicit kernel a quarter of its stores.  r and c L u cancel to
+// u^e, which costs it up to c |L| roundings of |u|: only up to 16 of them (a
+// step at an advective Courant number has 0.01 to 1), and only with room for
+// F between the two launches (force, or u^e's unused fields).
+bool ibm_from_rhs(const Plan &p, const FsStage &s)
+{
+    const double hy = p.desc.ly / p.ny, c = std::fabs(s.beta * s.dt / s.re);
+    return c * 4.0 * (1.0 / (p.hx * p.hx) + 1.0 / (hy * hy) + 1.0 / (p.hz * p.hz)) <= 16.0 &&
+           (s.force || s.nmarkers <= s.ve - s.ue);
 }
 
 hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st)
@@ -338,16 +376,27 @@ hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st)
     const int ntile = ((p.nx + ETX - 1) / ETX) * ((vr + ETY - 1) / ETY) * (p.nz / EKZ);
     dim3 grid(8 * ((ntile + 7) / 8));   // a whole number of blocks per XCD
     hipLaunchKernelGGL(explicit_kernel, grid, dim3(ENT), 0, st, g, cf, s.u, s.v, s.w, s.p, s.nu, s.nv, s.nw,
-                       s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.nu, s.nv, s.nw, s.nmarkers > 0 ? 1 : 0);
+                       s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.nu, s.nv, s.nw, s.nmarkers > 0 && !ibm_from_rhs(p, s) ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_ibm(const Plan &p, const FsStage &s, hipStream_t st)
 {
     if (s.nmarkers <= 0) return hipSuccess;
-    FsGeo g = fs_geo(p);
-    hipLaunchKernelGGL(ibm_kernel, dim3((s.nmarkers + 63) / 64), dim3(64), 0, st, g, s.dt, s.nmarkers,
-                       s.markers, s.ud, s.dvol, s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.force);
+    const FsGeo g = fs_geo(p);
+    const IbmFields f{{s.u, s.v, s.w}, {s.ue, s.ve, s.we}, {s.ru, s.rv, s.rw}, s.beta * s.dt / s.re};
+    constexpr int PER = 256 / IBM_LANES, MOST = 1 << 20;   // groups of lanes per block, blocks
+    const dim3 grid(std::min(MOST, s.nmarkers / PER + (s.nmarkers % PER != 0)), 3), blk(256);
+    auto go = [&](auto kernel, double *F) {
+        hipLaunchKernelGGL(kernel, grid, blk, 0, st, g, s.dt, s.nmarkers, s.markers, s.ud, s.dvol, f, F);
+    };
+    if (ibm_from_rhs(p, s)) {
+        double *F = s.force ? s.force : s.ue;
+        go(ibm_kernel<0>, F);
+        go(ibm_kernel<1>, F);
+    } else {
+        go(ibm_kernel<2>, s.force);
+    }
     return hipGetLastError();
 }
 
