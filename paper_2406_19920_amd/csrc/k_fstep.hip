@@ -51,7 +51,13 @@ static __device__ __forceinline__ int vrows(const FsGeo &g) { return g.py ? g.ny
 // one-point halo in x and y, so each plane of each field is read from HBM
 // once per block (plus the halo, which the neighbouring tiles on the same
 // XCD share in L2) instead of once per neighbour; the loads of plane k+2
-// are in flight while plane k is computed.  (A four-slot ring with one
+// are in flight while plane k is computed.  Bound by HBM in 10 to 13 streams:
+// 1.34 GB of a 256^3 stage in 316 us, with the previous N 1.75 GB in 368 us
+// (430 with loads, stores and wall rows under branches, where every use
+// waited for all loads in flight).  N is stored and read past the caches
+// (non-temporal: the next use is a whole solve away), r is not.  With the
+// waits for stores gone as well (loads a whole plane ahead of the ring's
+// refill) it took as long.  (A four-slot ring with one
 // barrier per plane needs 32 x 8 tiles to fit beside a second block and
 // measured slower: three waves per SIMD instead of four.)
 constexpr int ETX = 32, ETY = 16, ENT = ETX * ETY;
@@ -59,6 +65,8 @@ constexpr int EHX = ETX + 2, EHY = ETY + 2, EPL = EHX * EHY;
 constexpr int EKZ = 16;                               // nz is a multiple of 16
 constexpr int EPER = (4 * EPL + ENT - 1) / ENT;       // staged values per thread and plane
 
+// UE: u^e is stored.
+template <bool UE>
 __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const double *__restrict__ u,
                                                        const double *__restrict__ v,
                                                        const double *__restrict__ w,
@@ -66,8 +74,7 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
                                                        const double *nu_prev, const double *nv_prev,
                                                        const double *nw_prev, double *ue, double *ve,
                                                        double *we, double *ru, double *rv, double *rw,
-                                                       double *nu_out, double *nv_out, double *nw_out,
-                                                       int keep_ue)
+                                                       double *nu_out, double *nv_out, double *nw_out)
 {
     __shared__ double sm[3][4 * EPL];   // ring slot, then field (u, v, w, p) x tile
     const int nx = g.nx, ny = g.ny, nz = g.nz, vr = vrows(g);
@@ -75,7 +82,7 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
     // in turn; block b takes tile (b % 8) * per + b / 8, so each XCD walks a
     // contiguous run of tiles (x fastest, then y, then z) and the halo lines
     // that neighbouring tiles share are fetched into its own L2 once
-    const int gx = (nx + ETX - 1) / ETX, gy = (vr + ETY - 1) / ETY, ntile = gx * gy * (nz / EKZ);
+    const int gx = (nx + ETX - 1) / ETX, gy = (ny + ETY - 1) / ETY, ntile = gx * gy * (nz / EKZ);
     const int per = (ntile + 7) / 8;
     const int tile = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (tile >= ntile) return;   // whole block: before any barrier
@@ -85,39 +92,56 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
     const int k1 = k0 + EKZ;
     const int i = i0 + tx, j = j0 + ty;
 
-    // staging of one plane: this thread's EPER (field, tile point) values
+    // staging of one plane: this thread's EPER (field, tile point) values.
+    // Points beyond a wall or the tile's overhang stage any value of the
+    // plane: the formulas below never use them.  No load and no store of the
+    // march sits in a branch: the compiler would then wait for all that are
+    // in flight, not just for those it needs.
+    const double *src[EPER];
+    size_t pitch[EPER];   // of the field's planes
+    bool wall[EPER];      // v on a wall face: staged as zero (the stored value is ignored)
+#pragma unroll
+    for (int e = 0; e < EPER; ++e) {
+        const int idx = min((int)threadIdx.x + e * ENT, 4 * EPL - 1);
+        const int f = idx / EPL, r = idx - f * EPL;
+        const int hy = r / EHX, hx = r - hy * EHX;
+        const int rows = f == 1 ? vr : ny;
+        int gi = i0 - 1 + hx;
+        gi = gi < 0 ? gi + nx : (gi >= nx ? min(gi - nx, nx - 1) : gi);
+        int gj = j0 - 1 + hy;
+        if (g.py) gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);
+        wall[e] = f == 1 && !g.py && (gj <= 0 || gj >= ny);
+        gj = min(max(gj, 0), rows - 1);
+        src[e] = (f == 0 ? u : (f == 1 ? v : (f == 2 ? w : p))) + (size_t)gj * nx + gi;
+        pitch[e] = (size_t)rows * nx;
+    }
     double stg[EPER];
-#define ETILE_FETCH(kk_)                                                                       \
-    do {                                                                                       \
-        const int kq = (kk_);                                                                  \
-        const int kw = kq < 0 ? kq + nz : (kq >= nz ? kq - nz : kq);                           \
-        _Pragma("unroll") for (int e = 0; e < EPER; ++e) {                                     \
-            const int idx = threadIdx.x + e * ENT;                                             \
-            double val = 0.0;                                                                  \
-            if (idx < 4 * EPL) {                                                               \
-                const int f = idx / EPL, r = idx - f * EPL;                                    \
-                const int hy = r / EHX, hx = r - hy * EHX;                                     \
-                int gi = i0 - 1 + hx;                                                          \
-                gi = gi < 0 ? gi + nx : (gi >= nx ? gi - nx : gi);                             \
-                int gj = j0 - 1 + hy;                                                          \
-                const int rows = f == 1 ? vr : ny;                                             \
-                if (g.py) gj = gj < 0 ? gj + ny : (gj >= ny ? gj - ny : gj);                   \
-                if (gj >= 0 && gj < rows && gi < nx) {                                         \
-                    const double *src = f == 0 ? u : (f == 1 ? v : (f == 2 ? w : p));          \
-                    val = src[((size_t)kw * rows + gj) * nx + gi];                             \
-                }                                                                              \
-            }                                                                                  \
-            stg[e] = val;                                                                      \
-        }                                                                                      \
-    } while (0)
-#define ETILE_PUT(kk_)                                                                         \
-    do {                                                                                       \
-        double *dst = sm[((kk_) - k0 + 1) % 3];                                                \
-        _Pragma("unroll") for (int e = 0; e < EPER; ++e) {                                     \
-            const int idx = threadIdx.x + e * ENT;                                             \
-            if (idx < 4 * EPL) dst[idx] = stg[e];                                              \
-        }                                                                                      \
-    } while (0)
+    auto fetch = [&](int kq) {
+        const int kw = kq < 0 ? kq + nz : (kq >= nz ? kq - nz : kq);
+#pragma unroll
+        for (int e = 0; e < EPER; ++e) stg[e] = src[e][(size_t)kw * pitch[e]];
+    };
+    auto put = [&](int kq) {
+        double *dst = sm[(kq - k0 + 1) % 3];
+#pragma unroll
+        for (int e = 0; e < EPER; ++e) {
+            const int idx = threadIdx.x + e * ENT;
+            if (idx < 4 * EPL) dst[idx] = wall[e] ? 0.0 : stg[e];
+        }
+    };
+    // stores of a plane: offsets in the plane, out of range (dropped by the
+    // bounds check) where a thread has nothing to store
+    typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+    auto plane = [&](double *a, int k, int rows) {
+        return __builtin_amdgcn_make_buffer_rsrc(a + (size_t)k * rows * nx, 0, (unsigned)(rows * nx * 8), 0x00027000);
+    };
+    auto store_nt = [&](double val, __amdgpu_buffer_rsrc_t to, unsigned at) {   // non-temporal
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), to, at, 0, 2);
+    };
+    auto store = [&](double val, __amdgpu_buffer_rsrc_t to, unsigned at) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), to, at, 0, 0);
+    };
+    constexpr unsigned NONE = 0xfffffff8u;
 
     const double ihx = 1.0 / g.hx, ihz = 1.0 / g.hz;
     const double vis = cf.ab / cf.re;
@@ -132,35 +156,38 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
     const double i2D = 2.0 * iD;
     const double idn = crow && (g.py || j + 1 < ny) ? 1.0 / g.dyf[j + 1] : 0.0;
     const double ids = crow && (g.py || j > 0) ? 1.0 / g.dyf[j] : 0.0;
-    const bool frow = i < nx && j < vr && (g.py || (j > 0 && j < ny));
+    const bool frow = crow && (g.py || j > 0);
     const int jm = j > 0 ? j - 1 : ny - 1;   // the cell below a face (wraps when periodic)
     const double ifd = frow ? 1.0 / g.dyf[j] : 0.0;
     const double ifa = frow ? 1.0 / g.dyc[j] : 0.0;
     const double ifb = frow ? 1.0 / g.dyc[jm] : 0.0;
 
-    // rows outside a field (beyond a wall) are staged as zero; the formulas
-    // below never use them
-    ETILE_FETCH(k0 - 1);
-    ETILE_PUT(k0 - 1);
-    ETILE_FETCH(k0);
-    ETILE_PUT(k0);
-    ETILE_FETCH(k0 + 1);
+    const int oc = min(j, ny - 1) * nx + min(i, nx - 1);   // the thread's point in a plane, within the field
+    const unsigned os = crow ? 8u * (unsigned)(j * nx + i) : NONE;
+    const unsigned ow = crow && !g.py && j == ny - 1 ? 8u * (unsigned)(ny * nx + i) : NONE;   // the upper wall face
+    fetch(k0 - 1);
+    put(k0 - 1);
+    fetch(k0);
+    put(k0);
+    fetch(k0 + 1);
     for (int k = k0; k < k1; ++k) {
-        ETILE_PUT(k + 1);   // into the slot of plane k-2
+        put(k + 1);   // into the slot of plane k-2
+        // N_prev of this plane: before plane k+2's loads, which would
+        // otherwise have to arrive first
+        double pu = 0.0, pv = 0.0, pw = 0.0;
+        if (zprev) {
+            pu = __builtin_nontemporal_load(&nu_prev[(size_t)k * ny * nx + oc]);
+            pw = __builtin_nontemporal_load(&nw_prev[(size_t)k * ny * nx + oc]);
+            pv = __builtin_nontemporal_load(&nv_prev[(size_t)k * vr * nx + oc]);
+        }
         __syncthreads();
-        if (k + 2 <= k1) ETILE_FETCH(k + 2);
+        fetch(min(k + 2, k1));   // the last one is not used
         // field f at plane k + dk, row j + dj, column i + di (tile offsets)
         auto L = [&](int f, int dk, int dj, int di) {
             return sm[(k - k0 + 1 + dk) % 3][f * EPL + (ty + 1 + dj) * EHX + (tx + 1 + di)];
         };
-        // v with its wall faces read as zero (their stored values are ignored)
-        auto V = [&](int dk, int dj, int di) {
-            const int jj = j + dj;
-            if (!g.py && (jj <= 0 || jj >= ny)) return 0.0;
-            return L(1, dk, dj, di);
-        };
-        if (crow) {
-            const size_t o = ((size_t)k * ny + j) * nx + i;
+        auto V = [&](int dk, int dj, int di) { return L(1, dk, dj, di); };
+        {
             const bool hn = g.py || j + 1 < ny;   // a cell row above (else the wall)
             const bool hs = g.py || j > 0;        // a cell row below
             // y part of the Laplacian of a cell-height field at row j
@@ -168,8 +195,9 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
             // across the periodic wrap)
             auto lapy = [&](int f) {
                 const double fc = L(f, 0, 0, 0);
-                const double fu = hn ? (L(f, 0, 1, 0) - fc) * idn : -fc * i2D;
-                const double fl = hs ? (fc - L(f, 0, -1, 0)) * ids : fc * i2D;
+                const double in_u = (L(f, 0, 1, 0) - fc) * idn, in_l = (fc - L(f, 0, -1, 0)) * ids;
+                const double fu = hn ? in_u : -fc * i2D;
+                const double fl = hs ? in_l : fc * i2D;
                 return (fu - fl) * iD;
             };
             // ---- u at x-face (i, j, k)
@@ -181,17 +209,17 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
                 const double c1 = 0.5 * (uc + L(0, 0, 0, 1)), c0 = 0.5 * (L(0, 0, 0, -1) + uc);
                 const double dxx = (c1 * c1 - c0 * c0) * ihx;
                 // y fluxes v u on the faces j (below) and j+1 (above) at x-face i
-                const double fb = hs ? 0.5 * (V(0, 0, 0) + V(0, 0, -1)) * 0.5 * (L(0, 0, -1, 0) + uc) : 0.0;
-                const double ft = hn ? 0.5 * (V(0, 1, 0) + V(0, 1, -1)) * 0.5 * (uc + L(0, 0, 1, 0)) : 0.0;
-                const double dyy = (ft - fb) * iD;
+                const double fb = 0.5 * (V(0, 0, 0) + V(0, 0, -1)) * 0.5 * (L(0, 0, -1, 0) + uc);
+                const double ft = 0.5 * (V(0, 1, 0) + V(0, 1, -1)) * 0.5 * (uc + L(0, 0, 1, 0));
+                const double dyy = ((hn ? ft : 0.0) - (hs ? fb : 0.0)) * iD;
                 const double zb = 0.5 * (L(2, 0, 0, 0) + L(2, 0, 0, -1)) * 0.5 * (L(0, -1, 0, 0) + uc);
                 const double zt = 0.5 * (L(2, 1, 0, 0) + L(2, 1, 0, -1)) * 0.5 * (uc + L(0, 1, 0, 0));
                 const double N = dxx + dyy + (zt - zb) * ihz;
                 double e = uc + cf.dt * (vis * lap - cf.ab * gp - cf.gam * N);
-                if (zprev) e -= cf.dt * cf.zet * nu_prev[o];
-                if (keep_ue) ue[o] = e;
-                ru[o] = e - cf.c * lap;
-                nu_out[o] = N;
+                if (zprev) e -= cf.dt * cf.zet * pu;
+                if constexpr (UE) store(e, plane(ue, k, ny), os);
+                store(e - cf.c * lap, plane(ru, k, ny), os);
+                store_nt(N, plane(nu_out, k, ny), os);
             }
             // ---- w at z-face (i, j, k): the x <-> z mirror of u
             {
@@ -201,51 +229,49 @@ __global__ __launch_bounds__(ENT) void explicit_kernel(FsGeo g, FsCoef cf, const
                 const double gp = (L(3, 0, 0, 0) - L(3, -1, 0, 0)) * ihz;
                 const double c1 = 0.5 * (wc + L(2, 1, 0, 0)), c0 = 0.5 * (L(2, -1, 0, 0) + wc);
                 const double dzz = (c1 * c1 - c0 * c0) * ihz;
-                const double fb = hs ? 0.5 * (V(0, 0, 0) + V(-1, 0, 0)) * 0.5 * (L(2, 0, -1, 0) + wc) : 0.0;
-                const double ft = hn ? 0.5 * (V(0, 1, 0) + V(-1, 1, 0)) * 0.5 * (wc + L(2, 0, 1, 0)) : 0.0;
-                const double dyy = (ft - fb) * iD;
+                const double fb = 0.5 * (V(0, 0, 0) + V(-1, 0, 0)) * 0.5 * (L(2, 0, -1, 0) + wc);
+                const double ft = 0.5 * (V(0, 1, 0) + V(-1, 1, 0)) * 0.5 * (wc + L(2, 0, 1, 0));
+                const double dyy = ((hn ? ft : 0.0) - (hs ? fb : 0.0)) * iD;
                 const double xb = 0.5 * (L(0, 0, 0, 0) + L(0, -1, 0, 0)) * 0.5 * (L(2, 0, 0, -1) + wc);
                 const double xt = 0.5 * (L(0, 0, 0, 1) + L(0, -1, 0, 1)) * 0.5 * (wc + L(2, 0, 0, 1));
                 const double N = (xt - xb) * ihx + dyy + dzz;
                 double e = wc + cf.dt * (vis * lap - cf.ab * gp - cf.gam * N);
-                if (zprev) e -= cf.dt * cf.zet * nw_prev[o];
-                if (keep_ue) we[o] = e;
-                rw[o] = e - cf.c * lap;
-                nw_out[o] = N;
+                if (zprev) e -= cf.dt * cf.zet * pw;
+                if constexpr (UE) store(e, plane(we, k, ny), os);
+                store(e - cf.c * lap, plane(rw, k, ny), os);
+                store_nt(N, plane(nw_out, k, ny), os);
             }
         }
-        // ---- v at y-face (i, j, k)
-        if (i < nx && j < vr) {
-            const size_t o = ((size_t)k * vr + j) * nx + i;
-            if (!g.py && (j == 0 || j == ny)) {   // wall faces
-                if (keep_ue) ve[o] = 0.0;
-                rv[o] = 0.0;
-                nv_out[o] = 0.0;
-            } else {
-                const double vc = V(0, 0, 0);
-                const double lapy = ((V(0, 1, 0) - vc) * ifa - (vc - V(0, -1, 0)) * ifb) * ifd;
-                const double lap = (V(0, 0, 1) - 2.0 * vc + V(0, 0, -1)) * ihx * ihx +
-                                   (V(1, 0, 0) - 2.0 * vc + V(-1, 0, 0)) * ihz * ihz + lapy;
-                const double gp = (L(3, 0, 0, 0) - L(3, 0, -1, 0)) * ifd;
-                const double c1 = 0.5 * (vc + V(0, 1, 0)), c0 = 0.5 * (V(0, -1, 0) + vc);
-                const double dyy = (c1 * c1 - c0 * c0) * ifd;
-                // x fluxes u v on the x-faces i and i+1 at y-face j
-                const double xb = 0.5 * (L(0, 0, -1, 0) + L(0, 0, 0, 0)) * 0.5 * (vc + V(0, 0, -1));
-                const double xt = 0.5 * (L(0, 0, -1, 1) + L(0, 0, 0, 1)) * 0.5 * (V(0, 0, 1) + vc);
-                const double zb = 0.5 * (L(2, 0, -1, 0) + L(2, 0, 0, 0)) * 0.5 * (vc + V(-1, 0, 0));
-                const double zt = 0.5 * (L(2, 1, -1, 0) + L(2, 1, 0, 0)) * 0.5 * (V(1, 0, 0) + vc);
-                const double N = (xt - xb) * ihx + dyy + (zt - zb) * ihz;
-                double e = vc + cf.dt * (vis * lap - cf.ab * gp - cf.gam * N);
-                if (zprev) e -= cf.dt * cf.zet * nv_prev[o];
-                if (keep_ue) ve[o] = e;
-                rv[o] = e - cf.c * lap;
-                nv_out[o] = N;
+        // ---- v at y-face (i, j, k), zero on the walls; the last row's thread
+        // has the upper one too
+        {
+            const bool in = g.py || j > 0;
+            const double vc = V(0, 0, 0);
+            const double lapy = ((V(0, 1, 0) - vc) * ifa - (vc - V(0, -1, 0)) * ifb) * ifd;
+            const double lap = (V(0, 0, 1) - 2.0 * vc + V(0, 0, -1)) * ihx * ihx +
+                               (V(1, 0, 0) - 2.0 * vc + V(-1, 0, 0)) * ihz * ihz + lapy;
+            const double gp = (L(3, 0, 0, 0) - L(3, 0, -1, 0)) * ifd;
+            const double c1 = 0.5 * (vc + V(0, 1, 0)), c0 = 0.5 * (V(0, -1, 0) + vc);
+            const double dyy = (c1 * c1 - c0 * c0) * ifd;
+            // x fluxes u v on the x-faces i and i+1 at y-face j
+            const double xb = 0.5 * (L(0, 0, -1, 0) + L(0, 0, 0, 0)) * 0.5 * (vc + V(0, 0, -1));
+            const double xt = 0.5 * (L(0, 0, -1, 1) + L(0, 0, 0, 1)) * 0.5 * (V(0, 0, 1) + vc);
+            const double zb = 0.5 * (L(2, 0, -1, 0) + L(2, 0, 0, 0)) * 0.5 * (vc + V(-1, 0, 0));
+            const double zt = 0.5 * (L(2, 1, -1, 0) + L(2, 1, 0, 0)) * 0.5 * (V(1, 0, 0) + vc);
+            const double N = (xt - xb) * ihx + dyy + (zt - zb) * ihz;
+            double e = vc + cf.dt * (vis * lap - cf.ab * gp - cf.gam * N);
+            if (zprev) e -= cf.dt * cf.zet * pv;
+            if constexpr (UE) {
+                store(in ? e : 0.0, plane(ve, k, vr), os);
+                store(0.0, plane(ve, k, vr), ow);
             }
+            store(in ? e - cf.c * lap : 0.0, plane(rv, k, vr), os);
+            store_nt(in ? N : 0.0, plane(nv_out, k, vr), os);
+            store(0.0, plane(rv, k, vr), ow);
+            store(0.0, plane(nv_out, k, vr), ow);
         }
         __syncthreads();   // the slot of plane k-1 is refilled next
     }
-#undef ETILE_FETCH
-#undef ETILE_PUT
 }
 
 // Roma, Peskin and Berger's three-point regularised delta, grid units.
@@ -286,7 +312,7 @@ static __device__ __forceinline__ double lap_at(const FsGeo &g, int comp, const 
 // The lanes of a marker share the three axes' divisions and weights; the two
 // launches take 31 + 31 us for 18 529 markers in 256^3 (one thread per marker
 // reading u^e fields: 76 us, and 400 MB more for the explicit kernel to store,
-// 482 us instead of 427), bound by scattered accesses: order over the XCDs or
+// 482 us instead of 427 at the time), bound by scattered accesses: order over the XCDs or
 // fewer instructions no longer change it.
 // STEP 0: F of every marker (to F[3 m + comp]) from u^e = r + c L u; 1: the
 // spreading of F into r; 2: both at once, u^e a field of its own.
@@ -372,11 +398,13 @@ hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st)
     cf.dt = s.dt;
     cf.re = s.re;
     cf.c = s.beta * s.dt / s.re;
-    const int vr = p.py ? p.ny : p.ny + 1;
-    const int ntile = ((p.nx + ETX - 1) / ETX) * ((vr + ETY - 1) / ETY) * (p.nz / EKZ);
+    const int ntile = ((p.nx + ETX - 1) / ETX) * ((p.ny + ETY - 1) / ETY) * (p.nz / EKZ);
     dim3 grid(8 * ((ntile + 7) / 8));   // a whole number of blocks per XCD
-    hipLaunchKernelGGL(explicit_kernel, grid, dim3(ENT), 0, st, g, cf, s.u, s.v, s.w, s.p, s.nu, s.nv, s.nw,
-                       s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.nu, s.nv, s.nw, s.nmarkers > 0 && !ibm_from_rhs(p, s) ? 1 : 0);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(ENT), 0, st, g, cf, s.u, s.v, s.w, s.p, s.nu, s.nv, s.nw,
+                           s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.nu, s.nv, s.nw);
+    };
+    s.nmarkers > 0 && !ibm_from_rhs(p, s) ? go(explicit_kernel<true>) : go(explicit_kernel<false>);
     return hipGetLastError();
 }
 
