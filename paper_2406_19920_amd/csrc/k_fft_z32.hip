@@ -8,8 +8,9 @@ static void one(const FftSet &js, int rows, int nx, const int *skip, hipStream_t
 {
     constexpr int CW = 128 / sizeof(float);
     typedef typename FftReal<R1 * R2>::type T;
-    const dim3 grid(rows * nx / CW, js.n), blk(fft::Shape<R1, R2>::threads(AX, CW));
-    fft_z_kernel<float, T, R1, R2, INV, AX><<<grid, blk, 0, s>>>(js, nx, skip);
+    int runs;
+    const dim3 grid(fft_z_tiles<float>(rows, nx, runs), js.n), blk(fft::Shape<R1, R2>::threads(AX, CW));
+    fft_z_kernel<float, T, R1, R2, INV, AX><<<grid, blk, 0, s>>>(js, nx, runs, skip);
 }
 
 template <int R1, int R2>
