@@ -18,7 +18,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SOURCES = ["api.cpp", "plan.cpp", "k_xform.hip", "k_fold.hip", "k_tridiag.hip", "k_tridiag_cyc.hip",
            "k_stencil.hip", "k_split.hip", "k_fstep.hip", "k_multigrid.hip", "batch.cpp", "noalloc.hip",
            "fft.cpp", "k_fft_x64.hip", "k_fft_z64.hip", "k_fft_x32f.hip", "k_fft_x32i.hip", "k_fft_x32w.hip",
-           "k_fft_x32n.hip", "k_fft_z32.hip"]
+           "k_fft_x32n.hip", "k_fft_z32.hip", "k_plane.hip"]
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE,
          # no packed FP32 instructions in device code

@@ -247,6 +247,17 @@ static ibs_status run_fp64_stages(Plan &p, JobSet js, double *const *W, double *
                           : launch_zgemm_f64(js, p.nz, p.nz, p.nx, za[inverse], s);
     };
     const double xflop = transform_flops(p, js, false), zflop = transform_flops(p, js, true);
+    if (p.plane) {   // booked as x transforms
+        bind(RHS, PING);
+        e = timed(p, PK_XGEMM, xflop + zflop, rw, s, [&] { return launch_plane_f64(js, p, false, s); });
+        if (e != hipSuccess) return hip_fail(e, "x and z forward");
+        bind(PING, PING);
+        e = timed(p, PK_TRIDIAG, 20.0 * cells, rw, s, [&] { return launch_tridiag_f64(js, p, st, poisson, s); });
+        if (e != hipSuccess) return hip_fail(e, "tridiagonal");
+        bind(PING, SOL);
+        e = timed(p, PK_XGEMM, xflop + zflop, rw, s, [&] { return launch_plane_f64(js, p, true, s); });
+        return e == hipSuccess ? IBS_OK : hip_fail(e, "z and x inverse");
+    }
     bind(RHS, PONG);
     e = timed(p, PK_XGEMM, xflop, rw, s, [&] { return xform(false); });
     if (e != hipSuccess) return hip_fail(e, "x forward");
@@ -331,7 +342,9 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
         ss.j[q].slot = q;
         D1[q] = p.fx && p.fz ? W2[q] : W1[q];
     }
+    // with p.plane the x transform's launch includes z's
     auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
+        if (p.plane) return launch_plane_f32(all, p, st, inverse, in64, mode, pass, s);
         return p.fx ? launch_fft_x32(all, p, st, inverse, in64, mode, pass, s)
                     : launch_split_xgemm(all, p, st, inverse, in64, mode, pass, s);
     };
@@ -373,22 +386,22 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
             ss.j[q].in = pass == 0 ? static_cast<const void *>(ss.j[q].b) : static_cast<const void *>(W2[q]);
             ss.j[q].out = D1[q];
         }
-        e = timed(p, PK_XGEMM_SPLIT, xfl, (pass == 0 ? 12.0 : 8.0) * cells, s,
+        e = timed(p, PK_XGEMM_SPLIT, p.plane ? xfl + zfl : xfl, (pass == 0 ? 12.0 : 8.0) * cells, s,
                   [&] { return xform(ss, false, pass == 0, 0, pass); });
         if (e != hipSuccess) return hip_fail(e, "x forward (split)");
         for (int q = 0; q < ss.n; ++q) { ss.j[q].in = D1[q]; ss.j[q].out = W2[q]; }
-        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, false, pass); });
+        if (!p.plane) e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, false, pass); });
         if (e != hipSuccess) return hip_fail(e, "z forward (split)");
         for (int q = 0; q < ss.n; ++q) js.j[q].info = pass == 0 ? info[q] : nullptr;
         e = timed(p, PK_TRIDIAG_F32, 20.0 * cells, 8.0 * cells, s, [&] { return launch_tridiag_f32(js, p, st, poisson, pass, s); });
         if (e != hipSuccess) return hip_fail(e, "tridiagonal (refined)");
         for (int q = 0; q < ss.n; ++q) { ss.j[q].in = W2[q]; ss.j[q].out = D1[q]; }
-        e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, true, pass); });
+        if (!p.plane) e = timed(p, PK_ZGEMM_SPLIT, zfl, 8.0 * cells, s, [&] { return zform(ss, true, pass); });
         if (e != hipSuccess) return hip_fail(e, "z inverse (split)");
         for (int q = 0; q < ss.n; ++q) ss.j[q].in = D1[q];
         const int mode = pass == 0 ? (xs32 ? 3 : 1) : (xs32 ? 4 : 2);
         const double ub = mode == 3 ? 8.0 : (mode == 1 ? 12.0 : (mode == 4 ? 16.0 : 20.0));
-        e = timed(p, PK_UPDATE, xfl, ub * cells, s,
+        e = timed(p, PK_UPDATE, p.plane ? xfl + zfl : xfl, ub * cells, s,
                   [&] { return xform(ss, true, false, mode, pass); });
         if (e != hipSuccess) return hip_fail(e, "x inverse + update (split)");
         // a one-pass solve has no error estimate: pass 0's check says so

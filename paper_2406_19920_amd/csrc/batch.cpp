@@ -392,9 +392,9 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
             for (int a = 0; a < f.nx; a += 64) titems.push_back(make_int4((int)fi, c, a, 0));
     }
     // the groups' tables: per field the four transforms and the pencils
-    const size_t fe = fft_entry_bytes(), te = tri_entry_bytes();
+    const size_t fe = fft_entry_bytes(), te = tri_entry_bytes(), pe = plane_entry_bytes();
     std::vector<unsigned char> fast_img;
-    struct Chain { int nx, ny, nz, n; bool wx, wz; int xk, zk; size_t at[5]; };   // x, z forward, z, x inverse, pencils
+    struct Chain { int nx, ny, nz, n; bool wx, wz, plane; int xk, zk; size_t at[5]; };   // x, z forward, z, x inverse, pencils
     std::vector<Chain> chains;
     for (const auto &g : groups) {
         const std::vector<Fast> &all = g.second;
@@ -402,17 +402,19 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         const size_t per = std::max<size_t>(1, MG_CHAIN_BYTES / ((size_t)p0.nz * (p0.ny + 1) * p0.nx * sizeof(double)));
         for (size_t first = 0; first < all.size(); first += per) {
             const size_t n = std::min(per, all.size() - first);
-            Chain c{p0.nx, p0.ny, p0.nz, (int)n, p0.wx, p0.wz, all[first].job.xk, all[first].job.zk, {}};
+            Chain c{p0.nx, p0.ny, p0.nz, (int)n, p0.wx, p0.wz, p0.plane, all[first].job.xk, all[first].job.zk, {}};
             for (int stage = 0; stage < 5; ++stage) {
                 c.at[stage] = (fast_img.size() + 255) & ~size_t(255);
-                const size_t sz = stage < 4 ? fe : te;
+                if (c.plane && (stage == 1 || stage == 2)) continue;   // in the x transforms' launches
+                const size_t sz = stage == 4 ? te : (c.plane ? pe : fe);
                 fast_img.resize(c.at[stage] + n * sz);
                 for (size_t q = 0; q < n; ++q) {
                     const Fast &f = all[first + q];
                     FieldJob job = f.job;
                     if (stage != 0) job.in = job.out;   // in place after the first stage
                     void *to = fast_img.data() + c.at[stage] + q * sz;
-                    if (stage < 4) fft_entry_fill(to, *f.p, job, stage == 1 || stage == 2, stage >= 2);
+                    if (stage < 4 && c.plane) plane_entry_fill(to, *f.p, job, stage == 3);
+                    else if (stage < 4) fft_entry_fill(to, *f.p, job, stage == 1 || stage == 2, stage >= 2);
                     else tri_entry_fill(to, *f.p, job, f.poisson);
                 }
             }
@@ -473,7 +475,9 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         for (const Chain &c : chains) {
             const unsigned char *t = dev + o_fast;
             auto fft = [&](int stage, bool z_axis, bool inverse) {
-                if (le == hipSuccess)
+                if (le != hipSuccess) return;
+                if (c.plane && !z_axis) le = launch_plane_table(t + c.at[stage], c.n, c.nx, c.ny, c.nz, inverse, cap);
+                if (!c.plane)
                     le = launch_fft_table(t + c.at[stage], c.n, c.nx, c.ny, c.nz, z_axis, inverse, z_axis ? c.wz : c.wx,
                                           z_axis ? c.zk : c.xk, cap);
             };

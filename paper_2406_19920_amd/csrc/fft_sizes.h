@@ -13,6 +13,9 @@
     X(16, 4, 4) X(48, 8, 6) X(80, 10, 8) X(112, 14, 8) X(144, 16, 9) X(176, 16, 11) X(208, 16, 13)        \
     X(240, 16, 15) X(336, 24, 14) X(400, 20, 20) X(432, 24, 18)
 
+// Those the fused x-z transforms (k_plane.h) are built for.
+#define IBS_PLANE_SIZES(X) X(16, 4, 4) X(32, 8, 4) X(48, 8, 6) X(64, 8, 8)
+
 // FP32 fields (refined path): lines of up to this length are transformed in
 // FP64 arithmetic, longer ones in FP32.  The three-term bfloat16 products
 // these transforms replace carry a line's result to within a few roundings
@@ -22,4 +25,5 @@
 // by 2, and FP64 arithmetic there costs nothing: the pass is bound by memory.
 namespace ibs {
 constexpr int FFT_F64_ARITH_MAX = 64;
+constexpr int PLANE_MAX = 64;   // longest line of the fused x-z transforms
 }

@@ -159,6 +159,7 @@ struct Plan {
     bool wz = false;                               // walls at z = 0 and z = lz
     bool sx = false, sz = false;                   // stretched (wall-bounded) x / z
     bool fx = false, fz = false;                   // the x / z axis has fast transforms
+    bool plane = false;                            // and both run in one launch
     int tune[NUM_TUNE] = {-1, -1};   // candidate index per knob; -1 = default
     int nx, ny, nz;
     double hx, hz;
@@ -376,6 +377,16 @@ hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, 
 hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
                           int pass, hipStream_t s);
 hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s);
+
+// Both transforms of short periodic lines in one launch (k_plane.h): plans
+// with p.plane only.  As the pairs of launches above, x and z in the order of
+// the direction.
+hipError_t launch_plane_f64(const JobSet &js, const Plan &p, bool inverse, hipStream_t s);
+size_t plane_entry_bytes();
+void plane_entry_fill(void *to, const Plan &p, const FieldJob &job, bool inverse);
+hipError_t launch_plane_table(const void *entries, int n, int nx, int ny, int nz, bool inverse, hipStream_t s);
+hipError_t launch_plane_f32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
+                            int pass, hipStream_t s);
 
 inline const double *blob_ptr(const Plan &p, size_t off) {
     return reinterpret_cast<const double *>(static_cast<const unsigned char *>(p.dev_const) + off);

@@ -1140,6 +1140,7 @@ hipError_t launch_residual_f32(const SplitSet &ss, const Plan &p, const State &s
 // only on the grid.
 size_t update_slots(const Plan &p)
 {
+    if (p.plane) return p.ny;                                  // one per block
     if (p.fx) return (size_t)p.nz * p.ny / FFT_RW;   // one per block
     const size_t rows = (size_t)8 * 16 * x_wm(x_nbt(p.nx));
     return ((size_t)p.nz * p.ny + rows - 1) / rows * UPD_WAVES;

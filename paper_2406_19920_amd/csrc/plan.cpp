@@ -857,6 +857,13 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     const int nzk = p->wz ? NUM_XK : 1;   // distinct z tables
     p->fx = !ax[0]->fft[0].empty();
     p->fz = !az[0]->fft[0].empty();
+    // one launch for both up to 64 x 64 points, where a plane in FP64 takes 33 KB
+    // of LDS and four blocks fit a CU, and where the refined path's lines are
+    // transformed in FP64 arithmetic anyway.  Both sides, us: FP64 32^3 three
+    // Helmholtz 15.3 -> 13.7, 64^3 31.9 -> 24.6, 64x512x64 97 -> 83, refined
+    // 64^3 64 -> 59; Poisson 64^3 equal (20.3 / 19.7)
+    p->plane = p->fx && p->fz && !p->wx && !p->wz && std::max(nx, nz) <= PLANE_MAX;
+    static_assert(PLANE_MAX <= FFT_F64_ARITH_MAX, "the plane's tables are FP64");
 
     // blob layout
     BlobLayout &L = p->lay;

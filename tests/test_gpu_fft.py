@@ -85,3 +85,29 @@ def test_component_groups(ibs, ny):
     for q in range(3):
         assert torch.equal(got[q], S.helmholtz([q], c[q:q + 1], rs[q:q + 1])[0])
         assert S.read_info(0).status == 0
+
+
+# both classes of blocks (few planes, and above 2048), every size of the fused
+# x-z transforms beside another one
+@pytest.mark.parametrize("refined", [False, True])
+@pytest.mark.parametrize("nx,ny,nz", [(16, 17, 64), (64, 9, 48), (48, 700, 32), (32, 700, 64), (64, 700, 64), (64, 17, 64)])
+def test_planes(ibs, nx, ny, nz, refined):
+    if refined and (nx % 32 or nz % 32):
+        pytest.skip("the refined path takes multiples of 32")
+    print("case planes", nx, ny, nz, refined, flush=True)
+    S = ibs.Solver(nx, ny, nz, beta=0.5, precision=ibs.IBS_REFINED_BF16X3 if refined else ibs.IBS_FP64)
+    c = 0.125 / max(nx, ny, nz) ** 2
+    xs, rs = [], []
+    for comp in range(3):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(comp)
+        x = torch.randn(S.shape(comp + 1), generator=g, dtype=torch.float64, device="cuda")
+        if comp == 1:
+            x[:, 0] = 0
+            x[:, ny] = 0
+        xs.append(x)
+        rs.append(-S.residual(comp + 1, c, x, torch.zeros_like(x)))
+    got = S.helmholtz([0, 1, 2], [c] * 3, rs)
+    for comp in range(3):
+        assert float((got[comp] - xs[comp]).norm() / xs[comp].norm()) < TOL[refined]
+        assert S.read_info(comp).status == 0
