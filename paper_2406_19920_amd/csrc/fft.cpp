@@ -11,14 +11,18 @@ static int axis_form(bool walls, int xk)
     return !walls ? fft::AX_PERIODIC : (xk == XK_F ? fft::AX_FACES : fft::AX_CENTRES);
 }
 
-static FftJob fft_job(const Plan &p, bool z_axis, bool inverse, int rows, int ykind, int kind, int slot)
+// f32: forward in FP32 arithmetic
+static FftJob fft_job(const Plan &p, bool z_axis, bool inverse, int rows, int ykind, int kind, int slot,
+                      bool f32 = false)
 {
     const BlobLayout &L = p.lay;
     FftJob f{};
     const bool faces = axis_form(z_axis ? p.wz : p.wx, kind) == fft::AX_FACES;
     if (faces) f.tw = table(p, z_axis ? L.ftz_face : L.ftx_face);
+    else if (f32 && !inverse) f.tw = table(p, z_axis ? L.ftz_fwd32 : L.ftx_fwd32);
     else f.tw = table(p, z_axis ? (inverse ? L.ftz_inv : L.ftz_fwd) : (inverse ? L.ftx_inv : L.ftx_fwd));
-    f.rot = table(p, z_axis ? (inverse ? L.frz_inv : L.frz_fwd) : (inverse ? L.frx_inv : L.frx_fwd));
+    if (f32 && !inverse) f.rot = table(p, z_axis ? L.frz_fwd32 : L.frx_fwd32);
+    else f.rot = table(p, z_axis ? (inverse ? L.frz_inv : L.frz_fwd) : (inverse ? L.frx_inv : L.frx_fwd));
     f.rows = rows;
     f.skip = skip_first_row(ykind);
     f.kind = kind;
@@ -73,20 +77,21 @@ hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bo
     double *red = upd ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
     const double *scale = upd ? st.scale : nullptr;
     const int stride = (int)update_slots(p);
+    const bool exact = ss.j[0].op == IBS_OP_POISSON;   // a set's jobs are of one kind
     for (int ax = 0; ax < 3; ++ax) {
         FftSet f{};
         for (int q = 0; q < ss.n; ++q) {
             const SplitJob &j = ss.j[q];
             if (axis_form(p.wx, j.xk) != ax) continue;
             FftJob &to = f.j[f.n++];
-            to = fft_job(p, false, inverse, j.rows, j.kind, j.xk, j.slot);
+            to = fft_job(p, false, inverse, j.rows, j.kind, j.xk, j.slot, !exact && p.nx > FFT_F64_ARITH_MAX);
             to.in = j.in;
             to.out = !inverse ? static_cast<void *>(j.out) : (mode == 3 ? j.xs : static_cast<void *>(j.x));
             to.xs = j.xs;
             to.x0 = j.x;
         }
         hipError_t e;
-        if (!inverse) e = launch_fft_x32_fwd(f, p.nx, p.ny, p.nz, ax, in64, skip, s);
+        if (!inverse) e = launch_fft_x32_fwd(f, p.nx, p.ny, p.nz, ax, exact, in64, skip, s);
         else if (ax == fft::AX_FACES) e = launch_fft_x32_face(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
         else if (ax) e = launch_fft_x32_wall(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
         else e = launch_fft_x32_inv(f, p.nx, p.ny, p.nz, mode, red, stride, skip, scale, s);
@@ -97,17 +102,19 @@ hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bo
 
 hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s)
 {
+    const bool exact = ss.j[0].op == IBS_OP_POISSON;
     for (int ax = 0; ax < 3; ++ax) {
         FftSet f{};
         for (int q = 0; q < ss.n; ++q) {
             const SplitJob &j = ss.j[q];
             if (axis_form(p.wz, j.zk) != ax) continue;
             FftJob &to = f.j[f.n++];
-            to = fft_job(p, true, inverse, j.rows, j.kind, j.zk, j.slot);
+            to = fft_job(p, true, inverse, j.rows, j.kind, j.zk, j.slot, !exact && p.nz > FFT_F64_ARITH_MAX);
             to.in = j.in;
             to.out = j.out;
         }
-        if (hipError_t e = launch_fft_z32(f, p.nz, p.ny, p.nx, inverse, ax, pass >= 2 ? st.done : nullptr, s); e != hipSuccess)
+        if (hipError_t e = launch_fft_z32(f, p.nz, p.ny, p.nx, inverse, ax, exact,
+                                          pass >= 2 ? st.done : nullptr, s); e != hipSuccess)
             return e;
     }
     return hipSuccess;

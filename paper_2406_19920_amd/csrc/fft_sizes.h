@@ -16,13 +16,19 @@
 // Those the fused x-z transforms (k_plane.h) are built for.
 #define IBS_PLANE_SIZES(X) X(16, 4, 4) X(32, 8, 4) X(48, 8, 6) X(64, 8, 8)
 
-// FP32 fields (refined path): lines of up to this length are transformed in
-// FP64 arithmetic, longer ones in FP32.  The three-term bfloat16 products
-// these transforms replace carry a line's result to within a few roundings
-// whatever its length; the FP32 butterflies lose about one per level.  From
-// 96 points on they come out ahead (refined solves at 128-416 points end 1.5
-// to 6 times closer to the FP64 solution), at 64 and below they fell behind
-// by 2, and FP64 arithmetic there costs nothing: the pass is bound by memory.
+// FP32 fields (refined path): a pressure solve's forward transforms and all
+// lines of up to this length take FP64 arithmetic, the others FP32.
+// The three-term bfloat16 products these transforms replace carried a line's
+// result to within a few roundings whatever its length.  FP32 butterflies
+// forward spread eps of the whole line over every mode, and the pressure
+// solve multiplies what falls on the lowest by 1 / lambda: refined Poisson
+// solves ended up to 2.7 times further from the FP64 solution than with the
+// products (416x32x64), with walls in x up to 6 times (512x32x64); with FP64
+// they end as near or up to 20 times nearer.  Helmholtz solves (largest factor
+// 1) and inverse transforms do not amplify it: those end 1.5 to 6 times nearer
+// in FP32 already.  At 256^3 FP64 costs a pressure z transform 28 us
+// instead of 24 and an x transform 26 instead of 22, up to 64 points nothing
+// (the pass is bound by memory).
 namespace ibs {
 constexpr int FFT_F64_ARITH_MAX = 64;
 constexpr int PLANE_MAX = 64;   // longest line of the fused x-z transforms

@@ -47,6 +47,7 @@ struct BlobLayout {
     // N/2 + 1 coefficient pairs and the twiddle factors of the faces' lines
     size_t ftx_fwd, ftx_inv, frx_fwd, frx_inv, ftx_face;
     size_t ftz_fwd, ftz_inv, frz_fwd, frz_inv, ftz_face;
+    size_t ftx_fwd32, frx_fwd32, ftz_fwd32, frz_fwd32;   // the forward ones in FP32 (refined path, long lines)
     size_t lam_x[NUM_XK], lam_z[NUM_XK];   // eigenvalues (double) per x / z kind
     size_t lo[NUM_KINDS], di[NUM_KINDS], up[NUM_KINDS];  // y operator rows
     size_t wy;               // Delta_j (pressure weights), ny doubles

@@ -38,9 +38,10 @@
 
 namespace ibs {
 
-// arithmetic type of FP32 fields' transforms
-template <int N> struct FftReal {
-    typedef typename std::conditional<(N <= FFT_F64_ARITH_MAX), double, float>::type type;
+// Arithmetic type of FP32 fields' transforms (fft_sizes.h); EXACT: forward
+// transforms of a pressure solve.
+template <int N, bool EXACT> struct FftReal {
+    typedef typename std::conditional<(EXACT || N <= FFT_F64_ARITH_MAX), double, float>::type type;
 };
 
 struct FftJob {
@@ -118,6 +119,14 @@ static __device__ __forceinline__ void rows_out(const T *lds, const int *prow, T
 
 }  // namespace fft
 
+// Columns of the z kernel's tile: 128 bytes of every plane; 64 for long FP32
+// lines in FP64 arithmetic, whose exchange would leave two blocks per CU (256^3
+// 37 us instead of 28).
+template <typename TS, typename T, int N> constexpr int fft_cw()
+{
+    return sizeof(TS) == 4 && sizeof(T) == 8 && N > FFT_F64_ARITH_MAX ? 16 : 128 / (int)sizeof(TS);
+}
+
 // z transform of a tile of CW consecutive columns (128 bytes of every plane):
 // lanes run along the columns, so every load and store is whole lines.
 // Neighbouring tiles share DRAM pages, so each XCD (blocks are dealt to the 8
@@ -132,13 +141,13 @@ static __device__ __forceinline__ void rows_out(const T *lds, const int *prow, T
 // (k1 apart) use different banks.
 // TS: stored type, T: arithmetic.
 template <typename TS, typename T, int R1, int R2, bool INV, int AX, typename Set>
-__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(AX, 128 / sizeof(TS)))) void fft_z_kernel(Set js, int nx, int runs,
+__global__ __launch_bounds__((fft::Shape<R1, R2>::threads(AX, fft_cw<TS, T, R1 * R2>()))) void fft_z_kernel(Set js, int nx, int runs,
                                                                                     const int *skip)
 {
     using namespace fft;
     typedef Shape<R1, R2> S;
     constexpr bool WALL = AX == AX_CENTRES;
-    constexpr int CW = 128 / sizeof(TS), NA = S::items(AX), KZ = (NA | 1) * CW;
+    constexpr int CW = fft_cw<TS, T, S::N>(), NA = S::items(AX), KZ = (NA | 1) * CW;
     __shared__ T sre[S::K1 * KZ], sim[S::K1 * KZ];
     const FftJob &jb = js.j[blockIdx.y];
     if (skip && skip[jb.slot]) return;
@@ -492,11 +501,11 @@ __global__ __launch_bounds__((fft::Shape<R1, R2>::threads(AX, FFT_RW))) void fft
 }
 
 // Grid and order of the z kernel's tiles (above); rows: transform rows, TS:
-// stored type.
-template <typename TS> inline int fft_z_tiles(int rows, int nx, int &runs)
+// stored type, cw: columns of a tile.
+template <typename TS> inline int fft_z_tiles(int rows, int nx, int cw, int &runs)
 {
     runs = sizeof(TS) == 4 || rows % 256 != 0;
-    const int tiles = rows * nx * (int)sizeof(TS) / 128;
+    const int tiles = rows * nx / cw;
     return runs ? (tiles + 7) / 8 * 8 : tiles;
 }
 
@@ -506,11 +515,12 @@ template <typename TS> inline int fft_z_tiles(int rows, int nx, int &runs)
 hipError_t launch_fft_z64(const FftTable &js, int n, int rows, int nx, bool inverse, int ax, hipStream_t s);
 hipError_t launch_fft_x64(const FftTable &js, int n, int rows, int nz, bool inverse, int ax, hipStream_t s);
 hipError_t launch_fft_z64(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, hipStream_t s);
-hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, const int *skip,
-                          hipStream_t s);
+hipError_t launch_fft_z32(const FftSet &js, int n, int rows, int nx, bool inverse, int ax, bool exact,
+                          const int *skip, hipStream_t s);
 hipError_t launch_fft_x64(const FftSet &js, int n, int rows, int nz, bool inverse, int ax, hipStream_t s);
-// mode as fft_x_kernel's; in64: the forward input is FP64
-hipError_t launch_fft_x32_fwd(const FftSet &js, int n, int rows, int nz, int ax, bool in64, const int *skip,
+// mode as fft_x_kernel's; in64: the forward input is FP64; exact: FP64
+// arithmetic
+hipError_t launch_fft_x32_fwd(const FftSet &js, int n, int rows, int nz, int ax, bool exact, bool in64, const int *skip,
                               hipStream_t s);
 hipError_t launch_fft_x32_inv(const FftSet &js, int n, int rows, int nz, int mode, double *red, int red_stride,
                               const int *skip, const double *scale, hipStream_t s);

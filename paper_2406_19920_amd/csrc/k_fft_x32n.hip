@@ -9,7 +9,7 @@ template <int R1, int R2, int AX>
 static void go(const FftSet &js, int rows, int nz, int mode, double *red, int red_stride, const int *skip,
                const double *scale, hipStream_t s)
 {
-    typedef typename FftReal<R1 * R2>::type T;
+    typedef typename FftReal<R1 * R2, false>::type T;
     const dim3 grid(nz * rows / FFT_RW, js.n), blk(fft::Shape<R1, R2>::threads(AX, FFT_RW));
     switch (mode) {
     case 1: fft_x_kernel<float, float, T, R1, R2, true, AX, 1><<<grid, blk, 0, s>>>(js, nz, red, red_stride, skip, scale); break;

@@ -8,7 +8,7 @@ static void one(const Set &js, int rows, int nx, hipStream_t s)
 {
     constexpr int CW = 128 / sizeof(double);
     int runs;
-    const dim3 grid(fft_z_tiles<double>(rows, nx, runs), js.n), blk(fft::Shape<R1, R2>::threads(AX, CW));
+    const dim3 grid(fft_z_tiles<double>(rows, nx, CW, runs), js.n), blk(fft::Shape<R1, R2>::threads(AX, CW));
     fft_z_kernel<double, double, R1, R2, INV, AX><<<grid, blk, 0, s>>>(js, nx, runs, nullptr);
 }
 

@@ -890,17 +890,20 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
     L.fz_inv_c = take(fold_z ? sizeof(double) * hz2 : 0);
     L.fz_inv_s = take(fold_z ? sizeof(double) * hz2 : 0);
     // fast transforms: one table set per axis (the wall kinds on cell centres
-    // share it) and the faces' table; in FP32 where the arithmetic is
+    // share it) and the faces' table; in FP32 where the arithmetic
+    // is (FftReal), the forward ones in both
     struct FastTable { size_t *at; const std::vector<double> *t; bool f32; };
     const bool f32x = split && nx > FFT_F64_ARITH_MAX, f32z = split && nz > FFT_F64_ARITH_MAX;
     const std::vector<double> none;
     const FastTable fast[] = {
-        {&L.ftx_fwd, &ax[0]->fft[0], f32x}, {&L.ftx_inv, &ax[0]->fft[1], f32x},
-        {&L.frx_fwd, &ax[0]->fft[2], f32x}, {&L.frx_inv, &ax[0]->fft[3], f32x},
-        {&L.ftz_fwd, &az[0]->fft[0], f32z}, {&L.ftz_inv, &az[0]->fft[1], f32z},
-        {&L.frz_fwd, &az[0]->fft[2], f32z}, {&L.frz_inv, &az[0]->fft[3], f32z},
+        {&L.ftx_fwd, &ax[0]->fft[0], false}, {&L.ftx_inv, &ax[0]->fft[1], f32x},
+        {&L.frx_fwd, &ax[0]->fft[2], false}, {&L.frx_inv, &ax[0]->fft[3], f32x},
+        {&L.ftz_fwd, &az[0]->fft[0], false}, {&L.ftz_inv, &az[0]->fft[1], f32z},
+        {&L.frz_fwd, &az[0]->fft[2], false}, {&L.frz_inv, &az[0]->fft[3], f32z},
         {&L.ftx_face, p->wx ? &ax[XK_F]->fft[0] : &none, f32x},
-        {&L.ftz_face, p->wz ? &az[XK_F]->fft[0] : &none, f32z}};
+        {&L.ftz_face, p->wz ? &az[XK_F]->fft[0] : &none, f32z},
+        {&L.ftx_fwd32, f32x ? &ax[0]->fft[0] : &none, true}, {&L.frx_fwd32, f32x ? &ax[0]->fft[2] : &none, true},
+        {&L.ftz_fwd32, f32z ? &az[0]->fft[0] : &none, true}, {&L.frz_fwd32, f32z ? &az[0]->fft[2] : &none, true}};
     for (const FastTable &f : fast) *f.at = take((f.f32 ? sizeof(float) : sizeof(double)) * f.t->size());
     for (int k = 0; k < NUM_XK; ++k) L.lam_x[k] = k < nxk ? take(sizeof(double) * nx) : L.lam_x[0];
     for (int k = 0; k < NUM_XK; ++k) L.lam_z[k] = k < nzk ? take(sizeof(double) * nz) : L.lam_z[0];

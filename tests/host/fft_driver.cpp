@@ -26,16 +26,16 @@ static void fail(const char *what, int n)
     std::exit(1);
 }
 
-template <int R1, int R2, bool WALL, typename T>
+template <int R1, int R2, bool WALL, typename T, typename TF = T>   // TF: forward
 static void check(const Plan &p, int basis)
 {
     typedef fft::Shape<R1, R2> S;
     constexpr int N = S::N;
     const bool sine = basis == XK_C;
-    auto tab = [&](size_t off) {
-        return reinterpret_cast<const fft::Cpx<T> *>(p.blob.data() + off);
-    };
-    const fft::Cpx<T> *twf = tab(p.lay.ftx_fwd), *twi = tab(p.lay.ftx_inv), *rf = tab(p.lay.frx_fwd), *ri = tab(p.lay.frx_inv);
+    const fft::Cpx<TF> *twf = reinterpret_cast<const fft::Cpx<TF> *>(p.blob.data() + (sizeof(TF) == 4 ? p.lay.ftx_fwd32 : p.lay.ftx_fwd));
+    const fft::Cpx<TF> *rf = reinterpret_cast<const fft::Cpx<TF> *>(p.blob.data() + (sizeof(TF) == 4 ? p.lay.frx_fwd32 : p.lay.frx_fwd));
+    const fft::Cpx<T> *twi = reinterpret_cast<const fft::Cpx<T> *>(p.blob.data() + p.lay.ftx_inv);
+    const fft::Cpx<T> *ri = reinterpret_cast<const fft::Cpx<T> *>(p.blob.data() + p.lay.frx_inv);
     const std::vector<double> &Q = *p.qx[basis < 0 ? 0 : basis];
     std::mt19937_64 g(N);
     std::normal_distribution<double> nd;
@@ -46,32 +46,33 @@ static void check(const Plan &p, int basis)
         std::vector<T> re(S::K1 * R2), im(S::K1 * R2);
         std::vector<int> hit(N, 0);
         // forward
+        std::vector<TF> fre(S::K1 * R2), fim(S::K1 * R2);
         for (int n2 = 0; n2 < R2; ++n2) {
-            T v[R1], yr[S::K1], yi[S::K1];
+            TF v[R1], yr[S::K1], yi[S::K1];
             for (int n1 = 0; n1 < R1; ++n1) {
                 const int i = fft::line_index<R1, R2, WALL>(n2, n1);
                 if (i < 0 || i >= N) fail("line index", N);
                 ++hit[i];
-                v[n1] = WALL && sine && 2 * n1 >= R1 ? -x[i] : x[i];
+                v[n1] = WALL && sine && 2 * n1 >= R1 ? -(TF)x[i] : (TF)x[i];
             }
-            fft::rdft<R1, T>(v, yr, yi);
+            fft::rdft<R1, TF>(v, yr, yi);
             for (int k1 = 0; k1 < S::K1; ++k1) {
-                const fft::Cpx<T> w = twf[k1 * R2 + n2];
-                re[k1 * R2 + n2] = w.x * yr[k1] - w.y * yi[k1];
-                im[k1 * R2 + n2] = w.x * yi[k1] + w.y * yr[k1];
+                const fft::Cpx<TF> w = twf[k1 * R2 + n2];
+                fre[k1 * R2 + n2] = w.x * yr[k1] - w.y * yi[k1];
+                fim[k1 * R2 + n2] = w.x * yi[k1] + w.y * yr[k1];
             }
         }
         for (int i = 0; i < N; ++i)
             if (hit[i] != 1) fail("input coverage", N);
         hit.assign(N, 0);
         for (int k1 = 0; k1 < S::K1; ++k1) {
-            T a[R2], b[R2];
-            for (int q = 0; q < R2; ++q) { a[q] = re[k1 * R2 + q]; b[q] = im[k1 * R2 + q]; }
-            fft::cdft<R2, -1, T>(a, b);
-            fft::emit<R1, R2, WALL, T>(a, b, k1, sine, rf, [&](int s, T v) {
+            TF a[R2], b[R2];
+            for (int q = 0; q < R2; ++q) { a[q] = fre[k1 * R2 + q]; b[q] = fim[k1 * R2 + q]; }
+            fft::cdft<R2, -1, TF>(a, b);
+            fft::emit<R1, R2, WALL, TF>(a, b, k1, sine, rf, [&](int s, TF v) {
                 if (s < 0 || s >= N) fail("spectral slot", N);
                 ++hit[s];
-                out[s] = v;
+                out[s] = (T)v;
             });
         }
         for (int i = 0; i < N; ++i)
@@ -185,8 +186,8 @@ template <int R1, int R2> static void size(int n, bool refined)
         if (build_plan(d, p) != IBS_OK) fail("plan", n);
         if (!p->fx) fail("kinds", n);
         if (refined && n > FFT_F64_ARITH_MAX) {
-            if (walls) { check<R1, R2, true, float>(*p, XK_P); check<R1, R2, true, float>(*p, XK_C); check_faces<R1, R2, float>(*p); }
-            else check<R1, R2, false, float>(*p, -1);
+            if (walls) { check<R1, R2, true, float, double>(*p, XK_P); check<R1, R2, true, float>(*p, XK_C); check_faces<R1, R2, float>(*p); }
+            else { check<R1, R2, false, float, double>(*p, -1); check<R1, R2, false, float>(*p, -1); }
         } else {
             if (walls) { check<R1, R2, true, double>(*p, XK_P); check<R1, R2, true, double>(*p, XK_C); check_faces<R1, R2, double>(*p); }
             else check<R1, R2, false, double>(*p, -1);

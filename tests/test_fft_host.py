@@ -25,7 +25,7 @@ def test_lines_match_the_dense_bases(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-300:]
     rows = [line.split() for line in r.stdout.splitlines() if line.startswith("fft ")]
-    assert len(rows) == 4 * (27 + 16)
+    assert len(rows) == 4 * (27 + 16) + 14   # refined periodic lines above 64 points in both forward arithmetics
     for _, n, basis, size, fwd, inv in rows:
         tol = 4 * EPS[int(size)]
         assert float(fwd) < tol and float(inv) < tol, (n, basis, size, fwd, inv)
