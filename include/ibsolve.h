@@ -16,10 +16,11 @@
  * velocity, homogeneous Neumann pressure, Appendix B), y faces optionally
  * stretched by tanh.
  *
- * Method: x and z are diagonalised by precomputed 1-D orthonormal
- * eigenvector matrices applied as dense contractions (the paper's 2-D FFT
- * of the two periodic directions, Section 2.3.3, items S1.1/S2.1, with the
- * modified wavenumbers of Appendix A as eigenvalues); every (x-mode,
+ * Method: x and z are diagonalised by 1-D orthonormal eigenbases (the
+ * paper's 2-D FFT of the two periodic directions, Section 2.3.3, items
+ * S1.1/S2.1, with the modified wavenumbers of Appendix A as eigenvalues):
+ * as fast transforms where the spacing is uniform and the length one of
+ * the built ones, else as dense contractions; every (x-mode,
  * z-mode) pencil is then a tridiagonal system along y (Appendix B), solved
  * directly.
  *
@@ -67,8 +68,8 @@ typedef enum {
     IBS_FP64 = 0,           /* every stage in FP64                              */
     IBS_REFINED_FP16X2 = 1, /* reserved: split-FP16 transforms; not built, so
                                solver_plan() returns IBS_ERR_UNSUPPORTED        */
-    IBS_REFINED_BF16X3 = 2, /* split-BF16 (3 terms) transforms, FP32
-                               accumulation, FP32 work arrays, refined against
+    IBS_REFINED_BF16X3 = 2, /* FP32 work arrays, fast transforms (split-BF16
+                               products, 3 terms, on stretched axes) refined against
                                an FP64 residual stored scaled by a power of
                                two taken from the first pass (rhs magnitudes
                                of about 1e-30 to 1e35 converge; beyond, a
@@ -102,8 +103,8 @@ typedef enum { IBS_PERIODIC = 0, IBS_DIRICHLET = 1, IBS_NEUMANN = 2 } ibs_bc;
  * not stored; its unknowns are slots 1..nx-1.  v and w (cell centres in x)
  * take the mirror-ghost Dirichlet row at the walls, the pressure zero flux.
  * The x transforms are then the cosine (pressure), sine-on-centres (v, w)
- * and sine-on-faces (u) eigenbases of the wall-bounded x operators, as
- * plain (unfolded) matrix products; ibs_rk_stage() is not served.
+ * and sine-on-faces (u) eigenbases of the wall-bounded x operators;
+ * ibs_rk_stage() is not served.
  * Walls in z (bc_z = IBS_DIRICHLET) are the same along z, w being the
  * face-normal component: w's plane 0 is the wall face z = 0 (ignored on
  * input, zero on output), the face z = lz is not stored; u and v take the

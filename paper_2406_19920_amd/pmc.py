@@ -29,17 +29,24 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 
 # profile class -> (kernel-name pattern, source files it is built from)
+_FFT = ("fft_core.h", "fft_line.h", "fft_sizes.h", "k_fft.h", "k_plane.h")
 CLASSES = {
-    "xgemm_f64": (r"\b(xgemm_f64_kernel|xfold_f64_kernel)<", ("k_xform.hip", "k_fold.hip")),
-    "zgemm_f64": (r"\b(zgemm_f64_kernel|zfold_f64_kernel)<", ("k_xform.hip", "k_fold.hip")),
-    "tridiag_f64": (r"\btridiag_kernel<double", ("k_tridiag.hip",)),
-    "tridiag_f32": (r"\btridiag_kernel<float", ("k_tridiag.hip",)),
+    "xgemm_f64": (r"\b(xgemm_f64_kernel|xfold_f64_kernel)<|\bfft_x_kernel<double, double,|\bplane_kernel<double, double,",
+                  ("k_xform.hip", "k_fold.hip", "k_fft_x64.hip", "k_plane.hip") + _FFT),
+    "zgemm_f64": (r"\b(zgemm_f64_kernel|zfold_f64_kernel)<|\bfft_z_kernel<double,",
+                  ("k_xform.hip", "k_fold.hip", "k_fft_z64.hip") + _FFT),
+    "tridiag_f64": (r"\btridiag_kernel<double", ("k_tridiag.hip", "tridiag.h")),
+    "tridiag_f32": (r"\btridiag_kernel<float", ("k_tridiag.hip", "tridiag.h")),
     "divergence": (r"\bdivergence_kernel\b", ("k_stencil.hip",)),
     "correct": (r"\bcorrect_kernel\b", ("k_stencil.hip",)),
     "residual": (r"\bresidual_f32_kernel\b", ("k_split.hip",)),
-    "xgemm_split": (r"\bsplit_x\w*kernel<\d+, \d+, (double|float), 0(, false)?(, \d+)?>", ("k_split.hip",)),
-    "zgemm_split": (r"\bsplit_z\w*kernel<", ("k_split.hip",)),
-    "update": (r"\bsplit_x\w*kernel<\d+, \d+, float, [1-4](, true)?(, \d+)?>", ("k_split.hip",)),
+    "xgemm_split": (r"\bsplit_x\w*kernel<\d+, \d+, (double|float), 0(, false)?(, \d+)?>|"
+                    r"\bfft_x_kernel<(double|float), float, \w+, \d+, \d+, false,|\bplane_kernel<(double|float), float, false,",
+                    ("k_split.hip", "k_fft_x32f.hip", "k_plane.hip") + _FFT),
+    "zgemm_split": (r"\bsplit_z\w*kernel<|\bfft_z_kernel<float,", ("k_split.hip", "k_fft_z32.hip") + _FFT),
+    "update": (r"\bsplit_x\w*kernel<\d+, \d+, float, [1-4](, true)?(, \d+)?>|"
+               r"\bfft_x_kernel<float, float, \w+, \d+, \d+, true,|\bplane_kernel<float, float, true,",
+               ("k_split.hip", "k_fft_x32i.hip", "k_fft_x32w.hip", "k_fft_x32n.hip", "k_plane.hip") + _FFT),
     "explicit": (r"\bexplicit_kernel\b", ("k_fstep.hip",)),
     "ibm": (r"\bibm_kernel\b", ("k_fstep.hip",)),
 }
