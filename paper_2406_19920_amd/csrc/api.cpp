@@ -298,6 +298,12 @@ static ibs_status run_fp64_pipeline_multi(Plan &p, const JobSet &js, double *con
         const ibs_status r = run_fp64_stages(p, jobs_from(js, q, n), W + q, X + q, true, on_w, st, poisson, s);
         if (r != IBS_OK) return r;
     }
+    // the pencils zero the left-out wall row of the field they work on: W
+    for (int q = 0; on_w && q < js.n; ++q)
+        if (skip_first_row(js.j[q].kind)) {
+            const hipError_t e = launch_wall_row(p, js.j[q].rows, X[q], s);
+            if (e != hipSuccess) return hip_fail(e, "wall row");
+        }
     return IBS_OK;
 }
 

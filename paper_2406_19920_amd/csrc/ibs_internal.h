@@ -305,6 +305,8 @@ bool ibm_from_rhs(const Plan &p, const FsStage &s);   // u^e is not written
 // rhs += the contribution of inhomogeneous wall data lo, hi ([nz][nx]).
 hipError_t launch_wall_data(const Plan &p, int op, double c, const double *lo, const double *hi,
                             double *rhs, hipStream_t s);
+// Zeros on the wall face y = 0 of a v field ([nz][rows][nx]).
+hipError_t launch_wall_row(const Plan &p, int rows, double *v, hipStream_t s);
 // Strict compatibility check of a Poisson rhs in FP64 (weighted mean against
 // weighted rms, on b itself): partial sums, then the verdict per job, which
 // sets st.incompat and, through the job's report, IBS_ERR_INCOMPATIBLE_RHS.

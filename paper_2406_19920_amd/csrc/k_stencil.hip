@@ -345,6 +345,21 @@ hipError_t launch_wall_data(const Plan &p, int op, double c, const double *lo, c
     return hipGetLastError();
 }
 
+// Row 0 of every plane of v = 0 (its wall face y = 0, which no transform
+// visits), for solves whose pencils worked on a scratch field.
+__global__ __launch_bounds__(256) void wall_row_kernel(int nx, int rows, double *__restrict__ v)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nx) v[(size_t)blockIdx.y * rows * nx + i] = 0.0;
+}
+
+hipError_t launch_wall_row(const Plan &p, int rows, double *v, hipStream_t s)
+{
+    const dim3 blk = row_block(p.nx), grid((p.nx + blk.x - 1) / blk.x, p.nz);
+    hipLaunchKernelGGL(wall_row_kernel, grid, blk, 0, s, p.nx, rows, v);
+    return hipGetLastError();
+}
+
 hipError_t launch_residual(const Plan &p, int op, double c, const double *x, const double *b,
                            double *r, double *norms2, double *red, hipStream_t s)
 {

@@ -1,0 +1,48 @@
+"""FP64 solves whose solutions lie on other components' right-hand sides: v's
+wall faces are zero on output wherever the solves work, as with buffers apart."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ibs():
+    from paper_2406_19920_amd import ibsolve
+    assert torch.cuda.is_available()
+    return ibsolve
+
+
+# fused planes; fast transforms, periodic and walled; dense products
+@pytest.mark.parametrize("nx,nz,walls", [(64, 64, False), (96, 48, False), (96, 48, True), (272, 32, False)])
+def test_wall_rows_of_v(ibs, nx, nz, walls):
+    print("case overlap", nx, nz, walls, flush=True)
+    ny, c = 21, [1e-3] * 3
+    S = ibs.Solver(nx, ny, nz, beta=0.5, **(dict(bc_x=ibs.IBS_DIRICHLET, bc_z=ibs.IBS_DIRICHLET) if walls else {}))
+    cells = nz * ny * nx
+
+    def flat(seed):   # room for any component
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        return torch.randn(nz * (ny + 1) * nx, generator=g, dtype=torch.float64, device="cuda")
+
+    def cell(t):
+        return t[:cells].view(nz, ny, nx)
+
+    def face(t):
+        return t.view(nz, ny + 1, nx)
+
+    # u and w change places, v in a buffer of its own that holds NaN
+    a, b, r = flat(1), flat(2), face(flat(3))
+    want = S.helmholtz([0, 1, 2], c, [cell(a).clone(), r, cell(b).clone()])
+    v = torch.full_like(r, float("nan"))
+    S.helmholtz([0, 1, 2], c, [cell(a), r, cell(b)], [cell(b), v, cell(a)])
+    for got, ref in zip((cell(b), v, cell(a)), want):
+        assert torch.equal(got, ref)
+    assert not v[:, 0].any() and not v[:, ny].any()
+    # v's solution on u's right-hand side
+    a, r = flat(4), face(flat(5))
+    want = S.helmholtz([0, 1], c[:2], [cell(a).clone(), r])
+    got = S.helmholtz([0, 1], c[:2], [cell(a), r], [S.empty(1), face(a)])
+    for x, ref in zip(got, want):
+        assert torch.equal(x, ref)
+    assert not got[1][:, 0].any() and not got[1][:, ny].any()
