@@ -291,8 +291,9 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         zk = pois ? XK_P : comp_zkind(p, j.comp[k]);
     };
     // The stage kernels read every right-hand side before any solution is
-    // written; chains do not.  A batch in which one field's solution overlaps
-    // another's right-hand side therefore takes the stage kernels alone.
+    // written; chains do not.  A batch in which a field's solution overlaps
+    // another's right-hand side, or its own by anything but being it, therefore
+    // takes the stage kernels alone.
     bool chains_ok = true;
     {
         struct Range { uintptr_t at, end; size_t field; };
@@ -315,7 +316,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
             // solutions are disjoint and in order: the first one ending beyond r.at
             auto it = std::upper_bound(xs.begin(), xs.end(), r.at, [](uintptr_t a, const Range &x) { return a < x.end; });
             for (; chains_ok && it != xs.end() && it->at < r.end; ++it)
-                if (it->field != r.field) chains_ok = false;
+                if (it->field != r.field || it->at != r.at) chains_ok = false;
         }
     }
     for (int q = 0; q < njobs && chains_ok; ++q) {

@@ -46,3 +46,26 @@ def test_wall_rows_of_v(ibs, nx, nz, walls):
     for x, ref in zip(got, want):
         assert torch.equal(x, ref)
     assert not got[1][:, 0].any() and not got[1][:, ny].any()
+
+
+# multi-grid batches: a solution on its own right-hand side (chains in place), or
+# one plane past or short of it; two fields make a group large enough for a chain
+@pytest.mark.parametrize("shift", [0, 1, -1])
+def test_batch_solution_partly_on_its_right_hand_side(ibs, shift):
+    print("case batch overlap", shift, flush=True)
+    n = 96
+    S = [ibs.Solver(n, n, n, beta=b) for b in (0.0, 1.0)]
+    flat = [torch.randn((n + 1) * n * n, generator=torch.Generator(device="cuda").manual_seed(q),
+                        dtype=torch.float64, device="cuda") for q in range(2)]
+    at = [max(shift, 0) * n * n, max(-shift, 0) * n * n]   # solution, right-hand side
+    x, b = ([f[o:o + n ** 3].view(n, n, n) for f in flat] for o in at)
+    want = [s.poisson(t.clone()) for s, t in zip(S, b)]
+    work = [torch.empty(s.work_p, dtype=torch.uint8, device="cuda") for s in S]
+    h = ibs.ibs_batch_build_multigrid([s.poisson_job(t, y, work=w) for s, t, y, w in zip(S, b, x, work)])
+    try:
+        ibs.ibs_batch_launch(h, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        ibs.ibs_batch_destroy(h)
+    for got, ref in zip(x, want):
+        assert float((got - ref).norm() / ref.norm()) < 1e-11
