@@ -185,7 +185,7 @@ ibs_status solver_plan(const ibs_grid_desc *desc, ibs_plan *out);
  * component on the FP64 path, three FP32 fields per component on the
  * refined path (cells of a field: nz * ny * nx, or nz * (ny+1) * nx for a
  * Helmholtz batch), followed by the call's mutable state (mean of the
- * rhs, refinement stop flags, reduction partials; under 2 MB at 512^3).
+ * rhs, refinement stop flags, reduction partials; under 256 KB).
  * Either output pointer may be NULL. */
 ibs_status solver_plan_bytes(ibs_plan plan, int32_t op, int32_t ncomp,
                              size_t *const_bytes, size_t *work_bytes);

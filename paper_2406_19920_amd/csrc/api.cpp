@@ -111,34 +111,25 @@ size_t field_bytes_for(const Plan &p, int op, int ncomp)
     return (size_t)ncomp * field_doubles(p, p.ny + 1) * per;
 }
 
-// Doubles of the state's reduction region: the update partials of every
-// refinement pass (refined path), at least the residual() partials.
-static size_t red_doubles(const Plan &p, int op, int ncomp)
-{
-    size_t n = 2 * (size_t)RESID_SLOTS;
-    if (p.desc.precision != IBS_FP64) {
-        const int nc = op == IBS_OP_POISSON ? 1 : ncomp;
-        const size_t upd = (size_t)default_passes(p, op == IBS_OP_POISSON) * update_region(p, nc);
-        n = upd > n ? upd : n;
-    }
-    return n;
-}
-
-static size_t state_bmax(const Plan &p) { return p.desc.precision == IBS_FP64 ? 0 : bmax_slots(p); }
-
 // State layout (after the fields, 256-byte aligned): bmean[4], done[4],
-// incompat[4], xsum[4][XSUM_SLOTS], compat[2 COMPAT_SLOTS], red[...],
-// bmax[4][bmax_slots], refined path, scale[4].
-size_t state_bytes_for(const Plan &p, int op, int ncomp)
+// incompat[4], xsum[4][XSUM_SLOTS], compat[2 COMPAT_SLOTS], red[2 RESID_SLOTS],
+// scale[4] and per pass totals[4][2].  The same for every grid: what grows with
+// one lies where it needs no room of its own.  The maxima of the first pass's pencils
+// lie over xsum (one job; a Helmholtz batch's over compat and red too): they
+// are read before the first residual writes xsum, compat is a Poisson solve's,
+// red residual()'s.  The partial sums of an update lie in a work field (State::upd).
+constexpr size_t XSUM_BYTES = (size_t)STATE_JOBS * XSUM_SLOTS * sizeof(double),
+                 COMPAT_BYTES = 2 * (size_t)COMPAT_SLOTS * sizeof(double),
+                 RED_BYTES = 2 * (size_t)RESID_SLOTS * sizeof(double),
+                 BMAX_BYTES = (size_t)REFINED_MAX * (REFINED_MAX / 16) * sizeof(float);   // most, one job
+static_assert(BMAX_BYTES <= XSUM_BYTES && 3 * BMAX_BYTES <= XSUM_BYTES + COMPAT_BYTES + RED_BYTES,
+              "the maxima fit the regions they share");
+static_assert(XSUM_BYTES % 256 == 0 && COMPAT_BYTES % 256 == 0 && RED_BYTES % 256 == 0, "aligned regions");
+static size_t state_bytes(const Plan &p, int op)
 {
-    size_t o = align256(STATE_JOBS * sizeof(double));
-    o += align256(2 * STATE_JOBS * sizeof(int));
-    o += align256((size_t)STATE_JOBS * XSUM_SLOTS * sizeof(double));
-    o += align256(2 * (size_t)COMPAT_SLOTS * sizeof(double));
-    o += align256(red_doubles(p, op, ncomp) * sizeof(double));
-    o += align256((size_t)STATE_JOBS * state_bmax(p) * sizeof(double));
-    o += align256(STATE_JOBS * sizeof(double));
-    return o;
+    const size_t passes = default_passes(p, op == IBS_OP_POISSON);
+    return align256(STATE_JOBS * sizeof(double)) + align256(2 * STATE_JOBS * sizeof(int)) + XSUM_BYTES + COMPAT_BYTES +
+           RED_BYTES + align256((1 + 2 * passes) * STATE_JOBS * sizeof(double));
 }
 
 State state_in(const Plan &p, void *work, int op, int ncomp)
@@ -151,22 +142,20 @@ State state_in(const Plan &p, void *work, int op, int ncomp)
     st.incompat = st.done + STATE_JOBS;
     b += align256(2 * STATE_JOBS * sizeof(int));
     st.xsum = reinterpret_cast<double *>(b);
-    b += align256((size_t)STATE_JOBS * XSUM_SLOTS * sizeof(double));
+    st.bmax = reinterpret_cast<float *>(b);
+    b += XSUM_BYTES;
     st.compat = reinterpret_cast<double *>(b);
-    b += align256(2 * (size_t)COMPAT_SLOTS * sizeof(double));
+    b += COMPAT_BYTES;
     st.red = reinterpret_cast<double *>(b);
-    st.red_count = red_doubles(p, op, ncomp);
-    st.upd_region = p.desc.precision == IBS_FP64 ? 0 : update_region(p, op == IBS_OP_POISSON ? 1 : ncomp);
-    b += align256(st.red_count * sizeof(double));
-    st.bmax = reinterpret_cast<double *>(b);
-    b += align256((size_t)STATE_JOBS * state_bmax(p) * sizeof(double));
+    b += RED_BYTES;
     st.scale = reinterpret_cast<double *>(b);
+    st.totals = st.scale + STATE_JOBS;
     return st;
 }
 
 size_t work_bytes_for(const Plan &p, int op, int ncomp)
 {
-    return align256(field_bytes_for(p, op, ncomp)) + state_bytes_for(p, op, ncomp);
+    return align256(field_bytes_for(p, op, ncomp)) + state_bytes(p, op);
 }
 
 static double total_cells(const JobSet &js, const Plan &p)
@@ -321,21 +310,17 @@ static ibs_status run_fp64_pipeline(Plan &p, JobSet js, double *W, double *X, co
 // second pass follows (that pass then writes x = W3 + d).
 // Every condition a refined launcher would refuse, checked on the host
 // before anything of the call is enqueued.
-static ibs_status check_refined(const Plan &p, int ncomp, int passes, const State &st)
+static ibs_status check_refined(int passes)
 {
     if (passes < 1 || passes > MAX_PASSES) {
         set_error("refinement passes out of range");
         return IBS_ERR_INVALID_ARG;
     }
-    if ((size_t)(passes > 1 ? passes - 1 : 0) * update_region(p, ncomp) > st.red_count) {
-        set_error("workspace state too small for the refinement passes");
-        return IBS_ERR_WORKSPACE_TOO_SMALL;
-    }
     return IBS_OK;
 }
 
 static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *const *W2,
-                              float *const *W3, const State &st, bool poisson, int passes, hipStream_t s)
+                              float *const *W3, State st, bool poisson, int passes, hipStream_t s)
 {
     hipError_t e;
     double cells = 0;
@@ -348,6 +333,10 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
         ss.j[q].slot = q;
         D1[q] = p.fx && p.fz ? W2[q] : W1[q];
     }
+    // the inverse x transforms read D1: the first job's other field takes the
+    // partial sums, 16 bytes for every 16 rows (or 128 bytes for 512) of at
+    // least 128 bytes each, times three jobs; the check reads them at once
+    st.upd = reinterpret_cast<double *>(D1[0] == W1[0] ? W2[0] : W1[0]);
     // with p.plane the x transform's launch includes z's
     auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
         if (p.plane) return launch_plane_f32(all, p, st, inverse, in64, mode, pass, s);
@@ -512,7 +501,7 @@ ibs_status solve_poisson(ibs_plan plan, const double *b, double *phi, void *work
     const State st = state_in(p, work, IBS_OP_POISSON, 1);
     if (p.desc.precision != IBS_FP64) {
         if (phi == b) { set_error("the refined path needs phi distinct from b"); return IBS_ERR_INVALID_ARG; }
-        ibs_status v = check_refined(p, 1, default_passes(p, true), st);
+        ibs_status v = check_refined(default_passes(p, true));
         if (v != IBS_OK) return v;
     }
     ibs_status r = compat_begin(p, b, st, s);
@@ -594,7 +583,7 @@ ibs_status solve_helmholtz_batch(ibs_plan plan, int32_t ncomp, const int32_t *co
             W2[q] = W1[q] + stride;
             W3[q] = W2[q] + stride;
         }
-        ibs_status v = check_refined(p, ncomp, default_passes(p, false), st);
+        ibs_status v = check_refined(default_passes(p, false));
         if (v != IBS_OK) return v;
         return run_refined(p, ss, W1, W2, W3, st, false, default_passes(p, false), s);
     }

@@ -74,7 +74,7 @@ hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bo
 {
     const int *skip = pass >= 2 ? st.done : nullptr;
     const bool upd = mode == 2 || mode == 4;
-    double *red = upd ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
+    double *red = upd ? st.upd : nullptr;
     const double *scale = upd ? st.scale : nullptr;
     const int stride = (int)update_slots(p);
     const bool exact = ss.j[0].op == IBS_OP_POISSON;   // a set's jobs are of one kind

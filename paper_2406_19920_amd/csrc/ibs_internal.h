@@ -75,6 +75,7 @@ constexpr int RESID_SLOTS = 4096;    // max blocks of the residual() norm reduct
 constexpr int FFT_RW = 16;           // rows per block of the fast x transforms
 constexpr int MAX_PASSES = 8;        // most refinement passes a solve may take (max_iter)
 constexpr int MAX_PLANES = 1024;     // largest nz a plan accepts
+constexpr int REFINED_MAX = 512;     // largest nx and nz of a refined plan
 // Smallest cell width a plan accepts, as a fraction of the domain length
 // along that axis.  The operators' condition numbers grow as the inverse
 // square of it: below about 1e-7 (tanh stretching beyond beta = 8 at 64
@@ -103,13 +104,13 @@ struct State {
     int *done = nullptr;       // per job: refinement stop flags
     int *incompat = nullptr;   // per job: strict compatibility check failed
     double *compat = nullptr;  // compatibility partials (2 per block)
-    double *red = nullptr;     // refinement update partials, then residual() partials
-    size_t red_count = 0;      // doubles in red
-    size_t upd_region = 0;     // doubles of red one refinement pass takes
-    double *bmax = nullptr;    // per job: largest magnitude of the first pass's pencil data
+    double *red = nullptr;     // residual() partials
+    double *upd = nullptr;     // update partials of the current refinement pass (a work field)
+    float *bmax = nullptr;     // per job: largest magnitude of the first pass's pencil data
                                // per z-mode and 16-wide x-tile (bmax_slots() each)
     double *scale = nullptr;   // per job: power of two sigma the refinement passes scale
                                // their FP32 residuals by
+    double *totals = nullptr;  // per refinement pass and job: its update sums (2)
 };
 
 // Kernel classes for the optional live profile (HIP events around launches).
@@ -240,7 +241,6 @@ inline int bmax_slots(const Plan &p) { return p.nz * (p.nx / 16); }
 
 // Workspace of one solve call: the work fields and the state after them.
 size_t field_bytes_for(const Plan &p, int op, int ncomp);
-size_t state_bytes_for(const Plan &p, int op, int ncomp);
 size_t work_bytes_for(const Plan &p, int op, int ncomp);
 State state_in(const Plan &p, void *work, int op, int ncomp);
 
@@ -347,10 +347,9 @@ struct SplitSet {
 // Kernels of pass >= 2 return at once for jobs whose stop flag is set.
 hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64,
                               int mode, int pass, hipStream_t s);
-// Update partials (pairs) one job writes per refinement pass, and the
-// doubles one pass of ncomp jobs takes (jobs update_slots() apart).
+// Update partials (pairs) one job writes per refinement pass to st.upd (jobs
+// update_slots() apart).
 size_t update_slots(const Plan &p);
-inline size_t update_region(const Plan &p, int ncomp) { return 2 * update_slots(p) * ncomp; }
 hipError_t launch_split_zgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass,
                               hipStream_t s);
 // pass: refinement pass (0 records the rhs mean; later passes steer the

@@ -83,7 +83,7 @@ hipError_t launch_plane_f32(const SplitSet &ss, const Plan &p, const State &st, 
         return in64 ? go<double, float, false, 0>(f, p.nx, p.ny, p.nz, s, nullptr, 0, skip)
                     : go<float, float, false, 0>(f, p.nx, p.ny, p.nz, s, nullptr, 0, skip);
     const bool upd = mode == 2 || mode == 4;
-    double *red = upd ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
+    double *red = upd ? st.upd : nullptr;
     const double *scale = upd ? st.scale : nullptr;
     const int stride = (int)update_slots(p);
     switch (mode) {

@@ -833,7 +833,7 @@ __global__ __launch_bounds__(256) void residual_f32_kernel(SplitSet ss, int nx, 
 }
 
 // After refinement pass p >= 1, one block per job sums the update partials of
-// pass p (and of pass p-1 when p >= 2) in a fixed order.  rel_correction =
+// pass p in a fixed order (and keeps the sums for pass p+1).  rel_correction =
 // ||d_p|| / ||x||; the error of the iterate is predicted as rel_correction
 // times the last observed contraction ||d_p|| / ||d_{p-1}|| (d_0 = the
 // first-pass solution, so the ratio is 1 at p = 1).  The report is written
@@ -860,8 +860,8 @@ static __device__ double2 sum_pairs(const double *r, int n)
     return t;
 }
 
-__global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const double *__restrict__ red_last,
-                                                           const double *__restrict__ red_prev,
+__global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const double *__restrict__ red,
+                                                           double *__restrict__ totals,
                                                            int count, int pass, double tol,
                                                            int *__restrict__ done)
 {
@@ -884,14 +884,18 @@ __global__ __launch_bounds__(256) void refine_check_kernel(SplitSet ss, const do
     }
     if (pass >= 2 && done[job]) return;     // stopped earlier: report stands
     const size_t off = (size_t)job * count * 2;
-    const double2 last = sum_pairs(red_last + off, count);
+    const double2 last = sum_pairs(red + off, count);
     double rprev = 1.0;
-    if (red_prev) {
-        const double2 prev = sum_pairs(red_prev + off, count);
+    if (pass >= 2) {
+        const double *t = totals + 2 * ((pass - 2) * STATE_JOBS + job);
+        const double2 prev = make_double2(t[0], t[1]);
         rprev = !(isfinite(prev.x) && isfinite(prev.y)) ? __builtin_nan("")
                                                         : (prev.y > 0.0 ? sqrt(prev.x / prev.y) : 0.0);
     }
     if (threadIdx.x == 0) {
+        double *t = totals + 2 * ((pass - 1) * STATE_JOBS + job);
+        t[0] = last.x;
+        t[1] = last.y;
         // a non-finite norm (a NaN or infinity in the data) predicts NaN,
         // which never meets tol
         const bool finite = isfinite(last.x) && isfinite(last.y) && isfinite(rprev);
@@ -974,13 +978,12 @@ static void launch_x_nb(const SplitSet &ss, const Plan &p, const b8 *qs, double 
 hipError_t launch_split_xgemm(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64,
                               int mode, int pass, hipStream_t s)
 {
-    // the caller (run_refined) has checked the mode, pass and state size
+    // the caller (run_refined) has checked the mode and pass
     const int *skip = pass >= 2 ? st.done : nullptr;
     dim3 grid;
     xgemm_grid(ss, p, grid);
-    // each refinement pass keeps its update partials in a region of its own
     const bool upd = mode == 2 || mode == 4;
-    double *red = st.red + (upd ? (size_t)(pass - 1) * st.upd_region : 0);
+    double *red = upd ? st.upd : nullptr;
     const double *scale = upd ? st.scale : nullptr;   // the residuals' sigma
     const size_t *tab = inverse ? p.lay.sx_inv : p.lay.sx_fwd;
     const b8 *qs = reinterpret_cast<const b8 *>(blob_ptr(p, tab[XK_P]));
@@ -1084,13 +1087,13 @@ int residual_tiles(const Plan &p)
 // bfloat16 exponent range whatever the rhs's own magnitude.  Scaling by a
 // power of two is exact: it changes no rounding unless a value would
 // otherwise leave that range.  One block per job, a fixed reduction order.
-__global__ __launch_bounds__(256) void residual_scale_kernel(const double *__restrict__ bmax, int slots,
+__global__ __launch_bounds__(256) void residual_scale_kernel(const float *__restrict__ bmax, int slots,
                                                              double *__restrict__ scale)
 {
     __shared__ double sm[4];
     const int job = blockIdx.x;
     double m = 0.0;
-    for (int q = threadIdx.x; q < slots; q += blockDim.x) m = fmax(m, bmax[(size_t)job * slots + q]);
+    for (int q = threadIdx.x; q < slots; q += blockDim.x) m = fmax(m, (double)bmax[(size_t)job * slots + q]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = fmax(m, __shfl_xor(m, d, 64));
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
@@ -1148,9 +1151,7 @@ size_t update_slots(const Plan &p)
 
 hipError_t launch_refine_check(const SplitSet &ss, const Plan &p, const State &st, int pass, hipStream_t s)
 {
-    const double *last = pass >= 1 ? st.red + (size_t)(pass - 1) * st.upd_region : nullptr;
-    const double *prev = pass >= 2 ? st.red + (size_t)(pass - 2) * st.upd_region : nullptr;
-    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, last, prev, (int)update_slots(p),
+    hipLaunchKernelGGL(refine_check_kernel, dim3(ss.n), dim3(256), 0, s, ss, st.upd, st.totals, (int)update_slots(p),
                        pass, p.desc.tol, st.done);
     return hipGetLastError();
 }

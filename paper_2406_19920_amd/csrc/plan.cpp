@@ -682,7 +682,7 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
         set_error("tol must not be NaN");
         return IBS_ERR_INVALID_ARG;
     }
-    if (d.precision != IBS_FP64 && (d.nx % 32 || d.nz % 32 || d.nx > 512 || d.nz > 512)) {
+    if (d.precision != IBS_FP64 && (d.nx % 32 || d.nz % 32 || d.nx > REFINED_MAX || d.nz > REFINED_MAX)) {
         set_error("the refined path needs nx and nz to be multiples of 32, at most 512");
         return IBS_ERR_UNSUPPORTED;
     }

@@ -93,7 +93,7 @@ struct TriParams {
     // the FP64 lane's tiles by its own launch), from which the refinement
     // passes take the power of two sigma that scales their FP32 residuals;
     // those passes then steer the mean in sigma units
-    double *bmax;          // first pass: the maxima, or null
+    float *bmax;           // first pass: the maxima, or null
     const double *scale;   // later passes: per job sigma, or null (1)
 };
 
@@ -290,7 +290,7 @@ __global__ __launch_bounds__((TA * P + 63) / 64 * 64, (tri_waves<R, P, M, TA>())
         if (tid < TA / 16) {
 #pragma unroll
             for (int w = 0; w < NW; ++w) m = fmaxf(m, mx_sm[w]);
-            tp.bmax[((size_t)job * tp.nz + c) * (nx / 16) + a0 / 16 + tid] = (double)m;
+            tp.bmax[((size_t)job * tp.nz + c) * (nx / 16) + a0 / 16 + tid] = m;
         }
     }
     __syncthreads();
