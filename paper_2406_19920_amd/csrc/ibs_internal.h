@@ -292,7 +292,7 @@ struct FsStage {
     double alpha, beta, gamma, zeta, dt, re;
     const double *u, *v, *w, *p;          // u^{n-1}, p^{n-1}
     double *nu, *nv, *nw;                 // in: N of the stage before (zeta != 0); out: N(u^{n-1})
-    double *ue, *ve, *we;                 // u^e (eq. a), one after the other
+    double *ue, *ve, *we;                 // u^e (eq. a)
     double *ru, *rv, *rw;                 // Helmholtz right-hand sides (eq. e)
     const double *markers, *ud, *dvol;    // immersed boundary: X_eta, U^d, dV_eta
     double *force;                        // F at the markers, or null
@@ -300,7 +300,6 @@ struct FsStage {
 };
 hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st);
 hipError_t launch_ibm(const Plan &p, const FsStage &s, hipStream_t st);
-bool ibm_from_rhs(const Plan &p, const FsStage &s);   // u^e is not written
 
 // rhs += the contribution of inhomogeneous wall data lo, hi ([nz][nx]).
 hipError_t launch_wall_data(const Plan &p, int op, double c, const double *lo, const double *hi,

@@ -7,7 +7,7 @@
 // together with the Helmholtz right-hand side without the forcing,
 //   r = u^e - c L u,  c = beta dt / Re                             (eq. e)
 // and N(u) itself (kept for the next stage's zeta term); u^e is written only
-// where markers interpolate it as a field (ibm_from_rhs()).  N is the
+// when markers will interpolate it.  N is the
 // convective term in divergence form, each product formed on the face or
 // edge where its derivative needs it from arithmetic means of the
 // neighbouring values; with walls, v = 0 on the wall faces and no product
@@ -22,8 +22,6 @@
 // r += dt F w dV / (hx hy hz) at each support point (eq. d, the spreading
 // added straight into the Helmholtz right-hand side) by atomic adds, as
 // the paper's L1 does.  Needs a uniform spacing in y (as the paper's grid).
-// u^e = r + c L u is formed at the support points alone, from the right-hand
-// side and u, in a launch of its own before any marker adds to r.
 #include "ibs_internal.h"
 
 #include <algorithm>
@@ -51,9 +49,10 @@ static __device__ __forceinline__ int vrows(const FsGeo &g) { return g.py ? g.ny
 // one-point halo in x and y, so each plane of each field is read from HBM
 // once per block (plus the halo, which the neighbouring tiles on the same
 // XCD share in L2) instead of once per neighbour; the loads of plane k+2
-// are in flight while plane k is computed.  Bound by HBM in 10 to 13 streams:
-// 1.34 GB of a 256^3 stage in 316 us, with the previous N 1.75 GB in 368 us
-// (430 with loads, stores and wall rows under branches, where every use
+// are in flight while plane k is computed.  Bound by HBM in 10 to 16 streams:
+// 1.34 GB of a 256^3 stage in 316 us, with the previous N 1.75 GB in 368 us,
+// with u^e for markers 1.75 GB in 377 us and both 2.15 GB in 437 us
+// (368 was 430 with loads, stores and wall rows under branches, where every use
 // waited for all loads in flight).  N is stored and read past the caches
 // (non-temporal: the next use is a whole solve away), r is not.  With the
 // waits for stores gone as well (loads a whole plane ahead of the ring's
@@ -286,46 +285,19 @@ static __device__ __forceinline__ double roma3(double r)
     return 0.0;
 }
 
-// L u of a component at point (i, j, k) of its grid, as explicit_kernel forms
-// it (v's wall faces read as zero).
-static __device__ __forceinline__ double lap_at(const FsGeo &g, int comp, const double *__restrict__ f, int rows,
-                                                int i, int j, int k)
-{
-    const int ie = i + 1 < g.nx ? i + 1 : 0, iw = i > 0 ? i - 1 : g.nx - 1;
-    const int kt = k + 1 < g.nz ? k + 1 : 0, kb = k > 0 ? k - 1 : g.nz - 1;
-    const int jn = g.py ? (j + 1 < g.ny ? j + 1 : 0) : j + 1, js = g.py ? (j > 0 ? j - 1 : g.ny - 1) : j - 1;
-    auto F = [&](int kk, int jj, int ii) { return f[((size_t)kk * rows + jj) * g.nx + ii]; };
-    const double ihx = 1.0 / g.hx, ihz = 1.0 / g.hz, fc = F(k, j, i);
-    const double xz = (F(k, j, ie) - 2.0 * fc + F(k, j, iw)) * ihx * ihx +
-                      (F(kt, j, i) - 2.0 * fc + F(kb, j, i)) * ihz * ihz;
-    if (comp == 1) {
-        const double fn = !g.py && jn == g.ny ? 0.0 : F(k, jn, i), fs = !g.py && js == 0 ? 0.0 : F(k, js, i);
-        const int jm = j > 0 ? j - 1 : g.ny - 1;
-        return xz + ((fn - fc) * (1.0 / g.dyc[j]) - (fc - fs) * (1.0 / g.dyc[jm])) * (1.0 / g.dyf[j]);
-    }
-    const double iD = 1.0 / g.dyc[j];
-    const double fu = g.py || j + 1 < g.ny ? (F(k, jn, i) - fc) * (1.0 / g.dyf[j + 1]) : -fc * (2.0 * iD);
-    const double fl = g.py || j > 0 ? (fc - F(k, js, i)) * (1.0 / g.dyf[j]) : fc * (2.0 * iD);
-    return xz + (fu - fl) * iD;
-}
-
-// The lanes of a marker share the three axes' divisions and weights; the two
-// launches take 31 + 31 us for 18 529 markers in 256^3 (one thread per marker
-// reading u^e fields: 76 us, and 400 MB more for the explicit kernel to store,
-// 482 us instead of 427 at the time), bound by scattered accesses: order over the XCDs or
-// fewer instructions no longer change it.
-// STEP 0: F of every marker (to F[3 m + comp]) from u^e = r + c L u; 1: the
-// spreading of F into r; 2: both at once, u^e a field of its own.
+// The lanes of a marker share the three axes' divisions and weights: 35 us for
+// 18 529 markers in 256^3 (one thread per marker: 76 us), bound by scattered
+// accesses.  u^e is read as a field.  Recovering it at the support points from
+// r + c L u would save the explicit kernel 62 to 69 us of stores, but loses
+// up to c |L| roundings to the cancellation.
 struct IbmFields {
-    const double *u[3], *ue[3];
+    const double *ue[3];
     double *r[3];
-    double c;
 };
 constexpr int IBM_LANES = 32;
-template <int STEP>
 __global__ __launch_bounds__(256) void ibm_kernel(FsGeo g, double dt, int nm, const double *__restrict__ X,
                                                   const double *__restrict__ ud,
-                                                  const double *__restrict__ dvol, IbmFields fd, double *F_)
+                                                  const double *__restrict__ dvol, IbmFields fd, double *force)
 {
     const double vol = g.hx * g.hy * g.hz;
     const int lane = threadIdx.x % IBM_LANES;
@@ -346,23 +318,12 @@ __global__ __launch_bounds__(256) void ibm_kernel(FsGeo g, double dt, int nm, co
         const int ix = __shfl(it, c, IBM_LANES), iy = __shfl(it, 3 + b, IBM_LANES), iz = __shfl(it, 6 + a, IBM_LANES);
         const bool on = lane < 27 && iy >= 0 && iy < rows;
         const size_t o = ((size_t)iz * rows + iy) * g.nx + ix;
-        double F;
-        if constexpr (STEP == 1) {
-            F = F_[3 * m + comp];
-        } else {
-            double U = 0.0;
-            if constexpr (STEP == 2) {
-                if (on) U = fd.ue[comp][o] * w;
-            } else if (on && (comp != 1 || g.py || (iy > 0 && iy < g.ny))) {   // u^e = 0 on v's wall faces
-                U = (fd.r[comp][o] + fd.c * lap_at(g, comp, fd.u[comp], rows, ix, iy, iz)) * w;
-            }
+        double U = on ? fd.ue[comp][o] * w : 0.0;
 #pragma unroll
-            for (int d = IBM_LANES / 2; d >= 1; d >>= 1) U += __shfl_xor(U, d, IBM_LANES);
-            F = (ud[3 * m + comp] - U) / dt;
-            if (F_ && lane == 0) F_[3 * m + comp] = F;
-        }
-        if constexpr (STEP != 0)
-            if (on) atomicAdd(&fd.r[comp][o], F * w * (dt * dvol[m] / vol));
+        for (int d = IBM_LANES / 2; d >= 1; d >>= 1) U += __shfl_xor(U, d, IBM_LANES);
+        const double F = (ud[3 * m + comp] - U) / dt;
+        if (force && lane == 0) force[3 * m + comp] = F;
+        if (on) atomicAdd(&fd.r[comp][o], F * w * (dt * dvol[m] / vol));
     }
 }
 
@@ -374,18 +335,6 @@ static FsGeo fs_geo(const Plan &p)
     g.dyc = blob_ptr(p, p.lay.dyc);
     g.dyf = blob_ptr(p, p.lay.dyf);
     return g;
-}
-
-// Whether u^e at the markers comes from r + c L u instead of a field: that
-// saves the explicit kernel a quarter of its stores.  r and c L u cancel to
-// u^e, which costs it up to c |L| roundings of |u|: only up to 16 of them (a
-// step at an advective Courant number has 0.01 to 1), and only with room for
-// F between the two launches (force, or u^e's unused fields).
-bool ibm_from_rhs(const Plan &p, const FsStage &s)
-{
-    const double hy = p.desc.ly / p.ny, c = std::fabs(s.beta * s.dt / s.re);
-    return c * 4.0 * (1.0 / (p.hx * p.hx) + 1.0 / (hy * hy) + 1.0 / (p.hz * p.hz)) <= 16.0 &&
-           (s.force || s.nmarkers <= s.ve - s.ue);
 }
 
 hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st)
@@ -404,7 +353,7 @@ hipError_t launch_explicit(const Plan &p, const FsStage &s, hipStream_t st)
         hipLaunchKernelGGL(kernel, grid, dim3(ENT), 0, st, g, cf, s.u, s.v, s.w, s.p, s.nu, s.nv, s.nw,
                            s.ue, s.ve, s.we, s.ru, s.rv, s.rw, s.nu, s.nv, s.nw);
     };
-    s.nmarkers > 0 && !ibm_from_rhs(p, s) ? go(explicit_kernel<true>) : go(explicit_kernel<false>);
+    s.nmarkers > 0 ? go(explicit_kernel<true>) : go(explicit_kernel<false>);
     return hipGetLastError();
 }
 
@@ -412,19 +361,10 @@ hipError_t launch_ibm(const Plan &p, const FsStage &s, hipStream_t st)
 {
     if (s.nmarkers <= 0) return hipSuccess;
     const FsGeo g = fs_geo(p);
-    const IbmFields f{{s.u, s.v, s.w}, {s.ue, s.ve, s.we}, {s.ru, s.rv, s.rw}, s.beta * s.dt / s.re};
+    const IbmFields f{{s.ue, s.ve, s.we}, {s.ru, s.rv, s.rw}};
     constexpr int PER = 256 / IBM_LANES, MOST = 1 << 20;   // groups of lanes per block, blocks
     const dim3 grid(std::min(MOST, s.nmarkers / PER + (s.nmarkers % PER != 0)), 3), blk(256);
-    auto go = [&](auto kernel, double *F) {
-        hipLaunchKernelGGL(kernel, grid, blk, 0, st, g, s.dt, s.nmarkers, s.markers, s.ud, s.dvol, f, F);
-    };
-    if (ibm_from_rhs(p, s)) {
-        double *F = s.force ? s.force : s.ue;
-        go(ibm_kernel<0>, F);
-        go(ibm_kernel<1>, F);
-    } else {
-        go(ibm_kernel<2>, s.force);
-    }
+    hipLaunchKernelGGL(ibm_kernel, grid, blk, 0, st, g, s.dt, s.nmarkers, s.markers, s.ud, s.dvol, f, s.force);
     return hipGetLastError();
 }
 
