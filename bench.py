@@ -451,7 +451,6 @@ def run_batch_modes(steps, warmup, specs, label):
         ms = (time.perf_counter() - t0) * 1e3 / steps
         status = [j.solver.read_info(q).status for j in B.jobs for q in (0, 1, 2, 3)]
         out[mode] = {"value": B.cell_solves / (ms * 1e-3) / 1e6, "ms_per_launch": ms,
-                     "kernel_launches_per_replay": 5 if mode == "multigrid" else None,
                      "all_status_ok": all(st == 0 for st in status)}
         if mode == "graph":
             out[mode]["schedule"] = {"nlanes": B.schedule[0], "policy": ["balanced", "in_order"][B.schedule[1]]}

@@ -449,11 +449,13 @@ ibs_status ibs_plan_export(ibs_plan plan, int32_t table, double *out, size_t *n)
  * ibs_profile_read() synchronises on the recorded events and returns, for
  * kernel class `kernel`, the summed device time (ms), the launch count and
  * the summed algorithmic flops and HBM bytes of those launches (the work
- * the method needs, not counter readings).  Kernel classes: 0 x transform
- * (FP64 matrix cores), 1 z transform (FP64), 2 y tridiagonal (FP64),
- * 3 divergence, 4 correction, 5 residual, 6 x transform (split),
- * 7 z transform (split), 8 y tridiagonal (FP32 data), 9 refinement update,
+ * the method needs, not counter readings).  Kernel classes: 0 x transform,
+ * 1 z transform, 2 y tridiagonal (FP64 data),
+ * 3 divergence, 4 correction, 5 residual, 6 x transform, 7 z transform,
+ * 8 y tridiagonal (FP32 data), 9 refinement update (inverse x transform),
  * 10 explicit estimate of a Runge-Kutta stage, 11 immersed-boundary forcing.
+ * Where the x and z transforms run in one launch (periodic axes of up to 64
+ * points) it counts under the x transform, or under 9 for the last of a pass.
  * Any output pointer may be NULL. */
 ibs_status ibs_profile(ibs_plan plan, int32_t enable);
 ibs_status ibs_profile_read(ibs_plan plan, int32_t kernel, double *ms, int64_t *launches,

@@ -1,8 +1,10 @@
 // Line lengths the fast transforms (k_fft.h) are built for, as (N, R1, R2):
 // N = R1 R2, R1 points of real data in stage A, R2 complex ones in stage B.
-// Every multiple of 16 up to 256, and those above up to 512 whose factors
-// keep both stages within 32 real or 20 complex values per thread.  Stage A
-// takes the larger factor: real data hold half as many registers per point.
+// Every multiple of 16 up to 512 without a prime factor above 13 (272, 304, 368,
+// 464 and 496 have one and take the dense products: such a stage is summed
+// directly), so that both stages stay within 32 real or 20 complex values per
+// thread.  Stage A takes the larger factor: real data hold half as many
+// registers per point.
 #pragma once
 
 #define IBS_FFT_SIZES_32(X)                                                                              \

@@ -134,9 +134,12 @@ template <typename TS, typename T, int N> constexpr int fft_cw()
 // eighth further in from XCD to XCD lest all meet in one channel.  Against
 // tiles in turn: 384^3 FP64 2.75 -> 2.66 ms for three solves, 512x384x384
 // 3.86 -> 3.73, refined 5.69 -> 5.46, 256^3 refined and FP64 equal.  FP64
-// planes whose pitch is a multiple of 256 rows conflict all the same and
-// lose (512x256x256 1.65 -> 1.68 ms): those take the tiles in turn (runs
-// = 0).
+// fields of a multiple of 256 rows take the tiles in turn (runs = 0); us for
+// three solves, in turn / in runs: 512x256x256 1627 / 1661, 256x512x256 1609 /
+// 1643, 128x256x512 723 / 730, 256^3 728 / 729 (v alone 221 / 228), but
+// 400x256x400 2232 / 2204 and 128x512x384 1083 / 1064.  The pitch of a plane
+// does not decide it: 512x128x384, its planes as long as 256 x 256 ones, takes
+// 1153 / 1127.
 // LDS [k1][n2][column], a pad line per k1 so that the two halves of a wave
 // (k1 apart) use different banks.
 // TS: stored type, T: arithmetic.

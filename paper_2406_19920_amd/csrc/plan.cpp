@@ -648,7 +648,7 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
         set_error("nx and nz must be multiples of 16 in [16, 1024]");
         return IBS_ERR_UNSUPPORTED;
     }
-    if (d.ny < 2 || d.ny > 768) {   // the tridiagonal shapes cover up to 800 system rows
+    if (d.ny < 2 || d.ny > 768) {   // 768: the most system rows of the tridiagonal shapes (k_tridiag.hip)
         set_error("ny must be in [2, 768]");
         return IBS_ERR_UNSUPPORTED;
     }

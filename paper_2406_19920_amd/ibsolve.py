@@ -289,7 +289,7 @@ def ibs_batch_build(jobs, nlanes: int, policy: int = IBS_SCHED_BALANCED) -> int:
 
 
 def ibs_batch_build_multigrid(jobs) -> int:
-    """Multi-grid batch: one persistent launch per solve stage over all jobs."""
+    """Multi-grid batch: stage launches over the fields of many jobs."""
     arr = (ibs_batch_job * len(jobs))(*jobs)
     h = ctypes.c_void_p()
     _check(lib.ibs_batch_build_multigrid(arr, len(jobs), ctypes.byref(h)), "ibs_batch_build_multigrid")
