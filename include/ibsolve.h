@@ -399,8 +399,9 @@ ibs_status ibs_batch_autotune(const ibs_batch_job *jobs, int32_t njobs, int32_t 
  * y tridiagonal, inverse z, inverse x; Section 2.3.3, items S2.1-S2.2) run
  * over device tables of fields.  Fields of equal grids with fast transforms
  * are chained through the single-grid kernels, five launches per up to 128 MB
- * of fields; the rest (stretched axes, few or short fields) share ONE
- * persistent launch per stage,
+ * of fields, where that is predicted to be faster; the rest (stretched axes,
+ * few or short fields, small groups beside others) share ONE persistent launch
+ * per stage,
  * whose waves walk a device work list of tiles drawn from all grids (plain
  * FP64 matrix-core transforms, Thomas pencils).  FP64 arithmetic throughout:
  * results agree with solve_poisson / solve_helmholtz_batch to rounding, not

@@ -207,6 +207,21 @@ ibs_status ibs_batch_destroy(ibs_batch batch)
 // one work list per stage kind (x transforms: tiles of rows x modes; z
 // transforms: tiles of modes x columns; pencils: 64-pencil runs of a plane),
 // the plain transform tables of every (plan, axis, kind, direction) used.
+//
+// Chains run one after the other, and before the stage kernels, which have to
+// run for the rest whatever it holds: beside a rest, or in many small groups,
+// they can take longer than the stage kernels alone (64^3 duct, four jobs and
+// one of 32^3: 188 us, stage kernels 137).  So the groups that become chains
+// are chosen by predicted time, fitted to 430 mixes of 32 to 272 points, 17 to
+// 512 rows and 8 to 200 MB (5% rms):
+//   stage kernels  35 us + 0.62 a row of the longest column
+//                  + a field's MB times 0.7 (times 64 / nx, rounded up by the
+//                    64-pencil runs) + 0.0103 (nx + nz)
+//                  + 0.94 for each MB beyond 46 (right-hand sides, solutions,
+//                    work fields and factors then exceed the Infinity Cache)
+//   chain          6.6 us a launch + 1.37 a MB
+// largest groups first, as many as give the least time, and none unless that is
+// 5% below the stage kernels alone.
 constexpr size_t MG_CHAIN_BYTES = size_t(128) << 20;
 constexpr size_t MG_GROUP_BYTES = size_t(8) << 20;
 constexpr int MG_THOMAS_ROWS = 16;
@@ -278,7 +293,6 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
     struct Fast { const Plan *p; FieldJob job; bool poisson; };
     typedef std::tuple<int, int, int, bool, bool, bool, bool> Key;
     std::map<Key, std::vector<Fast>> groups;
-    std::map<Key, size_t> group_bytes;
     auto key_of = [](const Plan &p, int xk, int zk) {
         return Key(p.nx, p.ny, p.nz, p.wx, p.wz, xk == XK_F, zk == XK_F);
     };
@@ -319,14 +333,59 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
                 if (it->field != r.field || it->at != r.at) chains_ok = false;
         }
     }
-    for (int q = 0; q < njobs && chains_ok; ++q) {
+    // bytes of the groups, and what the stage kernels have whatever is chained
+    struct Load { double mb = 0.0, us = 0.0; int ny = 0; };   // MB, their time, longest column
+    struct Group { size_t bytes = 0; Load load; double chain_us = 0.0; };
+    auto add = [](Load &to, const Load &l) {
+        to.mb += l.mb;
+        to.us += l.us;
+        to.ny = std::max(to.ny, l.ny);
+    };
+    std::map<Key, Group> all_groups;
+    Load rest;
+    for (int q = 0; q < njobs; ++q) {
         const ibs_batch_job &j = jobs[q];
         const Plan &p = *reinterpret_cast<const Plan *>(j.plan);
         for (int k = 0; k < (j.op == IBS_OP_POISSON ? 1 : j.ncomp); ++k) {
             int kind, xk, zk;
             kinds_of(j, k, kind, xk, zk);
-            if (fast_plan(p)) group_bytes[key_of(p, xk, zk)] += (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double);
+            const size_t bytes = (size_t)p.nz * p.rows[kind] * p.nx * sizeof(double);
+            const double mb = (double)bytes / (1 << 20);
+            const Load l{mb, mb * (0.7 * ((p.nx + 63) / 64 * 64) / p.nx + 0.0103 * (p.nx + p.nz)), p.ny};
+            if (!chains_ok || !fast_plan(p)) {
+                add(rest, l);
+                continue;
+            }
+            Group &g = all_groups[key_of(p, xk, zk)];
+            g.bytes += bytes;
+            add(g.load, l);
+            g.chain_us = 6.6 * (p.plane ? 3 : 5) * (double)((g.bytes + MG_CHAIN_BYTES - 1) / MG_CHAIN_BYTES) +
+                         1.37 * g.load.mb;
         }
+    }
+    std::vector<std::pair<Key, Group>> order;   // those that may be chains, largest first
+    for (const auto &g : all_groups) {
+        if (g.second.bytes >= MG_GROUP_BYTES) order.push_back(g);
+        else add(rest, g.second.load);
+    }
+    std::stable_sort(order.begin(), order.end(), [](const auto &a, const auto &c) { return a.second.bytes > c.second.bytes; });
+    auto stages_us = [&](size_t chained) {
+        Load l = rest;
+        for (size_t g = chained; g < order.size(); ++g) add(l, order[g].second.load);
+        return l.ny ? 35.0 + 0.62 * l.ny + l.us + 0.94 * std::max(0.0, l.mb - 46.0) : 0.0;
+    };
+    std::map<Key, bool> chained;
+    {
+        double chains_us = 0.0, least = 0.95 * stages_us(0);
+        size_t n = 0;
+        for (size_t g = 0; g < order.size(); ++g) {
+            chains_us += order[g].second.chain_us;
+            if (const double us = chains_us + stages_us(g + 1); us < least) {
+                least = us;
+                n = g + 1;
+            }
+        }
+        for (size_t g = 0; g < n; ++g) chained[order[g].first] = true;
     }
     for (int q = 0; q < njobs; ++q) {
         const ibs_batch_job &j = jobs[q];
@@ -336,7 +395,7 @@ ibs_status ibs_batch_build_multigrid(const ibs_batch_job *jobs, int32_t njobs, i
         for (int k = 0; k < nc; ++k) {
             int kind, xk, zk;
             kinds_of(j, k, kind, xk, zk);
-            if (fast_plan(p) && group_bytes[key_of(p, xk, zk)] >= MG_GROUP_BYTES) {
+            if (fast_plan(p) && chained.count(key_of(p, xk, zk))) {
                 Fast f{&p, FieldJob{}, pois};
                 f.job.in = j.rhs[k];
                 f.job.out = j.x[k];
