@@ -87,12 +87,16 @@ constexpr double MIN_CELL_FRACTION = 1e-7;
 // Refined path: pressure pencils whose condition bound 1 + g/|s| (g the
 // Gershgorin bound of the y operator, s the pencil's transverse eigenvalue)
 // exceeds this are solved with FP64 arithmetic (the FP64 lane); the rest in
-// FP32, whose rounding the refinement then removes.
-constexpr double LANE64_KAPPA = 1000.0;
+// FP32, whose rounding the refinement then removes.  A solve's error after two
+// passes follows the square of the largest bound left to FP32.  Poisson solves,
+// limit 1000 / 500: 192x160x96 (uniform) 3.3e-12 / 1.0e-12, 512x64x128 1.6e-11 /
+// 8e-13, 256x128x128 3.9e-11 / 1.4e-11, 256^3 9.9e-12 / 5.5e-12; time equal but
+// for 256^3 with beta = 2, 395 / 399 us.
+constexpr double LANE64_KAPPA = 500.0;
 // Cyclic pencils (periodic y) lose more to FP32 rounding at the same bound
-// (the reduced system's last step divides by EA + EB + EC, which cancels
-// towards the near-null constant mode): measured 1e-10 after two passes at
-// a bound of 935 on a 96 x 96 x 64 grid; their lane takes bounds above 100.
+// (the reduced system's last step divides by a sum that cancels towards the
+// near-null constant mode): measured 1e-10 after two passes at a bound of 935
+// on a 96 x 96 x 64 grid; their lane takes bounds above 100.
 constexpr double LANE64_KAPPA_CYCLIC = 100.0;
 // Smallest constant buffer a plan reports (const_bytes): fast transforms need
 // only a few KB of tables, where the dense factors of a 64-point axis alone
