@@ -1,9 +1,11 @@
 // C ABI of the solver library: validation, error layer, stage sequencing.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <string>
 
+#include "fft_sizes.h"
 #include "ibs_internal.h"
 
 namespace ibs {
@@ -337,16 +339,6 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
     // partial sums, 16 bytes for every 16 rows (or 128 bytes for 512) of at
     // least 128 bytes each, times three jobs; the check reads them at once
     st.upd = reinterpret_cast<double *>(D1[0] == W1[0] ? W2[0] : W1[0]);
-    // with p.plane the x transform's launch includes z's
-    auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
-        if (p.plane) return launch_plane_f32(all, p, st, inverse, in64, mode, pass, s);
-        return p.fx ? launch_fft_x32(all, p, st, inverse, in64, mode, pass, s)
-                    : launch_split_xgemm(all, p, st, inverse, in64, mode, pass, s);
-    };
-    auto zform = [&](const SplitSet &all, bool inverse, int pass) {
-        return p.fz ? launch_fft_z32(all, p, st, inverse, pass, s)
-                    : launch_split_zgemm(all, p, st, inverse, pass, s);
-    };
     JobSet js{};
     js.n = ss.n;
     void *info[4];
@@ -360,6 +352,18 @@ static ibs_status run_refined(Plan &p, SplitSet ss, float *const *W1, float *con
         js.j[q].zk = ss.j[q].zk;
         js.j[q].c = ss.j[q].c;
     }
+    // forward transforms in FP64 arithmetic: the rule's reasons in fft_sizes.h
+    const bool exact = poisson || !fp32_pencils(js, p) || p.nx + p.nz <= FFT_F64_FORWARD_SUM;
+    // with p.plane the x transform's launch includes z's
+    auto xform = [&](const SplitSet &all, bool inverse, bool in64, int mode, int pass) {
+        if (p.plane) return launch_plane_f32(all, p, st, inverse, in64, mode, pass, s);
+        return p.fx ? launch_fft_x32(all, p, st, inverse, exact, in64, mode, pass, s)
+                    : launch_split_xgemm(all, p, st, inverse, in64, mode, pass, s);
+    };
+    auto zform = [&](const SplitSet &all, bool inverse, int pass) {
+        return p.fz ? launch_fft_z32(all, p, st, inverse, exact, pass, s)
+                    : launch_split_zgemm(all, p, st, inverse, pass, s);
+    };
     // With a second pass to come, the first iterate is only FP32-accurate
     // and the second pass rewrites x: keep it in FP32 in W3 until then.
     const bool x32 = passes >= 2;

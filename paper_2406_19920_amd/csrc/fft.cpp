@@ -18,7 +18,7 @@ static FftJob fft_job(const Plan &p, bool z_axis, bool inverse, int rows, int yk
     const BlobLayout &L = p.lay;
     FftJob f{};
     const bool faces = axis_form(z_axis ? p.wz : p.wx, kind) == fft::AX_FACES;
-    if (faces) f.tw = table(p, z_axis ? L.ftz_face : L.ftx_face);
+    if (faces) f.tw = table(p, f32 || inverse ? (z_axis ? L.ftz_face : L.ftx_face) : (z_axis ? L.ftz_face64 : L.ftx_face64));
     else if (f32 && !inverse) f.tw = table(p, z_axis ? L.ftz_fwd32 : L.ftx_fwd32);
     else f.tw = table(p, z_axis ? (inverse ? L.ftz_inv : L.ftz_fwd) : (inverse ? L.ftx_inv : L.ftx_fwd));
     if (f32 && !inverse) f.rot = table(p, z_axis ? L.frz_fwd32 : L.frx_fwd32);
@@ -69,15 +69,14 @@ hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, 
     return z_axis ? launch_fft_z64(t, nz, ny, nx, inverse, ax, s) : launch_fft_x64(t, nx, ny, nz, inverse, ax, s);
 }
 
-hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
-                          int pass, hipStream_t s)
+hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool exact, bool in64,
+                          int mode, int pass, hipStream_t s)
 {
     const int *skip = pass >= 2 ? st.done : nullptr;
     const bool upd = mode == 2 || mode == 4;
     double *red = upd ? st.upd : nullptr;
     const double *scale = upd ? st.scale : nullptr;
     const int stride = (int)update_slots(p);
-    const bool exact = ss.j[0].op == IBS_OP_POISSON;   // a set's jobs are of one kind
     for (int ax = 0; ax < 3; ++ax) {
         FftSet f{};
         for (int q = 0; q < ss.n; ++q) {
@@ -100,9 +99,9 @@ hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bo
     return hipSuccess;
 }
 
-hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s)
+hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool exact, int pass,
+                          hipStream_t s)
 {
-    const bool exact = ss.j[0].op == IBS_OP_POISSON;
     for (int ax = 0; ax < 3; ++ax) {
         FftSet f{};
         for (int q = 0; q < ss.n; ++q) {

@@ -18,20 +18,29 @@
 // Those the fused x-z transforms (k_plane.h) are built for.
 #define IBS_PLANE_SIZES(X) X(16, 4, 4) X(32, 8, 4) X(48, 8, 6) X(64, 8, 8)
 
-// FP32 fields (refined path): a pressure solve's forward transforms and all
-// lines of up to this length take FP64 arithmetic, the others FP32.
+// FP32 fields (refined path): lines of up to FFT_F64_ARITH_MAX points take FP64
+// arithmetic, longer ones FP32; in forward transforms longer ones take FP64
+// too where the solve amplifies what they leave on the lowest modes (a
+// pressure solve; Helmholtz pencils of a condition bound beyond FP32's), and
+// where both axes together have at most FFT_F64_FORWARD_SUM points.
 // The three-term bfloat16 products these transforms replace carried a line's
 // result to within a few roundings whatever its length.  FP32 butterflies
 // forward spread eps of the whole line over every mode, and the pressure
 // solve multiplies what falls on the lowest by 1 / lambda: refined Poisson
 // solves ended up to 2.7 times further from the FP64 solution than with the
 // products (416x32x64), with walls in x up to 6 times (512x32x64); with FP64
-// they end as near or up to 20 times nearer.  Helmholtz solves (largest factor
-// 1) and inverse transforms do not amplify it: those end 1.5 to 6 times nearer
-// in FP32 already.  At 256^3 FP64 costs a pressure z transform 28 us
-// instead of 24 and an x transform 26 instead of 22, up to 64 points nothing
-// (the pass is bound by memory).
+// they end as near or up to 20 times nearer.  A Helmholtz solve multiplies by
+// 1 / (1 + c lambda), at most 1, but at c lambda beyond FP32's bound all that is
+// left of its solution are those modes: up to 4.3 times further (512x48x64,
+// walls in x, c = 1) in FP32, in FP64 at 0.03 to 0.4 of the products' error.
+// At small c longer lines end 1.05 to 6 times nearer in FP32 already, short ones
+// further (96^3 1.45 times, 128^3 1.37, 192x160x96 1.06; in FP64 0.75, 0.77,
+// 0.5), hence FFT_F64_FORWARD_SUM.  Inverse transforms do not amplify.
+// Cost: up to 64 points nothing (the pass is bound by memory), a 256^3 pressure
+// z transform 28 us instead of 24 and x 26 instead of 22, three Helmholtz
+// solves 104 -> 107 us at 96^3, 151 -> 158 at 128^3.
 namespace ibs {
 constexpr int FFT_F64_ARITH_MAX = 64;
+constexpr int FFT_F64_FORWARD_SUM = 288;
 constexpr int PLANE_MAX = 64;   // longest line of the fused x-z transforms
 }

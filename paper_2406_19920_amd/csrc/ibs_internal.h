@@ -48,6 +48,7 @@ struct BlobLayout {
     size_t ftx_fwd, ftx_inv, frx_fwd, frx_inv, ftx_face;
     size_t ftz_fwd, ftz_inv, frz_fwd, frz_inv, ftz_face;
     size_t ftx_fwd32, frx_fwd32, ftz_fwd32, frz_fwd32;   // the forward ones in FP32 (refined path, long lines)
+    size_t ftx_face64, ftz_face64;   // the faces' in FP64 (the others unless refined, long lines)
     size_t lam_x[NUM_XK], lam_z[NUM_XK];   // eigenvalues (double) per x / z kind
     size_t lo[NUM_KINDS], di[NUM_KINDS], up[NUM_KINDS];  // y operator rows
     size_t wy;               // Delta_j (pressure weights), ny doubles
@@ -283,6 +284,9 @@ hipError_t launch_tridiag_f64(const JobSet &js, const Plan &p, const State &st, 
 size_t tri_entry_bytes();
 void tri_entry_fill(void *to, const Plan &p, const FieldJob &job, bool poisson);
 hipError_t launch_tridiag_table(const void *entries, int n, int nx, int ny, int nz, hipStream_t s);
+// Whether the condition numbers of all Helmholtz pencils of the jobs are
+// provably small enough for FP32 arithmetic (refined path).
+bool fp32_pencils(const JobSet &js, const Plan &p);
 hipError_t launch_divergence(const Plan &p, const double *u, const double *v,
                              const double *w, double *b, double scale, hipStream_t s);
 hipError_t launch_correct(const Plan &p, const double *phi, double *u, double *v,
@@ -378,10 +382,12 @@ size_t fft_entry_bytes();
 void fft_entry_fill(void *to, const Plan &p, const FieldJob &job, bool z_axis, bool inverse);
 hipError_t launch_fft_table(const void *entries, int n, int nx, int ny, int nz, bool z_axis, bool inverse, bool walls,
                             int kind, hipStream_t s);
-// Refined path: in64, mode and pass as launch_split_xgemm().
-hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool in64, int mode,
-                          int pass, hipStream_t s);
-hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, int pass, hipStream_t s);
+// Refined path: in64, mode and pass as launch_split_xgemm(); exact: forward in
+// FP64 arithmetic whatever the length (fft_sizes.h).
+hipError_t launch_fft_x32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool exact, bool in64,
+                          int mode, int pass, hipStream_t s);
+hipError_t launch_fft_z32(const SplitSet &ss, const Plan &p, const State &st, bool inverse, bool exact, int pass,
+                          hipStream_t s);
 
 // Both transforms of short periodic lines in one launch (k_plane.h): plans
 // with p.plane only.  As the pairs of launches above, x and z in the order of

@@ -38,8 +38,8 @@
 
 namespace ibs {
 
-// Arithmetic type of FP32 fields' transforms (fft_sizes.h); EXACT: forward
-// transforms of a pressure solve.
+// Arithmetic type of FP32 fields' transforms; EXACT: forward ones in FP64
+// (fft_sizes.h).
 template <int N, bool EXACT> struct FftReal {
     typedef typename std::conditional<(EXACT || N <= FFT_F64_ARITH_MAX), double, float>::type type;
 };

@@ -21,7 +21,8 @@ hipError_t launch_fft_x32_fwd(const FftSet &js, int n, int rows, int nz, int ax,
     switch (n) {
 #define IBS_CASE(N, R1, R2)                                                                       \
     case N:                                                                                       \
-        if (ax == fft::AX_FACES) go<R1, R2, fft::AX_FACES, false>(js, rows, nz, in64, skip, s);   \
+        if (ax == fft::AX_FACES && exact) go<R1, R2, fft::AX_FACES, true>(js, rows, nz, in64, skip, s);   \
+        else if (ax == fft::AX_FACES) go<R1, R2, fft::AX_FACES, false>(js, rows, nz, in64, skip, s);      \
         else if (ax && exact) go<R1, R2, fft::AX_CENTRES, true>(js, rows, nz, in64, skip, s);     \
         else if (ax) go<R1, R2, fft::AX_CENTRES, false>(js, rows, nz, in64, skip, s);             \
         else if (exact) go<R1, R2, fft::AX_PERIODIC, true>(js, rows, nz, in64, skip, s);          \

@@ -16,7 +16,9 @@ static void one(const FftSet &js, int rows, int nx, const int *skip, hipStream_t
 template <int R1, int R2>
 static void go(const FftSet &js, int rows, int nx, bool inverse, int ax, bool exact, const int *skip, hipStream_t s)
 {
-    if (ax == fft::AX_FACES) one<R1, R2, true, fft::AX_FACES, false>(js, rows, nx, skip, s);   // its own inverse
+    // the faces' transform is its own inverse, in the direction's arithmetic
+    if (ax == fft::AX_FACES && exact && !inverse) one<R1, R2, true, fft::AX_FACES, true>(js, rows, nx, skip, s);
+    else if (ax == fft::AX_FACES) one<R1, R2, true, fft::AX_FACES, false>(js, rows, nx, skip, s);
     else if (inverse && ax) one<R1, R2, true, fft::AX_CENTRES, false>(js, rows, nx, skip, s);
     else if (inverse) one<R1, R2, true, fft::AX_PERIODIC, false>(js, rows, nx, skip, s);
     else if (ax && exact) one<R1, R2, false, fft::AX_CENTRES, true>(js, rows, nx, skip, s);

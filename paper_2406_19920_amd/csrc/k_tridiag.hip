@@ -62,6 +62,8 @@ static double helmholtz_kappa(const JobSet &js, const Plan &p)
     return kap;
 }
 
+bool fp32_pencils(const JobSet &js, const Plan &p) { return helmholtz_kappa(js, p) <= FP32_KAPPA; }
+
 // Launch shape by system size: padded partitions, or (periodic y) the
 // cyclic shapes, which need the exact row count.
 template <typename T, typename R>
@@ -133,7 +135,7 @@ static hipError_t launch_tridiag(const JobSet &js, const Plan &p, const State &s
     // removes anyway: FP32 data (refined path), Helmholtz, and pencil
     // condition numbers bounded by FP32_KAPPA.
     if constexpr (sizeof(T) == 4) {
-        if (!poisson && helmholtz_kappa(js, p) <= FP32_KAPPA) return launch_rows<T, float>(p, js, tp, n, s);
+        if (!poisson && fp32_pencils(js, p)) return launch_rows<T, float>(p, js, tp, n, s);
         // few tiles: FP64 arithmetic on all of them in one launch costs less
         // than the lane's launch on top of the FP32 one (us per pass, one
         // launch against both: 64^3 7 / 13, 128^3 15 / 17, 192x128x192 23 / 26,

@@ -902,9 +902,13 @@ ibs_status build_plan(const ibs_grid_desc &d, Plan *&out)
         {&L.frz_fwd, &az[0]->fft[2], false}, {&L.frz_inv, &az[0]->fft[3], f32z},
         {&L.ftx_face, p->wx ? &ax[XK_F]->fft[0] : &none, f32x},
         {&L.ftz_face, p->wz ? &az[XK_F]->fft[0] : &none, f32z},
+        {&L.ftx_face64, p->wx && f32x ? &ax[XK_F]->fft[0] : &none, false},
+        {&L.ftz_face64, p->wz && f32z ? &az[XK_F]->fft[0] : &none, false},
         {&L.ftx_fwd32, f32x ? &ax[0]->fft[0] : &none, true}, {&L.frx_fwd32, f32x ? &ax[0]->fft[2] : &none, true},
         {&L.ftz_fwd32, f32z ? &az[0]->fft[0] : &none, true}, {&L.frz_fwd32, f32z ? &az[0]->fft[2] : &none, true}};
     for (const FastTable &f : fast) *f.at = take((f.f32 ? sizeof(float) : sizeof(double)) * f.t->size());
+    if (!f32x) L.ftx_face64 = L.ftx_face;
+    if (!f32z) L.ftz_face64 = L.ftz_face;
     for (int k = 0; k < NUM_XK; ++k) L.lam_x[k] = k < nxk ? take(sizeof(double) * nx) : L.lam_x[0];
     for (int k = 0; k < NUM_XK; ++k) L.lam_z[k] = k < nzk ? take(sizeof(double) * nz) : L.lam_z[0];
     for (int kd = 0; kd < NUM_KINDS; ++kd) {

@@ -1,5 +1,6 @@
-"""Accuracy of refined pressure solves on y spacings that leave pencils of a
-large condition bound to FP32 arithmetic."""
+"""Accuracy of refined solves where FP32 arithmetic of the pencils or of the
+forward transforms shows: pressure pencils of a large condition bound, short
+lines, Helmholtz systems whose solution is mostly its lowest modes."""
 import numpy as np
 import pytest
 import torch
@@ -31,3 +32,29 @@ def test_pressure_error(shape, beta, bound):
         errs.append(float((S.poisson(b) - want).norm() / want.norm()))
         assert S.read_info(0).status == 0
     assert np.exp(np.mean(np.log(errs))) < bound, errs
+
+
+# bounds as above (eight right-hand sides; per component): short lines, a
+# condition bound of 630, and the sine transforms of faces and centres at c = 1
+@pytest.mark.parametrize("shape,beta,walls,c,smooth,bound", [
+    ((96, 100, 96), 0.0, False, 1e-5, True, (5.4e-14,) * 3), ((128, 128, 128), 0.0, False, 1e-6, False, (4.1e-14,) * 3),
+    ((192, 160, 96), 0.0, False, 1e-6, True, (5.9e-14,) * 3), ((384, 33, 96), 0.0, False, 1e-3, True, (8.3e-14,) * 3),
+    ((512, 48, 64), 0.5, True, 1.0, True, (2.9e-12, 3.4e-12, 3.5e-12))])
+def test_helmholtz_error(shape, beta, walls, c, smooth, bound):
+    from paper_2406_19920_amd import ibsolve as ibs
+    assert torch.cuda.is_available()
+    print("case refined helmholtz accuracy", shape, c, flush=True)
+    kw = dict(bc_x=ibs.IBS_DIRICHLET) if walls else {}
+    D = ibs.Solver(*shape, beta=beta, **kw)
+    S = ibs.Solver(*shape, beta=beta, precision=ibs.IBS_REFINED_BF16X3, **kw)
+    errs = [[], [], []]
+    for seed in range(8):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        r = [_smooth(S.shape(op), 10 * seed + op) if smooth else
+             torch.randn(S.shape(op), generator=g, dtype=torch.float64, device="cuda") for op in (1, 2, 3)]
+        want = D.helmholtz([0, 1, 2], [c] * 3, [t.clone() for t in r])
+        for q, (got, ref) in enumerate(zip(S.helmholtz([0, 1, 2], [c] * 3, r), want)):
+            errs[q].append(float((got - ref).norm() / ref.norm()))
+            assert S.read_info(q).status == 0
+    for e, most in zip(errs, bound):
+        assert np.exp(np.mean(np.log(e))) < most, errs
